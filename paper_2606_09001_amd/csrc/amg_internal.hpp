@@ -165,6 +165,8 @@ struct Ctl {
   double alpha, beta;
   double rho, omega;      // BiCGSTAB: <r^, r>, <t, s>/<t, t>
   double trr;             // true residual ||b - A x||^2
+  double* x;              // the solve's iterate (captured iterations find it here, so a replay is not tied to
+                          // the buffer it was captured with)
   int iters, maxiter;
   int done;               // nonzero: kernels of the current solve return at once
   int state;              // 0 running, 1 converged (recursive), 2 iteration limit, -1 breakdown
@@ -197,6 +199,7 @@ struct BatchHead {
   int W;
   int maxiter;
   int flexible;
+  double* x;     // the solve's iterates ([n][W]), as Ctl::x
 };
 struct BatchLevel {
   DBuf<double> x64, b64, r64;
@@ -230,8 +233,6 @@ struct Graphs {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipGraphExec_t exec[2] = {nullptr, nullptr};   // pair of iterations, by direction-buffer parity
   hipGraphExec_t bexec = nullptr;                 // one BiCGSTAB iteration
-  const void* key_x = nullptr;
-  const void* key_bx = nullptr;
   int key_flex = -1;
   int key_w = 0;
   void reset();

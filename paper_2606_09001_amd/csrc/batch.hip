@@ -591,12 +591,13 @@ __global__ void __launch_bounds__(kBlock) k_winit(int n, int W, const double* __
 
 // Active columns: x += alpha p, r -= alpha q, x0 = sw o r, <r, r>.
 template <int LW, bool SYS, class T>
-__global__ void __launch_bounds__(kBlock) k_wupdate(int n, int W, double* __restrict__ x, double* __restrict__ r,
+__global__ void __launch_bounds__(kBlock) k_wupdate(int n, int W, double* __restrict__ r,
                                                     const double* __restrict__ p, const double* __restrict__ q,
                                                     const T* __restrict__ sw, T* __restrict__ x0,
                                                     const WCtl* __restrict__ ctl, const BatchHead* __restrict__ head,
                                                     double* __restrict__ partials) {
   if (head->ndone >= head->W) return;
+  double* __restrict__ x = head->x;
   constexpr int RB = kBlock / LW;
   const int lr = threadIdx.x / LW, c = threadIdx.x & (LW - 1);
   const int64_t groups = ((int64_t)n + RB - 1) / RB;
@@ -696,11 +697,12 @@ __device__ inline void finish_column(WCtl& cc, BatchHead* head, int state) {
   atomicAdd(&head->ndone, 1);
 }
 
-__global__ void k_whead_reset(BatchHead* head, int W, int maxiter, int flexible) {
+__global__ void k_whead_reset(BatchHead* head, int W, int maxiter, int flexible, double* x) {
   head->ndone = 0;
   head->W = W;
   head->maxiter = maxiter;
   head->flexible = flexible;
+  head->x = x;
 }
 
 __global__ void __launch_bounds__(kWFin) k_wfin_init(WCtl* ctl, BatchHead* head, const double* __restrict__ partials,
@@ -1379,16 +1381,15 @@ amg_status solve_wide_impl(Hierarchy& H, const SolveOpts& o, const double* d_b, 
     AMG_HIP(hipEventRecord(H.gr.ev_in, caller));
     AMG_HIP(hipStreamWaitEvent(H.gr.gs, H.gr.ev_in, 0));
     s = H.gr.gs;
-    if (H.gr.key_x != d_x || H.gr.key_flex != flexible || H.gr.key_w != W) {
+    if (H.gr.key_flex != flexible || H.gr.key_w != W) {
       H.gr.reset();
-      H.gr.key_x = d_x;
       H.gr.key_flex = flexible;
       H.gr.key_w = W;
     }
   }
   double* part = B.partials.p;
   const int gw = wide_grid(n, LWv);
-  hipLaunchKernelGGL(k_whead_reset, dim3(1), dim3(1), 0, s, B.head.p, W, o.maxiter, flexible);
+  hipLaunchKernelGGL(k_whead_reset, dim3(1), dim3(1), 0, s, B.head.p, W, o.maxiter, flexible, d_x);
   AMG_DISPATCH_LW(LWv, hipLaunchKernelGGL((k_winit<LW>), dim3(gw), dim3(kBlock), 0, s, n, W, d_b, B.r.p, d_x, part));
   hipLaunchKernelGGL(k_wfin_init, dim3(W), dim3(kWFin), 0, s, B.ctl.p, B.head.p, part, W, gw, tol);
   AMG_HIP(hipGetLastError());
@@ -1408,7 +1409,7 @@ amg_status solve_wide_impl(Hierarchy& H, const SolveOpts& o, const double* d_b, 
     hipLaunchKernelGGL(k_wfin_alpha, dim3(W), dim3(kWFin), 0, stq, B.ctl.p, B.head.p, part, W, np);
     {
       WInstScope is(H, KID_CG_UPDATE, 0, stq);
-      AMG_DISPATCH_LW(LWv, hipLaunchKernelGGL((k_wupdate<LW, SYS, T>), dim3(gw), dim3(kBlock), 0, stq, n, W, d_x,
+      AMG_DISPATCH_LW(LWv, hipLaunchKernelGGL((k_wupdate<LW, SYS, T>), dim3(gw), dim3(kBlock), 0, stq, n, W,
                                               B.r.p, pb[c ^ 1], B.q.p, WB<T>::sw(L0), x0, B.ctl.p, B.head.p, part));
     }
     hipLaunchKernelGGL(k_wfin_update, dim3(W), dim3(kWFin), 0, stq, B.ctl.p, B.head.p, part, W, gw);

@@ -29,8 +29,6 @@ void Graphs::reset() {
     (void)hipGraphExecDestroy(bexec);
     bexec = nullptr;
   }
-  key_x = nullptr;
-  key_bx = nullptr;
   key_flex = -1;
   key_w = 0;
 }

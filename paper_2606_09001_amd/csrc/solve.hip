@@ -566,12 +566,13 @@ __global__ void __launch_bounds__(kBlock) k_cg_init(int n, const double* __restr
 // x += alpha p ; r -= alpha q ; partial <r, r>; also the level-0
 // pre-smoothed iterate x0 = sw o r of the next V-cycle (cycle precision T).
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict__ x, double* __restrict__ r,
+__global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict__ r,
                                                       const double* __restrict__ p, const double* __restrict__ q,
                                                       const T* __restrict__ sw, T* __restrict__ x0,
                                                       const Ctl* __restrict__ ctl, double* __restrict__ partials) {
   if (ctl->done) return;
   const double alpha = ctl->alpha;
+  double* __restrict__ x = ctl->x;
   const int base = vec_base();
   double xv[kVecPer], rv[kVecPer], pv[kVecPer], qv[kVecPer];
   T wv[kVecPer];
@@ -711,13 +712,14 @@ __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restri
 
 // x += alpha y ; s = r - alpha v ; partial <s, s>; with x0 also x0 = sw o s.
 template <class T>
-__global__ void __launch_bounds__(kBlock) k_bi_half(int n, double* __restrict__ x, const double* __restrict__ y,
+__global__ void __launch_bounds__(kBlock) k_bi_half(int n, const double* __restrict__ y,
                                                     const double* __restrict__ r, const double* __restrict__ v,
                                                     double* __restrict__ sv, const T* __restrict__ sw,
                                                     T* __restrict__ x0, const Ctl* __restrict__ ctl,
                                                     double* __restrict__ partials) {
   if (ctl->done) return;
   const double alpha = ctl->alpha;
+  double* __restrict__ x = ctl->x;
   const int base = vec_base();
   double xv[kVecPer], yv[kVecPer], rv[kVecPer], vv[kVecPer];
   T wv[kVecPer];
@@ -746,12 +748,13 @@ __global__ void __launch_bounds__(kBlock) k_bi_half(int n, double* __restrict__ 
 }
 
 // x += omega z ; r = s - omega t ; partials <r, r>, <r^, r>.
-__global__ void __launch_bounds__(kBlock) k_bi_full(int n, double* __restrict__ x, const double* __restrict__ z,
+__global__ void __launch_bounds__(kBlock) k_bi_full(int n, const double* __restrict__ z,
                                                     const double* __restrict__ sv, const double* __restrict__ t,
                                                     const double* __restrict__ rh, double* __restrict__ r,
                                                     const Ctl* __restrict__ ctl, double* __restrict__ partials) {
   if (ctl->done) return;
   const double omega = ctl->omega;
+  double* __restrict__ x = ctl->x;
   const int base = vec_base();
   double xv[kVecPer], zv[kVecPer], sl[kVecPer], tv[kVecPer], hv[kVecPer];
 #pragma unroll
@@ -819,7 +822,7 @@ __device__ inline void fold_partials(const double* __restrict__ partials, int np
 }
 
 __global__ void __launch_bounds__(kFinBlock) k_fin_init(Ctl* ctl, const double* __restrict__ partials, int np,
-                                                        double tol, int maxiter, int flexible) {
+                                                        double tol, int maxiter, int flexible, double* x) {
   double t[1];
   fold_partials<1>(partials, np, t);
   if (threadIdx.x != 0) return;
@@ -829,6 +832,7 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_init(Ctl* ctl, const double* 
   ctl->iters = 0;
   ctl->maxiter = maxiter;
   ctl->flexible = flexible;
+  ctl->x = x;
   ctl->state = 0;
   ctl->done = 0;
   ctl->trr = 0.0;
@@ -915,7 +919,7 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_trr(Ctl* ctl, const double* _
 
 // BiCGSTAB scalars.  rho = <r^, r> (= ||b||^2 at the start, r^ = r = b).
 __global__ void __launch_bounds__(kFinBlock) k_bfin_init(Ctl* ctl, const double* __restrict__ partials, int np,
-                                                         double tol, int maxiter) {
+                                                         double tol, int maxiter, double* x) {
   double t[1];
   fold_partials<1>(partials, np, t);
   if (threadIdx.x != 0) return;
@@ -925,6 +929,7 @@ __global__ void __launch_bounds__(kFinBlock) k_bfin_init(Ctl* ctl, const double*
   ctl->iters = 0;
   ctl->maxiter = maxiter;
   ctl->flexible = 0;
+  ctl->x = x;
   ctl->state = 0;
   ctl->done = 0;
   ctl->trr = 0.0;
@@ -1696,9 +1701,9 @@ void pattern_grad(Hierarchy& H, const double* d_lam, const double* d_x, double* 
 }
 
 template <class T>
-void launch_cg_update(Hierarchy& H, const SolveWork& w, int n, double* d_x, const double* p, hipStream_t s) {
+void launch_cg_update(Hierarchy& H, const SolveWork& w, int n, const double* p, hipStream_t s) {
   Level& L0 = H.lv[0];
-  hipLaunchKernelGGL((k_cg_update<T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, d_x, w.r, p, w.q,
+  hipLaunchKernelGGL((k_cg_update<T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
                      Bufs<T>::sw(L0), Bufs<T>::x(L0), w.ctl, w.partials);
 }
 
@@ -1768,9 +1773,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
     AMG_HIP(hipEventRecord(H.gr.ev_in, caller));
     AMG_HIP(hipStreamWaitEvent(H.gr.gs, H.gr.ev_in, 0));
     s = H.gr.gs;
-    if (H.gr.key_x != d_x || H.gr.key_flex != flexible || H.gr.key_w != 1) {
+    if (H.gr.key_flex != flexible || H.gr.key_w != 1) {
       H.gr.reset();
-      H.gr.key_x = d_x;
       H.gr.key_flex = flexible;
       H.gr.key_w = 1;
     }
@@ -1779,7 +1783,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   double* part = w.partials;
   const int gv = vec_grid(n);
   hipLaunchKernelGGL(k_cg_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, w.r, d_x, part);
-  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, flexible);
+  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, flexible,
+                     d_x);
   AMG_HIP(hipGetLastError());
   // search directions alternate between two buffers (the fused direction
   // update writes the new p while neighbours still gather the old one)
@@ -1796,8 +1801,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
     hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kFinBlock), 0, st, ctl, part, np);
     {
       InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
-      if (H.fp32()) launch_cg_update<float>(H, w, n, d_x, pb[c ^ 1], st);
-      else launch_cg_update<double>(H, w, n, d_x, pb[c ^ 1], st);
+      if (H.fp32()) launch_cg_update<float>(H, w, n, pb[c ^ 1], st);
+      else launch_cg_update<double>(H, w, n, pb[c ^ 1], st);
     }
     hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
     CycleArgs a{w.r, w.z, w.q, ctl, part, flexible ? 2 : 1, 0, multi ? 1 : 0};
@@ -1938,11 +1943,6 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
     AMG_HIP(hipEventRecord(H.gr.ev_in, caller));
     AMG_HIP(hipStreamWaitEvent(H.gr.gs, H.gr.ev_in, 0));
     s = H.gr.gs;
-    if (H.gr.key_bx != d_x && H.gr.bexec) {
-      (void)hipGraphExecDestroy(H.gr.bexec);
-      H.gr.bexec = nullptr;
-    }
-    H.gr.key_bx = d_x;
   }
   Ctl* ctl = H.ctl.p;
   double* part = H.partials.p;
@@ -1962,7 +1962,7 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
   }
   const int gv = vec_grid(n);
   hipLaunchKernelGGL(k_bi_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, r, rh, d_x, part);
-  hipLaunchKernelGGL(k_bfin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter);
+  hipLaunchKernelGGL(k_bfin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, d_x);
   AMG_HIP(hipGetLastError());
   // with a multilevel cycle the vector kernels also write the level-0
   // pre-smoothed iterate of the V-cycle that follows them
@@ -1979,10 +1979,10 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
   auto launch_half = [&](hipStream_t st) {
     Level& L0c = H.lv[0];
     if (H.fp32())
-      hipLaunchKernelGGL(k_bi_half<float>, dim3(gv), dim3(kBlock), 0, st, n, d_x, y, r, v, sv, Bufs<float>::sw(L0c),
+      hipLaunchKernelGGL(k_bi_half<float>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv, Bufs<float>::sw(L0c),
                          x0w ? Bufs<float>::x(L0c) : nullptr, ctl, part);
     else
-      hipLaunchKernelGGL(k_bi_half<double>, dim3(gv), dim3(kBlock), 0, st, n, d_x, y, r, v, sv,
+      hipLaunchKernelGGL(k_bi_half<double>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv,
                          Bufs<double>::sw(L0c), x0w ? Bufs<double>::x(L0c) : nullptr, ctl, part);
   };
   auto iteration = [&](int first, hipStream_t st) {
@@ -2002,7 +2002,7 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
       np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<2>{L0.av(), z, t, sv}, ctl, part, st);
     }
     hipLaunchKernelGGL(k_bfin_omega, dim3(1), dim3(kFinBlock), 0, st, ctl, part, np);
-    hipLaunchKernelGGL(k_bi_full, dim3(gv), dim3(kBlock), 0, st, n, d_x, z, sv, t, rh, r, ctl, part);
+    hipLaunchKernelGGL(k_bi_full, dim3(gv), dim3(kBlock), 0, st, n, z, sv, t, rh, r, ctl, part);
     hipLaunchKernelGGL(k_bfin_full, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
   };
   int restarts = 0;
