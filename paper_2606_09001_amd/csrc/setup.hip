@@ -865,10 +865,10 @@ template <class F>
 void cub_call(F&& f, hipStream_t s) {
   size_t tmp = 0;
   AMG_HIP(f(nullptr, tmp));
-  DBuf<unsigned char> buf;
+  Arena::Scope scope;
+  TBuf<unsigned char> buf;
   buf.alloc((int64_t)std::max<size_t>(tmp, 1));
   AMG_HIP(f(buf.p, tmp));
-  AMG_HIP(hipStreamSynchronize(s));  // the temporary buffer is freed on return
 }
 
 // Exclusive scan of cnt[0..m) into out[0..m) (int).
@@ -888,7 +888,8 @@ int64_t read_i64(const int64_t* d, hipStream_t s) {
 bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, const int* xrp, const int* xci,
                        const int* yrp, const int* yci, int64_t budget, DBuf<int64_t>& off, DBuf<int2>& pairs,
                        hipStream_t s) {
-  DBuf<int64_t> cnt;
+  Arena::Scope scope;
+  TBuf<int64_t> cnt;
   cnt.alloc(cnnz + 1);
   hipLaunchKernelGGL(k_pm_count, dim3((unsigned)((cnnz + kBlock) / kBlock)), dim3(kBlock), 0, s, nrows, cnnz, crp, cci,
                      xrp, xci, yrp, yci, cnt.p);
@@ -904,7 +905,6 @@ bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, 
   pairs.alloc(std::max<int64_t>(total, 1));
   hipLaunchKernelGGL(k_pm_fill, dim3((unsigned)((cnnz + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, nrows, cnnz, crp,
                      cci, xrp, xci, yrp, yci, off.p, pairs.p);
-  AMG_HIP(hipStreamSynchronize(s));  // cnt is freed on return
   return true;
 }
 
@@ -949,7 +949,8 @@ void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
     return;
   }
   // general path: emit (i,j) and (j,i) for every strong entry, sort, unique
-  DBuf<int> cnt, off;
+  Arena::Scope scope;
+  TBuf<int> cnt, off;
   cnt.alloc(L.n + 1);
   off.alloc(L.n + 1);
   AMG_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int) * (L.n + 1), s));
@@ -957,8 +958,8 @@ void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
                      L.diagpos.p, H.prm.theta, cnt.p);
   exclusive_scan(cnt.p, off.p, L.n + 1, s);
   int m = read_int(off.p + L.n, s);
-  DBuf<unsigned long long> keys, sorted, uniq;
-  DBuf<int> nuniq;
+  TBuf<unsigned long long> keys, sorted, uniq;
+  TBuf<int> nuniq;
   nuniq.alloc(1);
   int64_t mm = std::max(m, 1);
   keys.alloc(mm);
@@ -985,8 +986,9 @@ void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
 // Returns the number of aggregates.
 int aggregate(Hierarchy& H, Level& L, hipStream_t s) {
   const int n = L.n;
-  DBuf<int8_t> state, e1;
-  DBuf<unsigned long long> m1;
+  Arena::Scope scope;
+  TBuf<int8_t> state, e1;
+  TBuf<unsigned long long> m1;
   state.alloc(n);
   e1.alloc(n);
   m1.alloc(n);
@@ -1006,7 +1008,7 @@ int aggregate(Hierarchy& H, Level& L, hipStream_t s) {
     if (H.h_flags[1] == 0) break;
   }
   L.mis_rounds = rounds;
-  DBuf<int> isroot, rank, agg2;
+  TBuf<int> isroot, rank, agg2;
   isroot.alloc(n + 1);
   rank.alloc(n + 1);
   agg2.alloc(n);
@@ -1024,13 +1026,13 @@ int aggregate(Hierarchy& H, Level& L, hipStream_t s) {
 }
 
 double gershgorin(Hierarchy& H, Level& L, int sy, hipStream_t s) {
-  DBuf<unsigned long long> r;
-  r.alloc(1);
-  AMG_HIP(hipMemsetAsync(r.p, 0, sizeof(unsigned long long), s));
-  hipLaunchKernelGGL(k_rho, dim3(grid_for(L.n)), dim3(kBlock), 0, s, L.n, L.rp.p, L.v.p + sy, H.S, L.diagpos.p, r.p);
+  // a slot of the flag block (64 bytes, the error flags use its front)
+  unsigned long long* r = reinterpret_cast<unsigned long long*>(H.flags.p + 8);
+  AMG_HIP(hipMemsetAsync(r, 0, sizeof(unsigned long long), s));
+  hipLaunchKernelGGL(k_rho, dim3(grid_for(L.n)), dim3(kBlock), 0, s, L.n, L.rp.p, L.v.p + sy, H.S, L.diagpos.p, r);
   AMG_HIP(hipGetLastError());
   unsigned long long bits = 0;
-  AMG_HIP(hipMemcpyAsync(&bits, r.p, sizeof(bits), hipMemcpyDeviceToHost, s));
+  AMG_HIP(hipMemcpyAsync(&bits, r, sizeof(bits), hipMemcpyDeviceToHost, s));
   AMG_HIP(hipStreamSynchronize(s));
   double rho;
   std::memcpy(&rho, &bits, sizeof(rho));
@@ -1053,8 +1055,9 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   L.rho = L.rhoS[0];
   L.omegaP = L.omegaPS[0];
   // P
+  Arena::Scope scope;
   if (symbolic) {
-    DBuf<int> cnt;
+    TBuf<int> cnt;
     cnt.alloc(n + 1);
     hipLaunchKernelGGL(k_p_count, dim3(grid_for(n + 1)), b, 0, s, n, L.rp.p, L.ci.p, L.agg.p, cnt.p);
     L.prp.alloc(n + 1);
@@ -1079,7 +1082,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   // R = P^T
   const int nc = L.nagg;
   if (symbolic) {
-    DBuf<int> rowid, iota, keys_out, cnt;
+    TBuf<int> rowid, iota, keys_out, cnt;
     rowid.alloc(L.pnnz);
     iota.alloc(L.pnnz);
     keys_out.alloc(L.pnnz);
@@ -1102,7 +1105,6 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     for (int sy = 0; sy < S; ++sy)
       hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.rperm.p, rowid.p, L.pv.p + sy, S,
                          sy == 0 ? L.rci.p : (int*)nullptr, L.rv.p + sy);
-    AMG_HIP(hipStreamSynchronize(s));
   } else {
     for (int sy = 0; sy < S; ++sy)
       hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.rperm.p, (const int*)nullptr,
@@ -1121,7 +1123,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   const bool wide_ap = symbolic && (double)L.nnz * (double)L.pnnz >= 64.0 * (double)n * (double)n;
   bool apmap = false;
   if (symbolic) {
-    DBuf<int> cnt;
+    TBuf<int> cnt;
     cnt.alloc(n + 1);
     if (wide_ap)
       hipLaunchKernelGGL(k_spgemm_sym_w<0>, dim3(n + 1), dim3(64), 0, s, n, L.rp.p, L.ci.p, L.prp.p, L.pci.p,
@@ -1165,7 +1167,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   Level& Lr = H.lv[l];  // re-fetch: emplace_back may reallocate
   if (symbolic) {
     C.n = nc;
-    DBuf<int> cnt;
+    TBuf<int> cnt;
     cnt.alloc(nc + 1);
     hipLaunchKernelGGL(k_spgemm_sym_w<0>, dim3(nc + 1), dim3(64), 0, s, nc, Lr.rrp.p, Lr.rci.p, Lr.aprp.p,
                        Lr.apci.p, (const int*)nullptr, cnt.p);
@@ -1234,15 +1236,16 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
   if (H.S != 1) return;
   for (size_t l = 0; l < H.lv.size(); ++l) {
     Level& L = H.lv[l];
+    Arena::Scope scope;
     if (build) {
       L.sell = false;
       L.sell_form = 0;
       const int ns = (L.n + 63) / 64;
-      DBuf<int> cnt;
+      TBuf<int> cnt;
       cnt.alloc(ns + 1);
       {
         // offset form first: every slice's offsets fit kSellMaxW slots
-        DBuf<int> uoff;
+        TBuf<int> uoff;
         uoff.alloc((int64_t)ns * kSellMaxW);
         hipLaunchKernelGGL(k_sello_count, dim3((ns + kBlock) / kBlock), dim3(kBlock), 0, s, L.n, ns, L.rp.p, L.ci.p,
                            cnt.p, uoff.p);
@@ -1268,13 +1271,12 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
           L.sell_len = tot;
           L.sell = true;
           L.sell_form = 2;
-          AMG_HIP(hipStreamSynchronize(s));  // uoff is freed on leaving this scope
         }
       }
     }
     if (build && !L.sell) {
       const int ns = (L.n + 63) / 64;
-      DBuf<int> cnt;
+      TBuf<int> cnt;
       cnt.alloc(ns + 1);
       hipLaunchKernelGGL(k_sell_width, dim3((ns + kBlock) / kBlock), dim3(kBlock), 0, s, L.n, ns, L.rp.p, cnt.p);
       std::vector<int> h(ns + 1);
@@ -1365,7 +1367,14 @@ bool values_equal(const Hierarchy& H, const double* d_val, int* d_flags, int* h_
 }
 
 void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const double* d_val, hipStream_t s) {
+  // everything of an earlier setup goes first: its buffers share the arena
   H.lv.clear();
+  H.co = Coarse();
+  for (DBuf<double>* b : {&H.r, &H.z, &H.p, &H.z2, &H.q, &H.partials}) b->release();
+  H.ctl.release();
+  H.arena.reset();
+  Arena scratch;
+  Arena::Use use(&H.arena, &scratch);
   H.lv.emplace_back();
   {
     Level& L0 = H.lv[0];
@@ -1412,7 +1421,8 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
 void transpose_csr_pattern(int n, int64_t nnz, const int* rp, const int* ci, DBuf<int>& trp, DBuf<int>& tci,
                            DBuf<int>& perm, hipStream_t s) {
   const dim3 b(kBlock);
-  DBuf<int> rowid, iota, keys_out, cnt;
+  Arena::Scope scope;
+  TBuf<int> rowid, iota, keys_out, cnt;
   rowid.alloc(std::max<int64_t>(nnz, 1));
   iota.alloc(std::max<int64_t>(nnz, 1));
   keys_out.alloc(std::max<int64_t>(nnz, 1));
