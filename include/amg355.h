@@ -338,6 +338,9 @@ enum {
   AMG_KERNEL_XPAY = 6,       /* (fused into AMG_KERNEL_SPMV_DOT; never launched) */
   AMG_KERNEL_COARSE = 7      /* dense coarsest solve */
 };
+/* Levels in the two-sweep form launch their down sweep as AMG_KERNEL_RESTRICT,
+ * their up sweep as AMG_KERNEL_POST, and neither PRE nor PROLONG; the dense
+ * product at the cycle's end is AMG_KERNEL_COARSE on the coarsest level. */
 
 /* Time every launch of one kernel at one level (level -1: all levels)
  * inside subsequent solves with HIP event pairs on the solve stream

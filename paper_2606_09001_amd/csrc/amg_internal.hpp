@@ -168,6 +168,19 @@ struct Shape {
   int max_block_nnz = 0;
 };
 
+// Sliced rows with G lanes per row: a slice is the 64/G rows of one wavefront;
+// lane l of the wave holds entries l%G, l%G + G, ... of row l/G, so step t of
+// the slice is one coalesced 64-lane load at off[s] + 64 t.  Every slice is
+// padded to its longest row (column -1).  src names the source of each entry
+// for value refreshes.
+struct Ell {
+  int n = 0, g = 1, slices = 0, grid = 0;
+  int64_t len = 0;
+  DBuf<int> off, col, src;
+  DBuf<double> v;
+  DBuf<float> v32;
+};
+
 struct Level {
   int n = 0;
   int64_t nnz = 0;
@@ -238,6 +251,22 @@ struct Level {
   DBuf<float> x32, b32, r32, xs32, rs32;
   // kernel shapes (see choose_shapes)
   Shape shA, shP, shR;
+  // Two-sweep form of the level's V(1,1) cycle (fused.hip): dn = R (I - A S)
+  // takes b_l to b_{l+1}; up = [2S - S A S | (I - S A) P] takes (b_l, x_{l+1})
+  // to x_l.  qv: (I - S A) P on the pattern of A P; dtv: dn transposed on that
+  // pattern (empty when it equals qv); dperm: entry of dn's rows -> entry of
+  // A P; tpos: position of (j, i) for entry (i, j) of A (nonsymmetric values)
+  Ell up, dn;
+  DBuf<double> qv, dtv, apt;
+  DBuf<int> drp, dci, dperm, tpos;
+};
+
+// The coarse end of the two-sweep cycle as one dense matrix: x_lx = X b_lb.
+struct Tail {
+  int lb = 0, lx = 0, rows = 0, cols = 0, ld = 0;
+  const double* X = nullptr;  // row-major, in one of w or the coarsest inverse itself
+  DBuf<float> X32;
+  DBuf<double> w[3];          // products on the way (kept for value refreshes)
 };
 
 struct Coarse {
@@ -260,6 +289,8 @@ struct Ctl {
   double trr;             // true residual ||b - A x||^2
   double* x;              // the solve's iterate (captured iterations find it here, so a replay is not tied to
                           // the buffer it was captured with)
+  double rz2[2];          // folded solves: <r,z> by direction-buffer parity
+  int it2[2];             // folded solves: iterations by direction-buffer parity
   int iters, maxiter;
   int done;               // nonzero: kernels of the current solve return at once
   int state;              // 0 running, 1 converged (recursive), 2 iteration limit, -1 breakdown
@@ -343,6 +374,9 @@ struct Hierarchy {
   Arena arena;  // buffers of the levels, the coarsest solve and the solve workspace
   std::vector<Level> lv;
   Coarse co;
+  // levels lf .. run the two-sweep cycle (lf = number of levels: none)
+  int lf = 1 << 30;
+  Tail tail;
   // solve workspace (level 0, FP64); BiCGSTAB adds r^, v, y, s, t
   DBuf<double> r, z, p, z2, q;
   DBuf<double> rh, bv, by, bs, bt2;
@@ -452,6 +486,16 @@ void apply_vcycle(Hierarchy& H, const double* d_r, double* d_z, hipStream_t s);
 void pattern_grad(Hierarchy& H, const double* d_lam, const double* d_x, double* d_g, hipStream_t s);
 void graph_stream(Hierarchy& H);
 void capture_graph(hipStream_t s, hipGraphExec_t& ex, const std::function<void()>& body);
+// fused.hip: two-sweep levels.  build: pattern part and values; else values only.
+void fused_levels(Hierarchy& H, bool build, hipStream_t s);
+// x_lf = V-cycle from level lf on: b = the right-hand side of level lf in the
+// cycle precision; out = its result (level 0: z in FP64, with the <r, z> and
+// <z, q> partials of `red`; null otherwise: the level's x buffer).  Returns
+// the partials written per reduced value.
+template <class T>
+int fused_cycle(Hierarchy& H, const T* b, const double* r, double* z, const double* q, int red, const Ctl* ctl,
+                double* partials, hipStream_t s);
+double fused_bytes(const Hierarchy& H, int kid, int level);
 // small.hip
 bool small_solve_ok(Hierarchy& H);
 amg_status pcg_solve_small(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const double* d_b, double* d_x,
@@ -467,6 +511,17 @@ double kernel_bytes(const Hierarchy& H, int kid, int level, int flexible);
 double iteration_bytes(const Hierarchy& H, int flexible);
 void set_instrument(Hierarchy& H, int kid, int level);
 void read_instrument(Hierarchy& H, int* launches, double* total_ms, double* min_ms, double* max_ms);
+
+// Records an event pair around a launch when (kernel, level) is instrumented,
+// and, before the pair, the solve's done flag: a launch that starts with the
+// flag set returns at once and is left out of the statistics.
+struct InstScope {
+  Hierarchy& H;
+  hipStream_t s;
+  bool on;
+  InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const Ctl* ctl);
+  ~InstScope();
+};
 
 // ------------------------------------------------------- device helpers
 

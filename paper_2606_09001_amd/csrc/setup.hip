@@ -1370,6 +1370,7 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   // everything of an earlier setup goes first: its buffers share the arena
   H.lv.clear();
   H.co = Coarse();
+  H.tail = Tail();
   for (DBuf<double>* b : {&H.r, &H.z, &H.p, &H.z2, &H.q, &H.partials}) b->release();
   H.ctl.release();
   H.arena.reset();
@@ -1406,6 +1407,7 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   if (H.prm.precondition) coarse_setup(H, s);
   precision_copies(H, s);
   sliced_copies(H, true, s);
+  fused_levels(H, true, s);
   alloc_cycle_vectors(H);
   choose_shapes(H, s);
   alloc_solve_workspace(H);
@@ -1494,6 +1496,7 @@ void refresh_hierarchy(Hierarchy& H, const double* d_val, hipStream_t s) {
   if (H.prm.precondition) coarse_setup(H, s);
   precision_copies(H, s);
   sliced_copies(H, false, s);
+  fused_levels(H, false, s);
   AMG_HIP(hipStreamSynchronize(s));
 }
 

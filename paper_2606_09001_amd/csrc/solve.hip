@@ -66,6 +66,54 @@ inline int round8(int64_t g) {
 //                                 their latency overlaps the matrix stream)
 //   void epi(row, s, in, d[])     consumes the row sum s; d[] collects dot partials
 //   static constexpr int NRED     number of dot products reduced
+// and, with kFold, folds the partial sums of earlier kernels itself (see Fold).
+
+// Scalars from partial sums without a finalize launch.  On systems of a few
+// 100,000 rows a single-workgroup finalize kernel costs 2.7 us of an iteration
+// of ten kernels, almost all of it launch and load latency.  With at most
+// kFoldMax partials per sum every workgroup of the consuming kernel sums them
+// itself: the loads go out before the kernel's own (fold_load), the wave sums
+// are combined after its gathers (fold_total), in one fixed order, so every
+// workgroup holds the same bits.  2048 partials are 16 KB per workgroup from
+// L2; beyond that the finalize kernels stay.
+constexpr int kFoldMax = 2048;
+
+struct NoFold {};
+
+// Sum over the workgroup's threads of np partials: per-thread sum.
+__device__ inline double fold_load(const double* __restrict__ p, int np) {
+  if (np <= kBlock) {
+    const double a = p[min((int)threadIdx.x, np - 1)];
+    return (int)threadIdx.x < np ? a : 0.0;
+  }
+  double a[kFoldMax / kBlock];
+#pragma unroll
+  for (int u = 0; u < kFoldMax / kBlock; ++u) a[u] = p[min((int)threadIdx.x + u * kBlock, np - 1)];
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < kFoldMax / kBlock; ++u) s = (int)threadIdx.x + u * kBlock < np ? s + a[u] : s;
+  return s;
+}
+
+// Combines NV per-thread sums; every thread gets the totals.  Two barriers.
+template <int NV>
+__device__ inline void fold_total(double (&v)[NV]) {
+  __shared__ double fold_red[NV][kBlock / 64];
+#pragma unroll
+  for (int m = 0; m < NV; ++m) {
+    const double t = group_sum<64>(v[m]);
+    if ((threadIdx.x & 63) == 63) fold_red[m][threadIdx.x >> 6] = t;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < NV; ++m) {
+    double s = fold_red[m][0];
+#pragma unroll
+    for (int k = 1; k < kBlock / 64; ++k) s += fold_red[m][k];
+    v[m] = s;
+  }
+  __syncthreads();
+}
 
 // Direction update fused with the product: p' = z + beta p (p' = z on the
 // first iteration of a (re)start) and q' = A p', <p', q'>.  q' is formed as
@@ -100,6 +148,106 @@ struct OpSpmvXpayDev {
     d[0] += a.pr * qn;
   }
 };
+
+// The same sweep in a folded solve: beta, the convergence test of the last
+// update and the <r, z> test come from the partials of that update (pu) and of
+// the V-cycle (pz) instead of from finalize kernels.  Workgroup 0 records the
+// outcome; what other workgroups read of the control block (rz2[par], it2[par],
+// pq) is not written in this kernel, and a workgroup that sees `done` set by
+// workgroup 0 would have found the same outcome itself.
+struct OpSpmvFold {
+  using PT = double;
+  static constexpr int NRED = 1;
+  static constexpr bool kFold = true;
+  const double* v;
+  const double* z;
+  const double* p;
+  double* pn;
+  double* q;
+  Ctl* ctl;
+  const double* pz;
+  const double* pu;
+  int npz, npu, nz, first, par;
+  struct Fold {
+    double s[3], rz, pq, thresh;
+    int it, maxiter, flexible;
+  };
+  struct Row {
+    double z, p, q;
+  };
+  __device__ PT prod_v(double a, int j) const { return a * z[j]; }
+  __device__ PT prod(int k, int j) const { return prod_v(v[k], j); }
+  __device__ Row row_in(int row) const { return {z[row], first ? 0.0 : p[row], first ? 0.0 : q[row]}; }
+  __device__ Fold fold_in() const {
+    Fold f;
+    f.s[0] = fold_load(pz, npz);
+    f.s[1] = nz > 1 ? fold_load(pz + npz, npz) : 0.0;
+    f.s[2] = first ? 0.0 : fold_load(pu, npu);
+    f.rz = ctl->rz2[par];
+    f.pq = ctl->pq;
+    f.thresh = ctl->thresh;
+    f.it = ctl->it2[par];
+    f.maxiter = ctl->maxiter;
+    f.flexible = ctl->flexible;
+    return f;
+  }
+  // beta of this iteration; false when the solve ends here
+  __device__ bool fold_out(Fold& f, double& beta) const {
+    fold_total<3>(f.s);
+    const double rzn = f.s[0], rr = f.s[2];
+    int st = 0, it = f.it;
+    if (!first) {
+      ++it;
+      if (rr <= f.thresh) st = 1;
+      else if (!(rr == rr)) st = -1;
+      else if (it >= f.maxiter) st = 2;
+    }
+    if (st == 0 && !(rzn > 0.0)) st = -1;
+    beta = first ? 0.0 : f.flexible ? -f.s[1] / f.pq : rzn / f.rz;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      ctl->rz2[par ^ 1] = rzn;
+      ctl->it2[par ^ 1] = it;
+      if (!first) ctl->rr = rr;
+      if (st) {
+        ctl->iters = it;
+        ctl->state = st;
+        ctl->done = 1;
+      }
+    }
+    return st == 0;
+  }
+  __device__ void epi_fold(int row, PT s, const Row& a, double beta, double* d) const {
+    const double pr = first ? a.z : a.z + beta * a.p;
+    const double qn = first ? s : s + beta * a.q;
+    pn[row] = pr;
+    q[row] = qn;
+    d[0] += pr * qn;
+  }
+};
+
+template <class Op, class = void>
+struct HasFold : std::false_type {};
+template <class Op>
+struct HasFold<Op, std::void_t<typename Op::Fold>> : std::true_type {};
+
+// The folding hooks of a sweep: fin before its own loads, fout and the row
+// epilogue after its row sums (nothing for operators that do not fold).
+template <class Op>
+__device__ inline auto fold_in(const Op& op) {
+  if constexpr (HasFold<Op>::value) return op.fold_in();
+  else return NoFold{};
+}
+template <class Op, class F>
+__device__ inline bool fold_out(const Op& op, F& f, double& beta) {
+  if constexpr (HasFold<Op>::value) return op.fold_out(f, beta);
+  else return true;
+}
+template <class Op>
+__device__ inline void row_epi(const Op& op, int row, typename Op::PT s, const typename Op::Row& in, double beta,
+                               double* d) {
+  if constexpr (HasFold<Op>::value) op.epi_fold(row, s, in, beta, d);
+  else op.epi(row, s, in, d);
+}
 
 // r = b - A x, ||r||^2
 struct OpTrueResid {
@@ -310,6 +458,7 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
   using PT = typename Op::PT;
   __shared__ int s_rp[RB + 1];
   __shared__ PT s_p[kBlock * U];
+  auto fold = fold_in(op);
   const int r0 = logical_block() * RB;
   for (int t = threadIdx.x; t <= RB; t += kBlock) s_rp[t] = rp[min(r0 + t, n)];
   const int lr = threadIdx.x / G3, lane = threadIdx.x & (G3 - 1);
@@ -341,8 +490,9 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
     for (int k = s_rp[lr] - k0 + lane; k < e; k += G3) s += s_p[k];
   }
   s = group_sum<G3>(s);
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {};
-  if (row < n && group_leader<G3>()) op.epi(row, s, in, d);
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
+  if (!fold_out(op, fold, beta)) return;
+  if (row < n && group_leader<G3>()) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
 }
 
@@ -353,7 +503,9 @@ __global__ void __launch_bounds__(kBlock) k_vec(int n, const int* __restrict__ r
   using PT = typename Op::PT;
   constexpr int RB = kBlock / G;
   const int lr = threadIdx.x / G, lane = threadIdx.x & (G - 1);
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {};
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
+  auto fold = fold_in(op);
+  if (!fold_out(op, fold, beta)) return;
   constexpr int U = 4;
   for (int r0 = logical_block() * RB; r0 < n; r0 += gridDim.x * RB) {
     const int row = r0 + lr;
@@ -375,7 +527,7 @@ __global__ void __launch_bounds__(kBlock) k_vec(int n, const int* __restrict__ r
       }
     }
     s = group_sum<G>(s);
-    if (row < n && group_leader<G>()) op.epi(row, s, in, d);
+    if (row < n && group_leader<G>()) row_epi(op, row, s, in, beta, d);
   }
   publish_partials<Op::NRED>(d, partials);
 }
@@ -388,16 +540,19 @@ __global__ void __launch_bounds__(kBlock) k_vec(int n, const int* __restrict__ r
 template <bool NT, class Op>
 __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ soff, const int* __restrict__ sci,
                                                  Op op, const Ctl* __restrict__ ctl, double* __restrict__ partials) {
-  if ((ctl && ctl->done) || n <= 0) return;
+  if (n <= 0) return;
   using PT = typename Op::PT;
   const int row = logical_block() * kBlock + threadIdx.x;
   const int rc = min(row, n - 1);
-  const typename Op::Row in = op.row_in(rc);
   // the wave's 64 rows are one slice: its offsets are scalar loads, which
-  // leave the vector loads of the row operands in flight
+  // leave the vector loads of the row operands in flight; the done flag is
+  // loaded beside them
   const int sl = __builtin_amdgcn_readfirstlane(rc >> 6), lane = rc & 63;
   const int off = soff[sl];
   const int w = (soff[sl + 1] - off) >> 6;
+  if (ctl && ctl->done) return;
+  auto fold = fold_in(op);
+  const typename Op::Row in = op.row_in(rc);
   int col[kSellMaxW];
   typename std::remove_const<typename std::remove_pointer<decltype(op.v)>::type>::type val[kSellMaxW];
 #pragma unroll
@@ -412,8 +567,9 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
   PT s = 0;
 #pragma unroll
   for (int j = 0; j < kSellMaxW; ++j) s = j < w && col[j] >= 0 ? s + pv[j] : s;
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {};
-  if (row < n) op.epi(row, s, in, d);
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
+  if (!fold_out(op, fold, beta)) return;
+  if (row < n) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
 }
 
@@ -424,15 +580,17 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
 template <bool NT, class Op>
 __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__ soff, const int4* __restrict__ slots,
                                                   Op op, const Ctl* __restrict__ ctl, double* __restrict__ partials) {
-  if ((ctl && ctl->done) || n <= 0) return;
+  if (n <= 0) return;
   using PT = typename Op::PT;
   const int row = logical_block() * kBlock + threadIdx.x;
   const int rc = min(row, n - 1);
-  const typename Op::Row in = op.row_in(rc);
   const int sl = __builtin_amdgcn_readfirstlane(rc >> 6), lane = rc & 63;
   const int off = soff[sl];
   const int w = (soff[sl + 1] - off) >> 6;
   const int sb = off >> 6;
+  if (ctl && ctl->done) return;
+  auto fold = fold_in(op);
+  const typename Op::Row in = op.row_in(rc);
   typename std::remove_const<typename std::remove_pointer<decltype(op.v)>::type>::type val[kSellMaxW];
 #pragma unroll
   for (int j = 0; j < kSellMaxW; ++j) val[j] = stream_load<NT>(op.v + off + min(j, w - 1) * 64 + lane);
@@ -455,8 +613,9 @@ __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__
   PT s = 0;
 #pragma unroll
   for (int j = 0; j < kSellMaxW; ++j) s = has[j] ? s + pv[j] : s;
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {};
-  if (row < n) op.epi(row, s, in, d);
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
+  if (!fold_out(op, fold, beta)) return;
+  if (row < n) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
 }
 
@@ -563,9 +722,19 @@ __global__ void __launch_bounds__(kBlock) k_cg_init(int n, const double* __restr
   publish_partials<1>(d, partials);
 }
 
-// x += alpha p ; r -= alpha q ; partial <r, r>; also the level-0
-// pre-smoothed iterate x0 = sw o r of the next V-cycle (cycle precision T).
-template <class T>
+// What the vector kernels write for the V-cycle that follows them: its
+// level-0 pre-smoothed iterate x0 = sw o r, the right-hand side rounded to the
+// cycle precision (two-sweep level 0), or nothing (the cycle reads r itself).
+enum X0Mode { X0_NONE = 0, X0_SMOOTHED = 1, X0_COPY = 2 };
+
+X0Mode x0_mode(const Hierarchy& H) {
+  if (!H.prm.precondition || H.lv.size() < 2) return X0_NONE;
+  if (H.lf > 0) return X0_SMOOTHED;
+  return H.fp32() ? X0_COPY : X0_NONE;
+}
+
+// x += alpha p ; r -= alpha q ; partial <r, r>; and x0 (see X0Mode).
+template <int MODE, class T>
 __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict__ r,
                                                       const double* __restrict__ p, const double* __restrict__ q,
                                                       const T* __restrict__ sw, T* __restrict__ x0,
@@ -584,7 +753,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict_
     rv[u] = ok ? r[i] : 0.0;
     pv[u] = ok ? p[i] : 0.0;
     qv[u] = ok ? q[i] : 0.0;
-    wv[u] = ok ? sw[i] : (T)0;
+    if constexpr (MODE == X0_SMOOTHED) wv[u] = ok ? sw[i] : (T)0;
   }
   double d[1] = {0.0};
 #pragma unroll
@@ -594,11 +763,64 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict_
       x[i] = xv[u] + alpha * pv[u];
       const double ri = rv[u] - alpha * qv[u];
       r[i] = ri;
-      x0[i] = wv[u] * (T)ri;
+      if constexpr (MODE == X0_SMOOTHED) x0[i] = wv[u] * (T)ri;
+      if constexpr (MODE == X0_COPY) x0[i] = (T)ri;
       d[0] += ri * ri;
     }
   }
   publish_partials<1>(d, partials);
+}
+
+// The same update in a folded solve: alpha from the product sweep's partials
+// (pa), <r, z> of parity par ^ 1 as that sweep recorded it; its own partials go
+// to pu.  Workgroup 0 records <p, q> and a breakdown.
+template <int MODE, class T>
+__global__ void __launch_bounds__(kBlock) k_cg_update_fold(int n, double* __restrict__ r, const double* __restrict__ p,
+                                                           const double* __restrict__ q, T* __restrict__ x0, Ctl* ctl,
+                                                           const double* __restrict__ pa, int npa,
+                                                           double* __restrict__ pu, int par) {
+  const int done = ctl->done;
+  const double rz = ctl->rz2[par ^ 1];
+  const int it = ctl->it2[par ^ 1];
+  double* __restrict__ x = ctl->x;
+  if (done) return;
+  double f[1] = {fold_load(pa, npa)};
+  const int base = vec_base();
+  double xv[kVecPer], rv[kVecPer], pv[kVecPer], qv[kVecPer];
+#pragma unroll
+  for (int u = 0; u < kVecPer; ++u) {
+    const int i = min(base + (int)threadIdx.x + u * kBlock, n - 1);
+    rv[u] = r[i];
+    pv[u] = p[i];
+    qv[u] = q[i];
+    xv[u] = x[i];
+  }
+  fold_total<1>(f);
+  const double pq = f[0];
+  const bool ok = pq > 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctl->pq = pq;
+    if (!ok) {
+      ctl->iters = it;
+      ctl->state = -1;
+      ctl->done = 1;
+    }
+  }
+  if (!ok) return;
+  const double alpha = rz / pq;
+  double d[1] = {0.0};
+#pragma unroll
+  for (int u = 0; u < kVecPer; ++u) {
+    const int i = base + threadIdx.x + u * kBlock;
+    if (i < n) {
+      x[i] = xv[u] + alpha * pv[u];
+      const double ri = rv[u] - alpha * qv[u];
+      r[i] = ri;
+      if constexpr (MODE == X0_COPY) x0[i] = (T)ri;
+      d[0] += ri * ri;
+    }
+  }
+  publish_partials<1>(d, pu);
 }
 
 // z = r (the identity preconditioner of plain CG).
@@ -613,7 +835,8 @@ __global__ void __launch_bounds__(kBlock) k_copy_z(int n, const double* __restri
   }
 }
 
-// x0 = sw o r (first V-cycle of a solve or restart).
+// x0 = sw o r, or r rounded to T when there is no sw (first V-cycle of a
+// solve or restart).
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_sw_mul(int n, const T* __restrict__ sw, const double* __restrict__ r,
                                                    T* __restrict__ x0, const Ctl* __restrict__ ctl) {
@@ -622,7 +845,7 @@ __global__ void __launch_bounds__(kBlock) k_sw_mul(int n, const T* __restrict__ 
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
-    if (i < n) x0[i] = sw[i] * (T)r[i];
+    if (i < n) x0[i] = sw ? sw[i] * (T)r[i] : (T)r[i];
   }
 }
 
@@ -680,7 +903,8 @@ __global__ void __launch_bounds__(kBlock) k_bi_init(int n, const double* __restr
 
 // p = r on the first iteration of a (re)start, else p = r + beta (p - omega v);
 // with x0, also the next V-cycle's level-0 pre-smoothed iterate x0 = sw o p
-// (cycle precision T), so that its first sweep only forms the residual.
+// (cycle precision T), so that its first sweep only forms the residual, or,
+// without sw, p rounded to T.
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restrict__ r,
                                                    const double* __restrict__ v, double* __restrict__ p,
@@ -697,7 +921,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restri
     rv[u] = r[i];
     vv[u] = v[i];
     pv[u] = p[i];
-    wv[u] = x0 ? sw[i] : (T)0;
+    wv[u] = x0 && sw ? sw[i] : (T)1;
   }
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
@@ -730,7 +954,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_half(int n, const double* __restr
     yv[u] = y[i];
     rv[u] = r[i];
     vv[u] = v[i];
-    wv[u] = x0 ? sw[i] : (T)0;
+    wv[u] = x0 && sw ? sw[i] : (T)1;
   }
   double d[1] = {0.0};
 #pragma unroll
@@ -830,6 +1054,7 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_init(Ctl* ctl, const double* 
   ctl->bb = bb;
   ctl->thresh = (tol * tol) * bb;
   ctl->iters = 0;
+  ctl->it2[0] = ctl->it2[1] = 0;
   ctl->maxiter = maxiter;
   ctl->flexible = flexible;
   ctl->x = x;
@@ -880,6 +1105,24 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_update(Ctl* ctl, const double
     ctl->done = 1;
   } else if (ctl->iters >= ctl->maxiter) {
     ctl->state = 2;
+    ctl->done = 1;
+  }
+}
+
+// Folded solve, end of a chunk of iterations: the outcome of its last update
+// (of parity par) for the host; the next product sweep would find the same.
+__global__ void __launch_bounds__(kFinBlock) k_fin_chunk(Ctl* ctl, const double* __restrict__ pu, int np, int par) {
+  if (ctl->done) return;
+  double t[1];
+  fold_partials<1>(pu, np, t);
+  if (threadIdx.x != 0) return;
+  const double rr = t[0];
+  const int it = ctl->it2[par ^ 1] + 1;
+  ctl->rr = rr;
+  ctl->iters = it;
+  const int st = rr <= ctl->thresh ? 1 : !(rr == rr) ? -1 : it >= ctl->maxiter ? 2 : 0;
+  if (st) {
+    ctl->state = st;
     ctl->done = 1;
   }
 }
@@ -1037,6 +1280,7 @@ __global__ void k_bi_restart(Ctl* ctl) {
 __global__ void k_ctl_restart(Ctl* ctl) {
   ctl->done = 0;
   ctl->state = 0;
+  ctl->it2[0] = ctl->it2[1] = ctl->iters;
 }
 
 void launch_fin_beta(Ctl* ctl, double* partials, int np, int first, int nv, hipStream_t s) {
@@ -1051,29 +1295,6 @@ __global__ void k_snap_done(const Ctl* ctl, int* dst) {
   if (threadIdx.x == 0) dst[0] = ctl ? ctl->done : 0;
 }
 
-// Records an event pair around a launch when (kernel, level) is instrumented,
-// and, before the pair, the solve's done flag: a launch that starts with the
-// flag set returns at once and is left out of the statistics.
-struct InstScope {
-  Hierarchy& H;
-  hipStream_t s;
-  bool on;
-  InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const Ctl* ctl) : H(h), s(st) {
-    on = H.inst.kernel == kid && (H.inst.level == level || H.inst.level < 0) &&
-         2 * (H.inst.used + 1) <= (int)H.inst.ev.size();
-    if (on) {
-      hipLaunchKernelGGL(k_snap_done, dim3(1), dim3(64), 0, s, ctl, H.inst.was_done.p + H.inst.used);
-      AMG_HIP(hipEventRecord(H.inst.ev[2 * H.inst.used], s));
-    }
-  }
-  ~InstScope() {
-    if (on) {
-      (void)hipEventRecord(H.inst.ev[2 * H.inst.used + 1], s);
-      ++H.inst.used;
-    }
-  }
-};
-
 struct CycleArgs {
   const double* r0;   // level-0 right-hand side (CG residual), FP64
   double* z0;         // level-0 result, FP64
@@ -1082,7 +1303,8 @@ struct CycleArgs {
   double* partials;
   int red;            // 0 none, 1 <r,z>, 2 <r,z> and <z,q>
   int first;
-  int x0_ready;       // level-0 x = sw o r0 already written
+  int x0_ready;       // what the cycle starts from (X0Mode) already written
+  int fold = 0;       // the partials' consumer folds them: no finalize launch
 };
 
 template <class T>
@@ -1137,8 +1359,9 @@ void launch_prolong(Hierarchy& H, Level& L, const T* xc, T* x, const Ctl* ctl, h
 // With a.red, the level-0 post-smoother emits the <r,z> (and <z,q>) partials
 // and the finalize kernel forms beta.  Extra smoothing sweeps (nu > 1)
 // ping-pong through the level's spare buffers.
+// Returns the number of partials per reduced value.
 template <class T>
-void vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
+int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
   const int nl = (int)H.lv.size();
   Coarse& C = H.co;
   Ctl* ctl = a.ctl;
@@ -1151,7 +1374,7 @@ void vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
       hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, n, a.r0, a.z0, a.q ? a.q : a.z0, ctl, a.partials);
       launch_fin_beta(ctl, a.partials, g, a.first, 2, s);
     }
-    return;
+    return 0;
   }
   if (nl == 1) {
     {
@@ -1164,14 +1387,29 @@ void vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
       hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, C.n, a.r0, a.z0, a.q ? a.q : a.z0, ctl, a.partials);
       launch_fin_beta(ctl, a.partials, g, a.first, 2, s);
     }
-    return;
+    return 0;
+  }
+  const int lf = H.lf;  // levels from here on run the two-sweep cycle
+  if (lf == 0) {
+    const T* b0;
+    if constexpr (std::is_same<T, double>::value) {
+      b0 = a.r0;
+    } else {
+      T* c = Bufs<T>::x(H.lv[0]);
+      if (!a.x0_ready)
+        hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(H.n)), dim3(kBlock), 0, s, H.n, (const T*)nullptr, a.r0, c, ctl);
+      b0 = c;
+    }
+    const int np = fused_cycle<T>(H, b0, a.r0, a.z0, a.q, a.red, ctl, a.partials, s);
+    if (a.red && !a.fold) launch_fin_beta(ctl, a.partials, np, a.first, a.red, s);
+    return np;
   }
   T* cx[AMG_MAX_LEVELS];
   T* cr[AMG_MAX_LEVELS];
   T* sx[AMG_MAX_LEVELS];
   T* sr[AMG_MAX_LEVELS];
   const int npre = H.prm.nu_pre, npost = H.prm.nu_post;
-  for (int l = 0; l < nl - 1; ++l) {
+  for (int l = 0; l < lf; ++l) {
     Level& L = H.lv[l];
     cx[l] = Bufs<T>::x(L);
     cr[l] = Bufs<T>::r(L);
@@ -1204,20 +1442,20 @@ void vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
     {
       InstScope is(H, KID_RESTRICT, l, s, a.ctl);
       Level& Ln = H.lv[l + 1];
-      const bool coarsest = (l + 1 == nl - 1);
-      launch_restrict<T>(H, L, cr[l], Bufs<T>::b(Ln), coarsest ? nullptr : Bufs<T>::sw(Ln),
-                         coarsest ? nullptr : Bufs<T>::x(Ln), ctl, s);
+      const bool last = (l + 1 == lf);  // the two-sweep levels start from b
+      launch_restrict<T>(H, L, cr[l], Bufs<T>::b(Ln), last ? nullptr : Bufs<T>::sw(Ln),
+                         last ? nullptr : Bufs<T>::x(Ln), ctl, s);
     }
   }
-  T* res;
-  {
-    Level& Lc = H.lv[nl - 1];
-    InstScope is(H, KID_COARSE, nl - 1, s, a.ctl);
+  T* res = Bufs<T>::x(H.lv[lf]);
+  int np0 = 0;
+  if (H.S == 1) {
+    fused_cycle<T>(H, nullptr, nullptr, nullptr, nullptr, 0, ctl, nullptr, s);
+  } else {  // several systems: no dense tail (lf is the coarsest level)
     hipLaunchKernelGGL((k_coarse<T, T, T>), dim3((C.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, C.n, C.m,
-                       Bufs<T>::inv(C), Bufs<T>::b(Lc), Bufs<T>::x(Lc), ctl);
-    res = Bufs<T>::x(Lc);
+                       Bufs<T>::inv(C), Bufs<T>::b(H.lv[lf]), res, ctl);
   }
-  for (int l = nl - 2; l >= 0; --l) {
+  for (int l = lf - 1; l >= 0; --l) {
     Level& L = H.lv[l];
     {
       InstScope is(H, KID_PROLONG, l, s, a.ctl);
@@ -1244,7 +1482,8 @@ void vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
             sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 0>{vv, sw, a.r0, cur, a.z0, nullptr}, ctl,
                   nullptr, s);
         }
-        if (a.red) launch_fin_beta(ctl, a.partials, np, a.first, a.red, s);
+        if (a.red && !a.fold) launch_fin_beta(ctl, a.partials, np, a.first, a.red, s);
+        np0 = np;
       } else {
         T* dst = spare[k & 1];
         InstScope is(H, KID_POST, l, s, a.ctl);
@@ -1261,11 +1500,12 @@ void vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
     res = cur;
   }
   AMG_HIP(hipGetLastError());
+  return np0;
 }
 
-void vcycle(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
-  if (H.fp32()) vcycle_impl<float>(H, a, s);
-  else vcycle_impl<double>(H, a, s);
+int vcycle(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
+  if (H.fp32()) return vcycle_impl<float>(H, a, s);
+  return vcycle_impl<double>(H, a, s);
 }
 
 void read_ctl(Hierarchy& H, hipStream_t s) {
@@ -1317,6 +1557,22 @@ std::vector<int> host_copy(const DBuf<int>& d, int64_t count) {
 }  // namespace
 
 // ================================================================ public
+
+InstScope::InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const Ctl* ctl) : H(h), s(st) {
+  on = H.inst.kernel == kid && (H.inst.level == level || H.inst.level < 0) &&
+       2 * (H.inst.used + 1) <= (int)H.inst.ev.size();
+  if (on) {
+    hipLaunchKernelGGL(k_snap_done, dim3(1), dim3(64), 0, s, ctl, H.inst.was_done.p + H.inst.used);
+    AMG_HIP(hipEventRecord(H.inst.ev[2 * H.inst.used], s));
+  }
+}
+
+InstScope::~InstScope() {
+  if (on) {
+    (void)hipEventRecord(H.inst.ev[2 * H.inst.used + 1], s);
+    ++H.inst.used;
+  }
+}
 
 namespace {
 
@@ -1554,11 +1810,14 @@ void choose_shapes(Hierarchy& H, hipStream_t s) {
   AMG_HIP(hipStreamSynchronize(s));
 }
 
-int64_t solve_partials_count(const Hierarchy& H) {
+// Partials per reduced value of the largest reducing grid of a solve on H.
+int64_t partials_region(const Hierarchy& H) {
   int64_t np = std::max<int64_t>(vec_grid(H.n), H.lv[0].shA.grid);
-  np = std::max<int64_t>(np, vec_grid(H.co.n));
-  return np * 4 + 64;
+  np = std::max<int64_t>(np, H.lv[0].up.grid);
+  return std::max<int64_t>(np, vec_grid(H.co.n));
 }
+
+int64_t solve_partials_count(const Hierarchy& H) { return partials_region(H) * 4 + 64; }
 
 SolveWork solve_work(Hierarchy& H) {
   return SolveWork{H.r.p, H.z.p, H.p.p, H.z2.p, H.q.p, H.partials.p, H.ctl.p, H.h_ctl, true};
@@ -1607,6 +1866,7 @@ double kernel_bytes(const Hierarchy& H, int kid, int level, int flexible) {
   };
   const double bw = level == 0 ? 8.0 : v;                       // rhs of the level
   const bool has_next = level + 1 < nl;
+  if (nl > 1 && level >= H.lf && H.S == 1 && kid != KID_SPMV_DOT && kid != KID_CG_UPDATE) return fused_bytes(H, kid, level);
   const bool next_coarsest = level + 2 == nl;
   switch (kid) {
     // direction update fused with the product: gathers z, reads old p and q,
@@ -1627,7 +1887,10 @@ double kernel_bytes(const Hierarchy& H, int kid, int level, int flexible) {
       if (!has_next) return 0.0;
       return M((double)L.pnnz, n, pw) + v * (double)L.nagg + 2.0 * v * n;
     // x, r, p, q read; x, r written; sw read and x0 = sw o r written in cycle precision
-    case KID_CG_UPDATE: return 48.0 * n + 2.0 * v * n;
+    case KID_CG_UPDATE: {
+      const X0Mode m = x0_mode(H);
+      return 48.0 * n + (m == X0_SMOOTHED ? 2.0 : m == X0_COPY ? 1.0 : 0.0) * v * n;
+    }
     case KID_XPAY: return 0.0;  // fused into KID_SPMV_DOT
     case KID_COARSE: {
       const double nc = H.co.n;
@@ -1704,15 +1967,28 @@ void pattern_grad(Hierarchy& H, const double* d_lam, const double* d_x, double* 
 template <class T>
 void launch_cg_update(Hierarchy& H, const SolveWork& w, int n, const double* p, hipStream_t s) {
   Level& L0 = H.lv[0];
-  hipLaunchKernelGGL((k_cg_update<T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
-                     Bufs<T>::sw(L0), Bufs<T>::x(L0), w.ctl, w.partials);
+  switch (x0_mode(H)) {
+    case X0_SMOOTHED:
+      hipLaunchKernelGGL((k_cg_update<X0_SMOOTHED, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
+                         Bufs<T>::sw(L0), Bufs<T>::x(L0), w.ctl, w.partials);
+      break;
+    case X0_COPY:
+      hipLaunchKernelGGL((k_cg_update<X0_COPY, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
+                         (const T*)nullptr, Bufs<T>::x(L0), w.ctl, w.partials);
+      break;
+    default:
+      hipLaunchKernelGGL((k_cg_update<X0_NONE, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
+                         (const T*)nullptr, (T*)nullptr, w.ctl, w.partials);
+  }
 }
 
 template <class T>
 void launch_sw_mul(Hierarchy& H, const SolveWork& w, int n, hipStream_t s) {
   Level& L0 = H.lv[0];
-  hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, Bufs<T>::sw(L0), w.r,
-                     Bufs<T>::x(L0), w.ctl);
+  const X0Mode m = x0_mode(H);
+  if (m == X0_NONE) return;
+  hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n,
+                     m == X0_COPY ? (const T*)nullptr : Bufs<T>::sw(L0), w.r, Bufs<T>::x(L0), w.ctl);
 }
 
 void read_ctl(const SolveWork& w, hipStream_t s) {
@@ -1783,6 +2059,13 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   Ctl* ctl = w.ctl;
   double* part = w.partials;
   const int gv = vec_grid(n);
+  // folded form: no finalize launches, the consuming kernels sum the partials
+  // (each reduction in a region of its own: product, update, V-cycle)
+  const int64_t region = partials_region(H);
+  const bool fold = multi && H.lf == 0 && region <= kFoldMax;
+  double* pu = fold ? part + region : part;
+  double* pz = fold ? part + 2 * region : part;
+  int npz = 0;
   hipLaunchKernelGGL(k_cg_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, w.r, d_x, part);
   hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, flexible,
                      d_x);
@@ -1794,6 +2077,25 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   // one PCG iteration: p = z + beta p and q = A p; alpha; x, r update; z = M^-1 r, beta
   auto iteration = [&](int first, int c, hipStream_t st) {
     int np;
+    if (fold) {
+      const int nz = !first && flexible ? 2 : 1;
+      {
+        InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
+        np = sweep(L0.shA, n, L0.arp(), L0.aci(),
+                   OpSpmvFold{L0.av(), w.z, pb[c], pb[c ^ 1], w.q, ctl, pz, pu, npz, gv, nz, first, c}, ctl, part, st);
+      }
+      {
+        InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
+        if (H.fp32())
+          hipLaunchKernelGGL((k_cg_update_fold<X0_COPY, float>), dim3(gv), dim3(kBlock), 0, st, n, w.r, pb[c ^ 1], w.q,
+                             Bufs<float>::x(L0), ctl, part, np, pu, c);
+        else
+          hipLaunchKernelGGL((k_cg_update_fold<X0_NONE, double>), dim3(gv), dim3(kBlock), 0, st, n, w.r, pb[c ^ 1],
+                             w.q, (double*)nullptr, ctl, part, np, pu, c);
+      }
+      vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, flexible ? 2 : 1, 0, 1, 1}, st);
+      return;
+    }
     {
       InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
       np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvXpayDev{L0.av(), w.z, pb[c], pb[c ^ 1], w.q, ctl, first},
@@ -1826,8 +2128,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       if (H.fp32()) launch_sw_mul<float>(H, w, n, s);
       else launch_sw_mul<double>(H, w, n, s);
     }
-    CycleArgs a0{w.r, w.z, w.q, ctl, part, 1, 1, multi ? 1 : 0};
-    vcycle(H, a0, s);
+    CycleArgs a0{w.r, w.z, w.q, ctl, pz, 1, 1, multi ? 1 : 0, fold ? 1 : 0};
+    npz = vcycle(H, a0, s);
     int first = 1;
     // Iterations are queued in chunks; between chunks the host reads the
     // control block and sizes the next chunk from the observed decay of
@@ -1850,6 +2152,7 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
         iteration(0, cur, s);
         cur ^= 1;
       }
+      if (fold) hipLaunchKernelGGL(k_fin_chunk, dim3(1), dim3(kFinBlock), 0, s, ctl, pu, gv, cur ^ 1);
       AMG_HIP(hipGetLastError());
       read_ctl(w, s);
       if (w.h_ctl->done) break;
@@ -1965,26 +2268,30 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
   hipLaunchKernelGGL(k_bi_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, r, rh, d_x, part);
   hipLaunchKernelGGL(k_bfin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, d_x);
   AMG_HIP(hipGetLastError());
-  // with a multilevel cycle the vector kernels also write the level-0
-  // pre-smoothed iterate of the V-cycle that follows them
-  const bool x0w = prec && H.lv.size() > 1;
+  // with a multilevel cycle the vector kernels also write what the V-cycle
+  // that follows them starts from
+  const X0Mode x0m = x0_mode(H);
+  const bool x0w = x0m != X0_NONE, smoothed = x0m == X0_SMOOTHED;
   auto launch_dir = [&](int first, hipStream_t st) {
     Level& L0c = H.lv[0];
     if (H.fp32())
-      hipLaunchKernelGGL(k_bi_dir<float>, dim3(gv), dim3(kBlock), 0, st, n, r, v, p, Bufs<float>::sw(L0c),
+      hipLaunchKernelGGL(k_bi_dir<float>, dim3(gv), dim3(kBlock), 0, st, n, r, v, p,
+                         smoothed ? Bufs<float>::sw(L0c) : nullptr,
                          x0w ? Bufs<float>::x(L0c) : nullptr, ctl, first);
     else
-      hipLaunchKernelGGL(k_bi_dir<double>, dim3(gv), dim3(kBlock), 0, st, n, r, v, p, Bufs<double>::sw(L0c),
+      hipLaunchKernelGGL(k_bi_dir<double>, dim3(gv), dim3(kBlock), 0, st, n, r, v, p,
+                         smoothed ? Bufs<double>::sw(L0c) : nullptr,
                          x0w ? Bufs<double>::x(L0c) : nullptr, ctl, first);
   };
   auto launch_half = [&](hipStream_t st) {
     Level& L0c = H.lv[0];
     if (H.fp32())
-      hipLaunchKernelGGL(k_bi_half<float>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv, Bufs<float>::sw(L0c),
+      hipLaunchKernelGGL(k_bi_half<float>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv,
+                         smoothed ? Bufs<float>::sw(L0c) : nullptr,
                          x0w ? Bufs<float>::x(L0c) : nullptr, ctl, part);
     else
       hipLaunchKernelGGL(k_bi_half<double>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv,
-                         Bufs<double>::sw(L0c), x0w ? Bufs<double>::x(L0c) : nullptr, ctl, part);
+                         smoothed ? Bufs<double>::sw(L0c) : nullptr, x0w ? Bufs<double>::x(L0c) : nullptr, ctl, part);
   };
   auto iteration = [&](int first, hipStream_t st) {
     launch_dir(first, st);
