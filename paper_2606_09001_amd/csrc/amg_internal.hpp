@@ -225,6 +225,7 @@ struct Level {
   int mis_rounds = 0;
   double rho = 0.0, omegaP = 0.0;            // system 0
   std::vector<double> rhoS, omegaPS;         // per system
+  DBuf<double> drho;                         // rhoS on the device
   // prolongator / restriction
   int64_t pnnz = 0;
   DBuf<int> prp, pci, rrp, rci, rperm;

@@ -20,7 +20,9 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int kCoBlock = 256;  // one workgroup, four wavefronts
 
 // Dense m x m (row-major) copy of the CSR matrix; padding rows/cols get the identity.
+// (The setup kernels of the coarsest matrix run one system per blockIdx.y.)
 __global__ void k_densify(int n, int m, double* __restrict__ W) {
+  W += (int64_t)blockIdx.y * m * m;
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   int64_t mm = (int64_t)m * m;
   for (int64_t e = t; e < mm; e += (int64_t)gridDim.x * blockDim.x) {
@@ -31,6 +33,8 @@ __global__ void k_densify(int n, int m, double* __restrict__ W) {
 
 __global__ void k_scatter(int n, int m, const int* __restrict__ rp, const int* __restrict__ ci,
                           const double* __restrict__ v, int vs, double* __restrict__ W) {
+  W += (int64_t)blockIdx.y * m * m;
+  v += blockIdx.y;
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   for (int k = rp[i]; k < rp[i + 1]; ++k) W[(int64_t)i * m + ci[k]] = v[(int64_t)k * vs];
@@ -62,6 +66,7 @@ __device__ inline void mfma_tile_update(double* __restrict__ W, int m, int I, in
 // columns: column-by-column right-looking factorization restricted to the
 // panel, then a rank-16 update of the trailing lower triangle on MFMA.
 __global__ void __launch_bounds__(kCoBlock) k_cholesky(int m, double* __restrict__ W, int* flags) {
+  W += (int64_t)blockIdx.y * m * m;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, nwaves = kCoBlock / 64;
   __shared__ int s_bad;
@@ -128,6 +133,8 @@ __device__ inline void wave_lds_sync() {
 // Linv[k][j]) / L[i][i], Linv[j][j] = 1 / L[j][j].
 __global__ void __launch_bounds__(64 * kTriWaves) k_tri_inverse(int m, const double* __restrict__ L,
                                                                 double* __restrict__ Linv) {
+  L += (int64_t)blockIdx.y * m * m;
+  Linv += (int64_t)blockIdx.y * m * m;
   __shared__ double s_col[kTriWaves][AMG_MAX_DENSE_COARSE];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int j = blockIdx.x * kTriWaves + w;
@@ -150,6 +157,8 @@ __global__ void __launch_bounds__(64 * kTriWaves) k_tri_inverse(int m, const dou
 
 // Transpose (m x m): Y = X^T.
 __global__ void k_transpose(int m, const double* __restrict__ X, double* __restrict__ Y) {
+  X += (int64_t)blockIdx.y * m * m;
+  Y += (int64_t)blockIdx.y * m * m;
   int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= (int64_t)m * m) return;
   int i = (int)(e / m), j = (int)(e % m);
@@ -159,6 +168,8 @@ __global__ void k_transpose(int m, const double* __restrict__ X, double* __restr
 // inv = Linv^T Linv = X X^T with X = Linv^T (row-major): tile (I, J) sums
 // over all 16-column panels of X.  One wavefront per tile.
 __global__ void k_gram(int m, const double* __restrict__ X, double* __restrict__ G) {
+  X += (int64_t)blockIdx.y * m * m;
+  G += (int64_t)blockIdx.y * m * m;
   const int T = m / 16;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (wave >= T * T) return;
@@ -305,31 +316,27 @@ void coarse_setup(Hierarchy& H, hipStream_t s) {
   const int64_t mm = (int64_t)m * m;
   C.L.alloc(mm * S);
   C.inv.alloc(mm * S);
-  C.work.alloc(mm);
-  const bool lu = !H.prm.symmetric;
-  if (lu) C.piv.alloc((int64_t)m * S);
+  const bool lu = !H.prm.symmetric;  // (one system)
+  if (lu) C.piv.alloc(m);
+  else C.work.alloc(mm * S);
   const int grid = (int)std::min<int64_t>((mm + kBlock - 1) / kBlock, 4096);
   const int T = m / 16;
   AMG_HIP(hipMemsetAsync(H.flags.p, 0, sizeof(int), s));
-  // one dense factorization (and inverse) per system sharing the pattern
-  for (int sy = 0; sy < S; ++sy) {
-    double* Ls = C.L.p + sy * mm;
-    double* Is = C.inv.p + sy * mm;
-    hipLaunchKernelGGL(k_densify, dim3(grid), dim3(kBlock), 0, s, C.n, m, Ls);
-    hipLaunchKernelGGL(k_scatter, dim3((C.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, C.n, m, L.rp.p, L.ci.p,
-                       L.v.p + sy, S, Ls);
-    if (lu) {
-      int* ps = C.piv.p + (int64_t)sy * m;
-      hipLaunchKernelGGL(k_lu, dim3(1), dim3(kLuBlock), 0, s, m, Ls, ps, H.flags.p);
-      hipLaunchKernelGGL(k_lu_inverse_t, dim3((m + kTriWaves - 1) / kTriWaves), dim3(64 * kTriWaves), 0, s, m, Ls,
-                         ps, Is);
-      continue;
-    }
-    hipLaunchKernelGGL(k_cholesky, dim3(1), dim3(kCoBlock), 0, s, m, Ls, H.flags.p);
-    hipLaunchKernelGGL(k_tri_inverse, dim3((m + kTriWaves - 1) / kTriWaves), dim3(64 * kTriWaves), 0, s, m, Ls,
-                       Is);
-    hipLaunchKernelGGL(k_transpose, dim3((int)((mm + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, m, Is, C.work.p);
-    hipLaunchKernelGGL(k_gram, dim3((T * T * 64 + kBlock - 1) / kBlock), dim3(kBlock), 0, s, m, C.work.p, Is);
+  // the dense factorizations (and inverses) of the systems sharing the pattern
+  hipLaunchKernelGGL(k_densify, dim3(grid, S), dim3(kBlock), 0, s, C.n, m, C.L.p);
+  hipLaunchKernelGGL(k_scatter, dim3((C.n + kBlock - 1) / kBlock, S), dim3(kBlock), 0, s, C.n, m, L.rp.p, L.ci.p,
+                     L.v.p, S, C.L.p);
+  if (lu) {
+    hipLaunchKernelGGL(k_lu, dim3(1), dim3(kLuBlock), 0, s, m, C.L.p, C.piv.p, H.flags.p);
+    hipLaunchKernelGGL(k_lu_inverse_t, dim3((m + kTriWaves - 1) / kTriWaves), dim3(64 * kTriWaves), 0, s, m, C.L.p,
+                       C.piv.p, C.inv.p);
+  } else {
+    hipLaunchKernelGGL(k_cholesky, dim3(1, S), dim3(kCoBlock), 0, s, m, C.L.p, H.flags.p);
+    hipLaunchKernelGGL(k_tri_inverse, dim3((m + kTriWaves - 1) / kTriWaves, S), dim3(64 * kTriWaves), 0, s, m, C.L.p,
+                       C.inv.p);
+    hipLaunchKernelGGL(k_transpose, dim3((int)((mm + kBlock - 1) / kBlock), S), dim3(kBlock), 0, s, m, C.inv.p,
+                       C.work.p);
+    hipLaunchKernelGGL(k_gram, dim3((T * T * 64 + kBlock - 1) / kBlock, S), dim3(kBlock), 0, s, m, C.work.p, C.inv.p);
   }
   AMG_HIP(hipGetLastError());
   AMG_HIP(hipMemcpyAsync(H.h_flags, H.flags.p, sizeof(int), hipMemcpyDeviceToHost, s));

@@ -95,58 +95,81 @@ __global__ void k_diff_bits(int64_t count, const double* __restrict__ a, const d
 
 // ------------------------------------------------------- level numerics
 
-// Diagonal position, 1/a_ii and the smoother weight of every row.
-// Value arrays of several systems sharing the pattern are interleaved with
-// stride vs (entry k of system s at [k*vs + s]); callers pass the pointers
-// offset by s.
-__global__ void k_diag(int n, const int* __restrict__ rp, const int* __restrict__ ci, const double* __restrict__ v,
-                       int vs, int* __restrict__ diagpos, double* __restrict__ dinv, double* __restrict__ sw,
-                       float* __restrict__ sw32, double omega, int l1, int* flags) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int s = rp[i], e = rp[i + 1], pos = -1;
-  double asum = 0.0;
-  for (int k = s; k < e; ++k) {
-    if (ci[k] == i) pos = k;
-    asum += fabs(v[(int64_t)k * vs]);
-  }
-  const int64_t io = (int64_t)i * vs;
-  if (pos < 0) {
-    atomicOr(flags, F_ZERO_DIAG);
-    diagpos[i] = s;
-    dinv[io] = 0.0;
-    sw[io] = 0.0;
-    if (sw32) sw32[io] = 0.0f;
-    return;
-  }
-  const double a = v[(int64_t)pos * vs];
-  if (a == 0.0) atomicOr(flags, F_ZERO_DIAG);
-  diagpos[i] = pos;
-  double d = 1.0 / a;
-  dinv[io] = d;
-  double w = l1 ? 1.0 / asum : omega * d;
-  sw[io] = w;
-  if (sw32) sw32[io] = (float)w;
-}
+// Value arrays of S systems sharing the pattern are interleaved: entry k of
+// system y at [k*S + y].  The numeric kernels below give an item (a row, an
+// entry) 2^sh >= S consecutive lanes, one per system, so every value access
+// is one coalesced S-wide segment and the indices are read once per item.
+// (One launch per system instead, with stride S, moved whole cache lines for
+// 8 bytes: a refresh of 64 systems of 64^3 took 74 ms, now 6.)
 
-// Gershgorin bound max_i (sum_j |a_ij|) / |a_ii|; positive doubles order like
-// their bit patterns, so an integer max is exact and order-free.
-__global__ void k_rho(int n, const int* __restrict__ rp, const double* __restrict__ v, int vs,
-                      const int* __restrict__ diagpos, unsigned long long* out) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Diagonal position, 1/a_ii and the smoother weight of every row, and per
+// system the Gershgorin bound max_i (sum_j |a_ij|) / |a_ii| (positive doubles
+// order like their bit patterns, so an integer maximum is exact and
+// order-free; a workgroup only issues its atomic where it raises the value).
+__global__ void __launch_bounds__(kBlock) k_diag(int n, int S, int sh, const int* __restrict__ rp,
+                                                 const int* __restrict__ ci, const double* __restrict__ v,
+                                                 int* __restrict__ diagpos, double* __restrict__ dinv,
+                                                 double* __restrict__ sw, float* __restrict__ sw32, double omega, int l1,
+                                                 int* flags, unsigned long long* rho) {
+  __shared__ unsigned long long s_max[kBlock];
+  const int y = threadIdx.x & ((1 << sh) - 1);
+  const int step = gridDim.x * (kBlock >> sh);
   unsigned long long bits = 0;  // +0.0: below every ratio
-  if (i < n) {
-    double s = 0.0;
-    for (int k = rp[i]; k < rp[i + 1]; ++k) s += fabs(v[(int64_t)k * vs]);
-    const double r = s / fabs(v[(int64_t)diagpos[i] * vs]);
-    bits = (unsigned long long)__double_as_longlong(r);
+  for (int i = blockIdx.x * (kBlock >> sh) + (threadIdx.x >> sh); i < n; i += step) {
+    if (y >= S) continue;
+    const int k0 = rp[i], k1 = rp[i + 1];
+    int pos = -1;
+    double asum = 0.0, a = 0.0;
+    for (int k = k0; k < k1; k += 8) {  // 8 entries in flight, added in stored order
+      int c[8];
+      double x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int kk = min(k + u, k1 - 1);
+        c[u] = ci[kk];
+        x[u] = v[(int64_t)kk * S + y];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (k + u < k1) {
+          asum += fabs(x[u]);
+          if (c[u] == i) {
+            pos = k + u;
+            a = x[u];
+          }
+        }
+      }
+    }
+    const int64_t io = (int64_t)i * S + y;
+    if (pos < 0) {
+      atomicOr(flags, F_ZERO_DIAG);
+      if (y == 0) diagpos[i] = k0;
+      dinv[io] = 0.0;
+      sw[io] = 0.0;
+      if (sw32) sw32[io] = 0.0f;
+      continue;
+    }
+    if (a == 0.0) atomicOr(flags, F_ZERO_DIAG);
+    if (y == 0) diagpos[i] = pos;
+    const double d = 1.0 / a;
+    dinv[io] = d;
+    const double w = l1 ? 1.0 / asum : omega * d;
+    sw[io] = w;
+    if (sw32) sw32[io] = (float)w;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(asum / fabs(a));
+    bits = b > bits ? b : bits;
   }
-  // wavefront maximum first: one atomic per wave instead of one per row
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(bits, o, 64);
-    bits = other > bits ? other : bits;
+  s_max[threadIdx.x] = bits;
+  __syncthreads();
+  for (int o = kBlock >> 1; o >= (1 << sh); o >>= 1) {
+    if ((int)threadIdx.x < o) s_max[threadIdx.x] = max(s_max[threadIdx.x], s_max[threadIdx.x + o]);
+    __syncthreads();
   }
-  if ((threadIdx.x & 63) == 0) atomicMax(out, bits);
+  if ((int)threadIdx.x < S) {
+    const unsigned long long m = s_max[threadIdx.x];
+    if (m > __hip_atomic_load(rho + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(rho + threadIdx.x, m);
+  }
 }
 
 // ------------------------------------------------------- strength graph
@@ -388,22 +411,24 @@ __global__ void k_pmap_build(int n, const int* __restrict__ rp, const int* __res
   if (i == n - 1) pao[prp[n]] = rp[n];
 }
 
-// Prolongator values through the map (thread per entry): the same
-// expression and fold as k_p_fill.
-__global__ void k_p_refill(int64_t pnnz, const int* __restrict__ pao, const int* __restrict__ pak,
+// Prolongator values through the map (entry by system): the same expression
+// and fold as k_p_fill, omega_P = (4/3) / rho.
+__global__ void k_p_refill(int64_t pnnz, int S, int sh, const int* __restrict__ pao, const int* __restrict__ pak,
                            const int* __restrict__ prow, const int* __restrict__ pci, const double* __restrict__ v,
-                           int vs, const int* __restrict__ diagpos, const int* __restrict__ agg, double omegaP,
-                           double* __restrict__ pv) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= pnnz) return;
+                           const int* __restrict__ diagpos, const int* __restrict__ agg,
+                           const double* __restrict__ rho, double* __restrict__ pv) {
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t e = t >> sh;
+  const int y = (int)(t & ((1 << sh) - 1));
+  if (e >= pnnz || y >= S) return;
   const int i = prow[e];
-  const double w = omegaP / v[(int64_t)diagpos[i] * vs];
+  const double w = ((4.0 / 3.0) / rho[y]) / v[(int64_t)diagpos[i] * S + y];
   double sJ = 0.0;
-  for (int t = pao[e]; t < pao[e + 1]; ++t)
-    if (pak[t] >= 0) sJ += v[(int64_t)pak[t] * vs];
+  for (int q = pao[e]; q < pao[e + 1]; ++q)
+    if (pak[q] >= 0) sJ += v[(int64_t)pak[q] * S + y];
   const double delta = (pci[e] == agg[i]) ? 1.0 : 0.0;
   const double ws = w * sJ;
-  pv[e * vs] = delta - ws;
+  pv[e * S + y] = delta - ws;
 }
 
 __global__ void k_row_ids(int n, const int* __restrict__ rp, int* __restrict__ rowid) {
@@ -424,13 +449,12 @@ __global__ void k_col_count(int64_t m, const int* __restrict__ ci, int* __restri
 
 // R = P^T: entry t of R is entry perm[t] of P (stable sort by column keeps
 // source rows ascending inside each row of R).
-__global__ void k_r_fill(int64_t m, const int* __restrict__ perm, const int* __restrict__ rowid,
-                         const double* __restrict__ pv, int vs, int* __restrict__ rci, double* __restrict__ rv) {
-  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= m) return;
-  int k = perm[t];
-  if (rci) rci[t] = rowid[k];
-  rv[t * vs] = pv[(int64_t)k * vs];
+__global__ void k_r_fill(int64_t m, int S, int sh, const int* __restrict__ perm, const double* __restrict__ pv,
+                         double* __restrict__ rv) {
+  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t t = q >> sh;
+  const int y = (int)(q & ((1 << sh) - 1));
+  if (t < m && y < S) rv[t * S + y] = pv[(int64_t)perm[t] * S + y];
 }
 
 // Columns of a transposed pattern: entry t holds the source row of entry perm[t].
@@ -717,14 +741,16 @@ __global__ void k_pm_fill(int nrows, int64_t cnnz, const int* __restrict__ crp, 
   }
 }
 
-// Numeric product through the map: the same fold (ascending inner index, each
-// product rounded before the add) as k_spgemm_fill_entries, with all loads
-// independent of each other.
-__global__ void k_pm_apply(int64_t cnnz, const int64_t* __restrict__ off, const int2* __restrict__ pairs,
-                           const double* __restrict__ xv, const double* __restrict__ yv, double* __restrict__ cv,
-                           int vs) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= cnnz) return;
+// Numeric product through the map (entry by system): the same fold (ascending
+// inner index, each product rounded before the add) as k_spgemm_fill_entries,
+// with all loads independent of each other.
+__global__ void k_pm_apply(int64_t cnnz, int S, int sh, const int64_t* __restrict__ off,
+                           const int2* __restrict__ pairs, const double* __restrict__ xv,
+                           const double* __restrict__ yv, double* __restrict__ cv) {
+  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t e = q >> sh;
+  const int y = (int)(q & ((1 << sh) - 1));
+  if (e >= cnnz || y >= S) return;
   double acc = 0.0;
   const int64_t p0 = off[e], p1 = off[e + 1];
   // 4 terms in flight: unconditional loads at clamped positions, the adds
@@ -736,11 +762,11 @@ __global__ void k_pm_apply(int64_t cnnz, const int64_t* __restrict__ off, const 
     for (int u = 0; u < U; ++u) t[u] = pairs[min(p + u, p1 - 1)];
     double prod[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) prod[u] = xv[(int64_t)t[u].x * vs] * yv[(int64_t)t[u].y * vs];
+    for (int u = 0; u < U; ++u) prod[u] = xv[(int64_t)t[u].x * S + y] * yv[(int64_t)t[u].y * S + y];
 #pragma unroll
     for (int u = 0; u < U; ++u) acc = p + u < p1 ? acc + prod[u] : acc;
   }
-  cv[e * vs] = acc;
+  cv[e * S + y] = acc;
 }
 
 // ------------------------------------------------------ precision copies
@@ -915,18 +941,30 @@ int read_int(const int* d, hipStream_t s) {
   return h;
 }
 
+// Lanes per item (as a shift) and workgroups of the per-system kernels.
+int sys_shift(int S) {
+  int sh = 0;
+  while ((1 << sh) < S) ++sh;
+  return sh;
+}
+unsigned sys_grid(int64_t items, int sh) { return (unsigned)std::max<int64_t>(1, ((items << sh) + kBlock - 1) / kBlock); }
+
 void level_numerics(Hierarchy& H, Level& L, hipStream_t s) {
-  const int S = H.S;
+  const int S = H.S, sh = sys_shift(S);
   L.diagpos.alloc(L.n);
   L.dinv.alloc((int64_t)L.n * S);
   L.sw.alloc((int64_t)L.n * S);
+  L.drho.alloc(S);
   if (H.fp32()) L.sw32.alloc((int64_t)L.n * S);
   zero_flags(H.flags.p, 1, s);
-  for (int sy = 0; sy < S; ++sy)
-    hipLaunchKernelGGL(k_diag, dim3(grid_for(L.n)), dim3(kBlock), 0, s, L.n, L.rp.p, L.ci.p, L.v.p + sy, S,
-                       L.diagpos.p, L.dinv.p + sy, L.sw.p + sy, H.fp32() ? L.sw32.p + sy : nullptr, H.prm.omega,
-                       (int)(H.prm.smoother == AMG_SMOOTHER_L1), H.flags.p);
+  AMG_HIP(hipMemsetAsync(L.drho.p, 0, L.drho.bytes(), s));
+  const int grid = (int)std::min<int64_t>(sys_grid(L.n, sh), 8192);
+  hipLaunchKernelGGL(k_diag, dim3(grid), dim3(kBlock), 0, s, L.n, S, sh, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.dinv.p,
+                     L.sw.p, H.fp32() ? L.sw32.p : nullptr, H.prm.omega, (int)(H.prm.smoother == AMG_SMOOTHER_L1),
+                     H.flags.p, reinterpret_cast<unsigned long long*>(L.drho.p));
   AMG_HIP(hipGetLastError());
+  L.rhoS.resize(S);
+  AMG_HIP(hipMemcpyAsync(L.rhoS.data(), L.drho.p, sizeof(double) * S, hipMemcpyDeviceToHost, s));
   sync_flags(H.flags.p, H.h_flags, 1, s);
   if (H.h_flags[0] & F_ZERO_DIAG) throw Error(AMG_ERR_ZERO_DIAG, "zero diagonal");
 }
@@ -1025,20 +1063,6 @@ int aggregate(Hierarchy& H, Level& L, hipStream_t s) {
   return nagg;
 }
 
-double gershgorin(Hierarchy& H, Level& L, int sy, hipStream_t s) {
-  // a slot of the flag block (64 bytes, the error flags use its front)
-  unsigned long long* r = reinterpret_cast<unsigned long long*>(H.flags.p + 8);
-  AMG_HIP(hipMemsetAsync(r, 0, sizeof(unsigned long long), s));
-  hipLaunchKernelGGL(k_rho, dim3(grid_for(L.n)), dim3(kBlock), 0, s, L.n, L.rp.p, L.v.p + sy, H.S, L.diagpos.p, r);
-  AMG_HIP(hipGetLastError());
-  unsigned long long bits = 0;
-  AMG_HIP(hipMemcpyAsync(&bits, r, sizeof(bits), hipMemcpyDeviceToHost, s));
-  AMG_HIP(hipStreamSynchronize(s));
-  double rho;
-  std::memcpy(&rho, &bits, sizeof(rho));
-  return rho;
-}
-
 // Builds P, R and the Galerkin operator of level l+1 (symbolic when
 // `symbolic`, else reusing the stored patterns).
 void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s) {
@@ -1046,12 +1070,9 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   const int n = L.n;
   const int S = H.S;
   const dim3 b(kBlock);
-  L.rhoS.resize(S);
+  const int sh = sys_shift(S);
   L.omegaPS.resize(S);
-  for (int sy = 0; sy < S; ++sy) {
-    L.rhoS[sy] = gershgorin(H, L, sy, s);
-    L.omegaPS[sy] = (4.0 / 3.0) / L.rhoS[sy];
-  }
+  for (int sy = 0; sy < S; ++sy) L.omegaPS[sy] = (4.0 / 3.0) / L.rhoS[sy];
   L.rho = L.rhoS[0];
   L.omegaP = L.omegaPS[0];
   // P
@@ -1075,9 +1096,9 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     hipLaunchKernelGGL(k_pmap_build, dim3(grid_for(n)), b, 0, s, n, L.rp.p, L.ci.p, L.agg.p, L.prp.p, L.pci.p,
                        L.pao.p, L.pak.p, L.prow.p);
   }
-  for (int sy = symbolic ? 1 : 0; sy < S; ++sy)
-    hipLaunchKernelGGL(k_p_refill, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.pao.p, L.pak.p, L.prow.p, L.pci.p,
-                       L.v.p + sy, S, L.diagpos.p, L.agg.p, L.omegaPS[sy], L.pv.p + sy);
+  if (!symbolic || S > 1)
+    hipLaunchKernelGGL(k_p_refill, dim3(sys_grid(L.pnnz, sh)), b, 0, s, L.pnnz, S, sh, L.pao.p, L.pak.p, L.prow.p,
+                       L.pci.p, L.v.p, L.diagpos.p, L.agg.p, L.drho.p, L.pv.p);
   AMG_HIP(hipGetLastError());
   // R = P^T
   const int nc = L.nagg;
@@ -1102,14 +1123,9 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     exclusive_scan(cnt.p, L.rrp.p, nc + 1, s);
     L.rci.alloc(L.pnnz);
     L.rv.alloc(L.pnnz * S);
-    for (int sy = 0; sy < S; ++sy)
-      hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.rperm.p, rowid.p, L.pv.p + sy, S,
-                         sy == 0 ? L.rci.p : (int*)nullptr, L.rv.p + sy);
-  } else {
-    for (int sy = 0; sy < S; ++sy)
-      hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.rperm.p, (const int*)nullptr,
-                         L.pv.p + sy, S, (int*)nullptr, L.rv.p + sy);
+    hipLaunchKernelGGL(k_t_cols, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.rperm.p, rowid.p, L.rci.p);
   }
+  hipLaunchKernelGGL(k_r_fill, dim3(sys_grid(L.pnnz, sh)), b, 0, s, L.pnnz, S, sh, L.rperm.p, L.pv.p, L.rv.p);
   AMG_HIP(hipGetLastError());
   // product maps for the refreshes (8 bytes per term; the budget keeps each
   // map within 128 bytes per fine-level nonzero: about 1.6 GB in all for
@@ -1147,14 +1163,20 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
       }
     }
   }
-  for (int sy = 0; sy < S; ++sy) {
-    if (symbolic && sy == 0 && !wide_ap)
-      hipLaunchKernelGGL(k_spgemm_fill, dim3(grid_for(n)), b, 0, s, n, L.rp.p, L.ci.p, L.v.p, L.prp.p, L.pci.p,
-                         L.pv.p, L.aprp.p, L.apci.p, L.apv.p, S);
-    else if (symbolic ? apmap : L.pmaps)
-      hipLaunchKernelGGL(k_pm_apply, dim3(grid_for(L.apnnz)), b, 0, s, L.apnnz, L.apmo.p, L.apm.p, L.v.p + sy,
-                         L.pv.p + sy, L.apv.p + sy, S);
-    else
+  if (symbolic && !wide_ap) {
+    hipLaunchKernelGGL(k_spgemm_fill, dim3(grid_for(n)), b, 0, s, n, L.rp.p, L.ci.p, L.v.p, L.prp.p, L.pci.p,
+                       L.pv.p, L.aprp.p, L.apci.p, L.apv.p, S);
+    AMG_HIP(hipGetLastError());
+    apmap = build_product_map(n, L.apnnz, L.aprp.p, L.apci.p, L.rp.p, L.ci.p, L.prp.p, L.pci.p, budget, L.apmo,
+                              L.apm, s);
+  }
+  const int sy0 = symbolic && !wide_ap ? 1 : 0;  // systems formed by the merge above
+  if (sy0 >= S) {
+  } else if (symbolic ? apmap : L.pmaps) {
+    hipLaunchKernelGGL(k_pm_apply, dim3(sys_grid(L.apnnz, sh)), b, 0, s, L.apnnz, S, sh, L.apmo.p, L.apm.p, L.v.p,
+                       L.pv.p, L.apv.p);
+  } else {
+    for (int sy = sy0; sy < S; ++sy)
       hipLaunchKernelGGL(k_spgemm_fill_entries, dim3(grid_for(L.apnnz)), b, 0, s, n, L.apnnz, L.aprp.p, L.apci.p,
                          L.rp.p, L.ci.p, L.v.p + sy, L.prp.p, L.pci.p, L.pv.p + sy, L.apv.p + sy, S);
   }
@@ -1181,10 +1203,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     // column pattern of the coarse operator (wavefront per row), values below
     hipLaunchKernelGGL(k_spgemm_sym_w<1>, dim3(nc), dim3(64), 0, s, nc, Lr.rrp.p, Lr.rci.p, Lr.aprp.p, Lr.apci.p,
                        C.rp.p, C.ci.p);
-    // (the wide levels built the map of AP above)
-    Lr.pmaps = (wide_ap ? apmap
-                        : build_product_map(n, Lr.apnnz, Lr.aprp.p, Lr.apci.p, Lr.rp.p, Lr.ci.p, Lr.prp.p, Lr.pci.p,
-                                            budget, Lr.apmo, Lr.apm, s)) &&
+    Lr.pmaps = apmap &&
                build_product_map(nc, C.nnz, C.rp.p, C.ci.p, Lr.rrp.p, Lr.rci.p, Lr.aprp.p, Lr.apci.p, budget,
                                  Lr.cmo, Lr.cm, s);
     if (!Lr.pmaps) {
@@ -1194,11 +1213,11 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
       Lr.cm.release();
     }
   }
-  for (int sy = 0; sy < S; ++sy) {
-    if (Lr.pmaps)
-      hipLaunchKernelGGL(k_pm_apply, dim3(grid_for(C.nnz)), b, 0, s, C.nnz, Lr.cmo.p, Lr.cm.p, Lr.rv.p + sy,
-                         Lr.apv.p + sy, C.v.p + sy, S);
-    else
+  if (Lr.pmaps) {
+    hipLaunchKernelGGL(k_pm_apply, dim3(sys_grid(C.nnz, sh)), b, 0, s, C.nnz, S, sh, Lr.cmo.p, Lr.cm.p, Lr.rv.p,
+                       Lr.apv.p, C.v.p);
+  } else {
+    for (int sy = 0; sy < S; ++sy)
       hipLaunchKernelGGL(k_spgemm_fill_entries, dim3(grid_for(C.nnz)), b, 0, s, nc, C.nnz, C.rp.p, C.ci.p, Lr.rrp.p,
                          Lr.rci.p, Lr.rv.p + sy, Lr.aprp.p, Lr.apci.p, Lr.apv.p + sy, C.v.p + sy, S);
   }
@@ -1466,8 +1485,7 @@ void transpose_pattern(Hierarchy& H, hipStream_t s) {
 // Values of A^T in its entry order from A's current values.
 void transpose_values(Hierarchy& H, hipStream_t s) {
   const Level& L = H.lv[0];
-  hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.nnz)), dim3(kBlock), 0, s, L.nnz, H.tperm.p, (const int*)nullptr,
-                     L.v.p, 1, (int*)nullptr, H.tval.p);
+  hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.nnz)), dim3(kBlock), 0, s, L.nnz, 1, 0, H.tperm.p, L.v.p, H.tval.p);
   AMG_HIP(hipGetLastError());
 }
 
