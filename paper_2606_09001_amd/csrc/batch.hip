@@ -534,6 +534,82 @@ __global__ void __launch_bounds__(kBlock) k_wide(int n, int W, int spx, const in
   publish_w<LW, V, Op::NRED>(d, W, partials);
 }
 
+// Wide sweep for matrices of few rows with many entries (restrictions and the
+// coarse operators): `parts` neighbouring lane groups share a row, taking
+// chunks of U entries in turn, and the row's first group adds their sums in
+// group order.  One group per row leaves the chip idle there (the level-1
+// restriction of 128^3, 2,734 rows of 330 entries: 171 workgroups, 282 us for
+// 32 FP64 columns; level 2, 26 rows: 2 workgroups, 263 us).  Workgroups take
+// blocks of (lane groups / parts) rows in XCD-contiguous ranges.
+template <int LW, int V, class Op>
+__global__ void __launch_bounds__(kBlock) k_wide_split(int n, int W, int parts, const int* __restrict__ rp,
+                                                       const int* __restrict__ ci, Op op,
+                                                       const BatchHead* __restrict__ head) {
+  if ((head && head->ndone >= head->W) || n <= 0) return;
+  using PT = typename Op::PT;
+  using VT = typename Op::VT;
+  using GT = typename Op::GT;
+  constexpr int RB = kBlock / LW;
+  constexpr int U = 4;
+  __shared__ PT s_sum[kBlock * V];
+  const int lr = threadIdx.x / LW, c0 = (threadIdx.x & (LW - 1)) * V;
+  const bool live = c0 < W;
+  const int cc0 = min(c0, W - V);
+  const auto cs = op.template cols<V>(cc0);
+  const int rows = RB / parts, part = lr & (parts - 1);
+  const int nb = (n + rows - 1) / rows, lb = logical_block_w();
+  const int b0 = (int)((int64_t)nb * lb / gridDim.x), b1 = (int)((int64_t)nb * (lb + 1) / gridDim.x);
+  for (int blk = b0; blk < b1; ++blk) {
+    const int row = blk * rows + lr / parts;
+    const int rc = min(row, n - 1);
+    const int k0 = rp[rc], k1 = row < n ? rp[rc + 1] : k0;
+    GT xo[V];
+    if constexpr (Op::kOwn) ldv<V>(op.gv, (int64_t)rc * W + cc0, xo);
+    const auto in = op.template row_in<V>(rc, cc0, cs, xo);
+    PT s[V] = {};
+    for (int kb = k0 + part * U; kb < k1; kb += parts * U) {
+      int col[U];
+#pragma unroll
+      for (int e = 0; e < U; ++e) col[e] = ci[min(kb + e, k1 - 1)];
+      VT a[U][V];
+      GT x[U][V];
+#pragma unroll
+      for (int e = 0; e < U; ++e) {
+        vals_at<Op::kSys, V>(op.v, min(kb + e, k1 - 1), cc0, W, a[e]);
+        ldv<V>(op.gv, (int64_t)col[e] * W + cc0, x[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < U; ++e)
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          const PT p = Op::mul(a[e][u], x[e][u]);
+          s[u] = kb + e < k1 ? s[u] + p : s[u];
+        }
+    }
+    __syncthreads();  // the previous block's sums have been read
+#pragma unroll
+    for (int u = 0; u < V; ++u) s_sum[threadIdx.x * V + u] = s[u];
+    __syncthreads();
+    if (part == 0 && row < n && live) {
+      for (int q = 1; q < parts; ++q)
+#pragma unroll
+        for (int u = 0; u < V; ++u) s[u] += s_sum[(threadIdx.x + q * LW) * V + u];
+      double* none = nullptr;
+      op.template epi<V>(row, c0, s, in, cs, none);
+    }
+  }
+}
+
+// Lane groups per row for a matrix of n rows and nnz entries with `groups`
+// lane groups per workgroup: doubled from one while the launch has fewer than
+// 1024 workgroups (four per compute unit) and a group keeps at least two
+// chunks of four entries.
+inline int wide_parts(int n, int64_t nnz, int groups) {
+  int parts = 1;
+  while (parts < groups && (int64_t)n * parts < 1024 * (int64_t)groups && nnz >= 16 * (int64_t)parts * n) parts <<= 1;
+  return parts;
+}
+
 // Instrumented launches (amg_instrument) of the batched solve: the done
 // state of the batch (every column finished) is copied into the record
 // before the event pair, so launches that return at once are left out.
@@ -1015,23 +1091,42 @@ inline int wide_v(int W, int elem_bytes, int vmax) {
 }
 inline int wide_lanes(int W, int V) { return pow2_ceil((W + V - 1) / V); }
 
-// br > 0: staged kernel with br rows per block; 0: direct kernel.
+// br > 0: staged kernel with br rows per block; 0: direct kernel; the split
+// kernel instead of either where rows are few and long (wide_parts).
 template <int V, class Op>
-int wsweep_v(int spx, int br, int n, int W, const int* rp, const int* ci, const Op& op, const BatchHead* head,
-             double* partials, hipStream_t s) {
+int wsweep_v(int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op,
+             const BatchHead* head, double* partials, hipStream_t s) {
   const int LWv = wide_lanes(W, V);
   int grid = 0;
+  if constexpr (Op::NRED == 0) {
+    const int parts = wide_parts(n, nnz, kBlock / LWv);
+    if (parts > 1) {
+      const int rows = kBlock / LWv / parts;
+      grid = std::min((n + rows - 1) / rows, kWGrid);
+      if (grid >= 64) grid = grid / 8 * 8;
+      AMG_DISPATCH_LW(LWv, {
+        if constexpr (LW * V <= kMaxWidth)
+          hipLaunchKernelGGL((k_wide_split<LW, V, Op>), dim3(grid), dim3(kBlock), 0, s, n, W, parts, rp, ci, op, head);
+      });
+      return grid;
+    }
+  }
   if (br > 0) {
+    // (LW * V > kMaxWidth cannot occur: no such kernels are built)
     AMG_DISPATCH_LW(LWv, {
-      const void* kp = reinterpret_cast<const void*>(&k_wide_st<LW, V, Op>);
-      grid = std::min<int64_t>(resident_grid(kp), std::max<int64_t>(8, ((int64_t)n + br - 1) / br / 8 * 8));
-      hipLaunchKernelGGL((k_wide_st<LW, V, Op>), dim3(grid), dim3(kBlock), 0, s, n, W, spx, br, rp, ci, op, head,
-                         partials);
+      if constexpr (LW * V <= kMaxWidth) {
+        const void* kp = reinterpret_cast<const void*>(&k_wide_st<LW, V, Op>);
+        grid = std::min<int64_t>(resident_grid(kp), std::max<int64_t>(8, ((int64_t)n + br - 1) / br / 8 * 8));
+        hipLaunchKernelGGL((k_wide_st<LW, V, Op>), dim3(grid), dim3(kBlock), 0, s, n, W, spx, br, rp, ci, op, head,
+                           partials);
+      }
     });
   } else {
     grid = wide_grid(n, LWv);
-    AMG_DISPATCH_LW(LWv, hipLaunchKernelGGL((k_wide<LW, V, Op>), dim3(grid), dim3(kBlock), 0, s, n, W, spx, rp, ci,
-                                            op, head, partials));
+    AMG_DISPATCH_LW(LWv, {
+      if constexpr (LW * V <= kMaxWidth)
+        hipLaunchKernelGGL((k_wide<LW, V, Op>), dim3(grid), dim3(kBlock), 0, s, n, W, spx, rp, ci, op, head, partials);
+    });
   }
   return grid;
 }
@@ -1039,15 +1134,15 @@ int wsweep_v(int spx, int br, int n, int W, const int* rp, const int* ci, const 
 // A wide sweep with the columns per lane wide_v gives (every vector of the
 // operator aligned to 16 bytes unless vmax = 1).
 template <class Op>
-int wsweep(int vmax, int spx, int br, int n, int W, const int* rp, const int* ci, const Op& op,
+int wsweep(int vmax, int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op,
            const BatchHead* head, double* partials, hipStream_t s) {
   constexpr int eb = (int)sizeof(typename Op::GT);
   const int v = wide_v(W, eb, vmax);
   if constexpr (eb == 4) {
-    if (v == 4) return wsweep_v<4>(spx, br, n, W, rp, ci, op, head, partials, s);
+    if (v == 4) return wsweep_v<4>(spx, br, n, nnz, W, rp, ci, op, head, partials, s);
   }
-  if (v >= 2) return wsweep_v<2>(spx, br, n, W, rp, ci, op, head, partials, s);
-  return wsweep_v<1>(spx, br, n, W, rp, ci, op, head, partials, s);
+  if (v >= 2) return wsweep_v<2>(spx, br, n, nnz, W, rp, ci, op, head, partials, s);
+  return wsweep_v<1>(spx, br, n, nnz, W, rp, ci, op, head, partials, s);
 }
 
 std::vector<int> host_rows(const DBuf<int>& rp, int n) {
@@ -1097,12 +1192,12 @@ void w_restrict(Hierarchy& H, Level& L, int Vc, int spx, int br, int W, const T*
                 hipStream_t s) {
   const BatchHead* hd = H.bt.head.p;
   if constexpr (std::is_same<T, double>::value) {
-    wsweep(Vc, spx, br, L.nagg, W, L.rrp.p, L.rci.p, WRestrict<SYS, double, T>{L.rv.p, r, bc, swc, xc, W}, hd, nullptr, s);
+    wsweep(Vc, spx, br, L.nagg, L.pnnz, W, L.rrp.p, L.rci.p, WRestrict<SYS, double, T>{L.rv.p, r, bc, swc, xc, W}, hd, nullptr, s);
   } else if (H.bf16()) {
-    wsweep(Vc, spx, br, L.nagg, W, L.rrp.p, L.rci.p, WRestrict<SYS, uint16_t, T>{L.rbf.p, r, bc, swc, xc, W}, hd, nullptr,
+    wsweep(Vc, spx, br, L.nagg, L.pnnz, W, L.rrp.p, L.rci.p, WRestrict<SYS, uint16_t, T>{L.rbf.p, r, bc, swc, xc, W}, hd, nullptr,
            s);
   } else {
-    wsweep(Vc, spx, br, L.nagg, W, L.rrp.p, L.rci.p, WRestrict<SYS, float, T>{L.rv32.p, r, bc, swc, xc, W}, hd, nullptr, s);
+    wsweep(Vc, spx, br, L.nagg, L.pnnz, W, L.rrp.p, L.rci.p, WRestrict<SYS, float, T>{L.rv32.p, r, bc, swc, xc, W}, hd, nullptr, s);
   }
 }
 
@@ -1110,11 +1205,11 @@ template <bool SYS, class T>
 void w_prolong(Hierarchy& H, Level& L, int Vc, int spx, int br, int W, const T* xc, T* x, hipStream_t s) {
   const BatchHead* hd = H.bt.head.p;
   if constexpr (std::is_same<T, double>::value) {
-    wsweep(Vc, spx, br, L.n, W, L.prp.p, L.pci.p, WProlong<SYS, double, T>{L.pv.p, xc, x, W}, hd, nullptr, s);
+    wsweep(Vc, spx, br, L.n, L.pnnz, W, L.prp.p, L.pci.p, WProlong<SYS, double, T>{L.pv.p, xc, x, W}, hd, nullptr, s);
   } else if (H.bf16()) {
-    wsweep(Vc, spx, br, L.n, W, L.prp.p, L.pci.p, WProlong<SYS, uint16_t, T>{L.pbf.p, xc, x, W}, hd, nullptr, s);
+    wsweep(Vc, spx, br, L.n, L.pnnz, W, L.prp.p, L.pci.p, WProlong<SYS, uint16_t, T>{L.pbf.p, xc, x, W}, hd, nullptr, s);
   } else {
-    wsweep(Vc, spx, br, L.n, W, L.prp.p, L.pci.p, WProlong<SYS, float, T>{L.pv32.p, xc, x, W}, hd, nullptr, s);
+    wsweep(Vc, spx, br, L.n, L.pnnz, W, L.prp.p, L.pci.p, WProlong<SYS, float, T>{L.pv32.p, xc, x, W}, hd, nullptr, s);
   }
 }
 
@@ -1135,10 +1230,10 @@ void wvcycle(Hierarchy& H, int W, const double* r0, double* z0, const double* q,
     {
       WInstScope is(H, KID_PRE, l, s);
       if (l == 0)
-        wsweep(Vc, BL.spxA, BL.brA, L.n, W, L.rp.p, L.ci.p,
+        wsweep(Vc, BL.spxA, BL.brA, L.n, L.nnz, W, L.rp.p, L.ci.p,
                WResid<SYS, T, double>{WB<T>::v(L), r0, WB<T>::x(BL), WB<T>::r(BL), W}, hd, nullptr, s);
       else
-        wsweep(Vc, BL.spxA, BL.brA, L.n, W, L.rp.p, L.ci.p,
+        wsweep(Vc, BL.spxA, BL.brA, L.n, L.nnz, W, L.rp.p, L.ci.p,
                WResid<SYS, T, T>{WB<T>::v(L), WB<T>::b(BL), WB<T>::x(BL), WB<T>::r(BL), W}, hd, nullptr, s);
     }
     Level& Ln = H.lv[l + 1];
@@ -1169,13 +1264,13 @@ void wvcycle(Hierarchy& H, int W, const double* r0, double* z0, const double* q,
     if (l == 0) {
       int np = 0;
       if (red == 2)
-        np = wsweep(Vc, BL.spxA, BL.brA, L.n, W, L.rp.p, L.ci.p, WPost<SYS, T, double, double, 2>{vv, sw, r0, WB<T>::x(BL), z0, q, W},
+        np = wsweep(Vc, BL.spxA, BL.brA, L.n, L.nnz, W, L.rp.p, L.ci.p, WPost<SYS, T, double, double, 2>{vv, sw, r0, WB<T>::x(BL), z0, q, W},
                     hd, part, s);
       else if (red == 1)
-        np = wsweep(Vc, BL.spxA, BL.brA, L.n, W, L.rp.p, L.ci.p, WPost<SYS, T, double, double, 1>{vv, sw, r0, WB<T>::x(BL), z0, q, W},
+        np = wsweep(Vc, BL.spxA, BL.brA, L.n, L.nnz, W, L.rp.p, L.ci.p, WPost<SYS, T, double, double, 1>{vv, sw, r0, WB<T>::x(BL), z0, q, W},
                     hd, part, s);
       else
-        wsweep(Vc, BL.spxA, BL.brA, L.n, W, L.rp.p, L.ci.p, WPost<SYS, T, double, double, 0>{vv, sw, r0, WB<T>::x(BL), z0, q, W}, hd,
+        wsweep(Vc, BL.spxA, BL.brA, L.n, L.nnz, W, L.rp.p, L.ci.p, WPost<SYS, T, double, double, 0>{vv, sw, r0, WB<T>::x(BL), z0, q, W}, hd,
                nullptr, s);
       is.end();
       if (red == 2)
@@ -1183,7 +1278,7 @@ void wvcycle(Hierarchy& H, int W, const double* r0, double* z0, const double* q,
       else if (red == 1)
         hipLaunchKernelGGL(k_wfin_beta<1>, dim3(W), dim3(kWFin), 0, s, B.ctl.p, B.head.p, part, W, np);
     } else {
-      wsweep(Vc, BL.spxA, BL.brA, L.n, W, L.rp.p, L.ci.p,
+      wsweep(Vc, BL.spxA, BL.brA, L.n, L.nnz, W, L.rp.p, L.ci.p,
              WPost<SYS, T, T, T, 0>{vv, sw, WB<T>::b(BL), WB<T>::x(BL), WB<T>::r(BL), nullptr, W}, hd, nullptr, s);
       res = WB<T>::r(BL);
     }
@@ -1243,12 +1338,12 @@ void read_batch(Hierarchy& H, int W, hipStream_t s) {
 // operands and the fastest is kept and recorded in the tuning cache.
 
 template <class Op>
-double time_wide(int Vc, int spx, int br, int n, int W, const int* rp, const int* ci, const Op& op, hipStream_t s,
+double time_wide(int Vc, int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op, hipStream_t s,
                  hipEvent_t e0, hipEvent_t e1) {
-  wsweep(Vc, spx, br, n, W, rp, ci, op, nullptr, nullptr, s);
+  wsweep(Vc, spx, br, n, nnz, W, rp, ci, op, nullptr, nullptr, s);
   AMG_HIP(hipEventRecord(e0, s));
   constexpr int reps = 3;
-  for (int r = 0; r < reps; ++r) wsweep(Vc, spx, br, n, W, rp, ci, op, nullptr, nullptr, s);
+  for (int r = 0; r < reps; ++r) wsweep(Vc, spx, br, n, nnz, W, rp, ci, op, nullptr, nullptr, s);
   AMG_HIP(hipEventRecord(e1, s));
   AMG_HIP(hipEventSynchronize(e1));
   float ms = 0.f;
@@ -1286,7 +1381,7 @@ int pick_spx(Hierarchy& H, const char* kind, int W, int& br, int n, int nnz, con
   double tbest = 1e300;
   for (int form : {br, 0}) {  // staged (when the blocks fit), then direct
     for (int spx : spx_candidates()) {
-      const double t = time_wide(Vc, spx, form, n, W, rp, ci, op, s, e0, e1);
+      const double t = time_wide(Vc, spx, form, n, nnz, W, rp, ci, op, s, e0, e1);
       if (t < tbest) {
         tbest = t;
         best = spx;
@@ -1403,7 +1498,7 @@ amg_status solve_wide_impl(Hierarchy& H, const SolveOpts& o, const double* d_b, 
     int np;
     {
       WInstScope is(H, KID_SPMV_DOT, 0, stq);
-      np = wsweep(4, B.lv[0].spxA, B.lv[0].brA, n, W, L0.rp.p, L0.ci.p,
+      np = wsweep(4, B.lv[0].spxA, B.lv[0].brA, n, L0.nnz, W, L0.rp.p, L0.ci.p,
                   WSpmvXpay<SYS>{L0.v.p, B.z.p, pb[c], pb[c ^ 1], B.q.p, B.ctl.p, W}, B.head.p, part, stq);
     }
     hipLaunchKernelGGL(k_wfin_alpha, dim3(W), dim3(kWFin), 0, stq, B.ctl.p, B.head.p, part, W, np);
@@ -1468,7 +1563,7 @@ amg_status solve_wide_impl(Hierarchy& H, const SolveOpts& o, const double* d_b, 
     // true residuals of every column
     // the caller's x and b take two columns per lane only when 16-byte aligned
     const bool al = (((uintptr_t)d_x | (uintptr_t)d_b) & 15) == 0;
-    const int np = wsweep(al ? 4 : 1, B.lv[0].spxA, B.lv[0].brA, n, W, L0.rp.p, L0.ci.p,
+    const int np = wsweep(al ? 4 : 1, B.lv[0].spxA, B.lv[0].brA, n, L0.nnz, W, L0.rp.p, L0.ci.p,
                           WTrueResid<SYS>{L0.v.p, d_x, d_b, B.r.p, W}, nullptr, part, s);
     hipLaunchKernelGGL(k_wfin_trr, dim3(W), dim3(kWFin), 0, s, B.ctl.p, part, W, np);
     read_batch(H, W, s);
