@@ -1109,6 +1109,42 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_update(Ctl* ctl, const double
   }
 }
 
+// Plain CG (z = r): <r, z> = ||r||^2, so the update's sum also gives beta.
+__global__ void __launch_bounds__(kFinBlock) k_fin_update_plain(Ctl* ctl, const double* __restrict__ partials,
+                                                                int np) {
+  if (ctl->done) return;
+  double t[1];
+  fold_partials<1>(partials, np, t);
+  if (threadIdx.x != 0) return;
+  const double rr = t[0];
+  ctl->rr = rr;
+  ctl->iters += 1;
+  int st = 0;
+  if (rr <= ctl->thresh) st = 1;
+  else if (!(rr == rr)) st = -1;
+  else if (ctl->iters >= ctl->maxiter) st = 2;
+  if (st) {
+    ctl->state = st;
+    ctl->done = 1;
+    return;
+  }
+  ctl->beta = rr / ctl->rz;
+  ctl->rz = rr;
+}
+
+// Plain CG, (re)start: <r, z> = ||r||^2 of the right-hand side or of the true
+// residual.
+__global__ void k_plain_start(Ctl* ctl, int restart) {
+  if (ctl->done) return;
+  const double rz = restart ? ctl->trr : ctl->bb;
+  ctl->rz = rz;
+  ctl->beta = 0.0;
+  if (!(rz > 0.0)) {
+    ctl->state = -1;
+    ctl->done = 1;
+  }
+}
+
 // Folded solve, end of a chunk of iterations: the outcome of its last update
 // (of parity par) for the host; the next product sweep would find the same.
 __global__ void __launch_bounds__(kFinBlock) k_fin_chunk(Ctl* ctl, const double* __restrict__ pu, int np, int par) {
@@ -1903,8 +1939,9 @@ double kernel_bytes(const Hierarchy& H, int kid, int level, int flexible) {
 // Bytes of one PCG iteration (SpMV+dot, update, V-cycle, direction update).
 double iteration_bytes(const Hierarchy& H, int flexible) {
   const int nl = (int)H.lv.size();
-  if (!H.prm.precondition)  // plain CG: z = r (16n), <r,z>, <z,q> partials (24n)
-    return kernel_bytes(H, KID_SPMV_DOT, 0, flexible) + kernel_bytes(H, KID_CG_UPDATE, 0, flexible) + 40.0 * H.n;
+  if (!H.prm.precondition)  // plain CG; with the flexible beta also z = r (16n), <r,z> and <z,q> partials (24n)
+    return kernel_bytes(H, KID_SPMV_DOT, 0, flexible) + kernel_bytes(H, KID_CG_UPDATE, 0, flexible) +
+           (flexible ? 40.0 * H.n : 0.0);
   double b = kernel_bytes(H, KID_SPMV_DOT, 0, flexible) + kernel_bytes(H, KID_CG_UPDATE, 0, flexible) +
              kernel_bytes(H, KID_XPAY, 0, flexible) + kernel_bytes(H, KID_COARSE, nl - 1, flexible);
   for (int l = 0; l < nl - 1; ++l) {
@@ -2062,12 +2099,20 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   // folded form: no finalize launches, the consuming kernels sum the partials
   // (each reduction in a region of its own: product, update, V-cycle)
   const int64_t region = partials_region(H);
-  const bool fold = multi && H.lf == 0 && region <= kFoldMax;
+  // plain CG with the standard beta: z = r needs no copy and <r, z> = ||r||^2
+  // no sum of its own (10^7 unknowns: the copy and the dots were 63 of 320 us
+  // per iteration, the unused x0 = sw o r another 34)
+  const bool plain = !H.prm.precondition && !flexible;
+  const bool fold = (plain || (multi && H.lf == 0)) && region <= kFoldMax;
   double* pu = fold ? part + region : part;
   double* pz = fold ? part + 2 * region : part;
   int npz = 0;
-  hipLaunchKernelGGL(k_cg_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, w.r, d_x, part);
-  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, flexible,
+  double* zv = plain ? w.r : w.z;
+  // partials of ||b||^2 and of the true residual: plain folded solves start
+  // from them (pz), so they stay out of the product sweep's region
+  double* p0 = plain && fold ? pz : part;
+  hipLaunchKernelGGL(k_cg_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, w.r, d_x, p0);
+  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, p0, gv, tol, o.maxiter, flexible,
                      d_x);
   AMG_HIP(hipGetLastError());
   // search directions alternate between two buffers (the fused direction
@@ -2082,23 +2127,24 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       {
         InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
         np = sweep(L0.shA, n, L0.arp(), L0.aci(),
-                   OpSpmvFold{L0.av(), w.z, pb[c], pb[c ^ 1], w.q, ctl, pz, pu, npz, gv, nz, first, c}, ctl, part, st);
+                   OpSpmvFold{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, plain && !first ? pu : pz, pu,
+                              plain && !first ? gv : npz, gv, nz, first, c}, ctl, part, st);
       }
       {
         InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
-        if (H.fp32())
+        if (x0_mode(H) == X0_COPY)
           hipLaunchKernelGGL((k_cg_update_fold<X0_COPY, float>), dim3(gv), dim3(kBlock), 0, st, n, w.r, pb[c ^ 1], w.q,
                              Bufs<float>::x(L0), ctl, part, np, pu, c);
         else
           hipLaunchKernelGGL((k_cg_update_fold<X0_NONE, double>), dim3(gv), dim3(kBlock), 0, st, n, w.r, pb[c ^ 1],
                              w.q, (double*)nullptr, ctl, part, np, pu, c);
       }
-      vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, flexible ? 2 : 1, 0, 1, 1}, st);
+      if (!plain) vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, flexible ? 2 : 1, 0, 1, 1}, st);
       return;
     }
     {
       InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
-      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvXpayDev{L0.av(), w.z, pb[c], pb[c ^ 1], w.q, ctl, first},
+      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvXpayDev{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, first},
                  ctl, part, st);
     }
     hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kFinBlock), 0, st, ctl, part, np);
@@ -2106,6 +2152,10 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
       if (H.fp32()) launch_cg_update<float>(H, w, n, pb[c ^ 1], st);
       else launch_cg_update<double>(H, w, n, pb[c ^ 1], st);
+    }
+    if (plain) {
+      hipLaunchKernelGGL(k_fin_update_plain, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
+      return;
     }
     hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
     CycleArgs a{w.r, w.z, w.q, ctl, part, flexible ? 2 : 1, 0, multi ? 1 : 0};
@@ -2128,8 +2178,14 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       if (H.fp32()) launch_sw_mul<float>(H, w, n, s);
       else launch_sw_mul<double>(H, w, n, s);
     }
-    CycleArgs a0{w.r, w.z, w.q, ctl, pz, 1, 1, multi ? 1 : 0, fold ? 1 : 0};
-    npz = vcycle(H, a0, s);
+    if (!plain) {
+      CycleArgs a0{w.r, w.z, w.q, ctl, pz, 1, 1, multi ? 1 : 0, fold ? 1 : 0};
+      npz = vcycle(H, a0, s);
+    } else if (fold) {
+      npz = restarts ? L0.shA.grid : gv;
+    } else {
+      hipLaunchKernelGGL(k_plain_start, dim3(1), dim3(1), 0, s, ctl, restarts ? 1 : 0);
+    }
     int first = 1;
     // Iterations are queued in chunks; between chunks the host reads the
     // control block and sizes the next chunk from the observed decay of
@@ -2182,8 +2238,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       break;
     }
     // true residual r = b - A x
-    const int np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpTrueResid{L0.av(), d_x, d_b, w.r}, nullptr, part, s);
-    hipLaunchKernelGGL(k_fin_trr, dim3(1), dim3(kFinBlock), 0, s, ctl, part, np);
+    const int np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpTrueResid{L0.av(), d_x, d_b, w.r}, nullptr, p0, s);
+    hipLaunchKernelGGL(k_fin_trr, dim3(1), dim3(kFinBlock), 0, s, ctl, p0, np);
     read_ctl(w, s);
     const Ctl& c = *w.h_ctl;
     if (c.trr <= c.thresh) {
