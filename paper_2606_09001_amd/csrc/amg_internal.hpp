@@ -159,7 +159,8 @@ struct TBuf : DBuf<T> {
 // with `g` lanes; vec (fallback for very long rows): `g` lanes per row read
 // the row directly.
 struct Shape {
-  int stream = 1;  // 1: CSR-stream, 0: lanes-per-row, 2: sliced (thread per row), 3: sliced, slot offsets
+  int stream = 1;  // 1: CSR-stream, 0: lanes-per-row, 2: sliced (thread per row), 3: sliced, slot offsets,
+                   // 4: the same with one value per slot
   int g = 1;
   int u = 8;       // CSR-stream: staged entries per thread (buffer of kBlock*u entries)
   int nt = 0;      // 1: the operator's entry stream is read with nontemporal loads
@@ -198,20 +199,26 @@ struct Level {
   // holds the entries with offset slots[j].x of all its rows, in ascending
   // offset order; slots[j].z/.w are the 64-bit mask of the rows that have
   // that entry.  Values as above (0 where masked); no column array.
+  //
+  // Uniform offset form: when every slot of every slice holds one value (the
+  // constant-coefficient operators), the sweeps read that value per slot (suv,
+  // a scalar load beside the slot record) instead of one per entry.  Decided
+  // from the values at setup and on every refresh.
   bool sell = false;
   int sell_form = 0;          // 1: explicit columns, 2: slot offsets
+  bool sell_uniform = false;
   int64_t sell_len = 0;
   DBuf<int> soff, sci, sperm;
   DBuf<int4> sslot;
-  DBuf<double> sv;
-  DBuf<float> sv32;
+  DBuf<double> sv, suv;
+  DBuf<float> sv32, suv32;
   // arrays the operator sweeps over A_l read (sliced when present)
   const int* arp() const { return sell ? soff.p : rp.p; }
   const int* aci() const {
     return sell ? (sell_form == 2 ? reinterpret_cast<const int*>(sslot.p) : sci.p) : ci.p;
   }
-  const double* av() const { return sell ? sv.p : v.p; }
-  const float* av32() const { return sell ? sv32.p : v32.p; }
+  const double* av() const { return sell_uniform ? suv.p : sell ? sv.p : v.p; }
+  const float* av32() const { return sell_uniform ? suv32.p : sell ? sv32.p : v32.p; }
   DBuf<int> diagpos;          // position of a_ii in row i
   DBuf<double> dinv;          // 1 / a_ii
   DBuf<double> sw;            // smoother weight per row (omega/a_ii or 1/sum|a_ij|)

@@ -885,6 +885,33 @@ __global__ void k_sell_vals(int64_t m, const int* __restrict__ sperm, const doub
   if (sv32) sv32[p] = (float)a;
 }
 
+// Uniform offset form: one wavefront per slice, the value of each slot's first
+// row into uv; flags[0] |= 1 where a row of the slot holds another value (bits
+// compared, so -0.0 and NaN payloads are kept apart).
+__global__ void __launch_bounds__(kBlock) k_sell_uniform(int ns, const int* __restrict__ soff,
+                                                         const int4* __restrict__ slots,
+                                                         const double* __restrict__ sv, double* __restrict__ uv,
+                                                         float* __restrict__ uv32, int* flags) {
+  const int sl = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (sl >= ns) return;
+  // once a slot has been found to differ, nothing here is used any more
+  if (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+  const int base = soff[sl], w = (soff[sl + 1] - base) >> 6;
+  bool bad = false;
+  for (int j = 0; j < w; ++j) {
+    const int4 r = slots[(base >> 6) + j];
+    const unsigned long long mask = ((unsigned long long)(unsigned)r.w << 32) | (unsigned)r.z;
+    const double x = sv[base + 64 * j + lane];
+    const double x0 = __shfl(x, (int)__builtin_ctzll(mask | (1ull << 63)), 64);
+    bad |= ((mask >> lane) & 1ull) && __double_as_longlong(x) != __double_as_longlong(x0);
+    if (lane == 0) {
+      uv[(base >> 6) + j] = x0;
+      if (uv32) uv32[(base >> 6) + j] = (float)x0;
+    }
+  }
+  if (__ballot(bad) && lane == 0) atomicOr(flags, 1);
+}
+
 // ---------------------------------------------------------- host helpers
 
 template <class F>
@@ -1323,6 +1350,21 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
     if (!L.sell) continue;
     hipLaunchKernelGGL(k_sell_vals, dim3(grid_for(L.sell_len)), dim3(kBlock), 0, s, L.sell_len, L.sperm.p, L.v.p,
                        L.sv.p, H.fp32() ? L.sv32.p : nullptr);
+    if (L.sell_form == 2) {
+      const int ns = (L.n + 63) / 64;
+      L.suv.alloc(L.sell_len / 64 + kSellMaxW);  // padded like the slot records
+      if (H.fp32()) L.suv32.alloc(L.sell_len / 64 + kSellMaxW);
+      if (build) {
+        AMG_HIP(hipMemsetAsync(L.suv.p, 0, L.suv.bytes(), s));
+        if (H.fp32()) AMG_HIP(hipMemsetAsync(L.suv32.p, 0, L.suv32.bytes(), s));
+      }
+      zero_flags(H.flags.p, 1, s);
+      hipLaunchKernelGGL(k_sell_uniform, dim3((ns + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, s, ns,
+                         L.soff.p, L.sslot.p, L.sv.p, L.suv.p, H.fp32() ? L.suv32.p : nullptr, H.flags.p);
+      sync_flags(H.flags.p, H.h_flags, 1, s);
+      L.sell_uniform = H.h_flags[0] == 0;
+      if (!build) L.shA.stream = L.sell_uniform ? 4 : 3;
+    }
   }
   AMG_HIP(hipGetLastError());
 }
