@@ -297,8 +297,8 @@ struct Ctl {
   double trr;             // true residual ||b - A x||^2
   double* x;              // the solve's iterate (captured iterations find it here, so a replay is not tied to
                           // the buffer it was captured with)
-  double rz2[2];          // folded solves: <r,z> by direction-buffer parity
-  int it2[2];             // folded solves: iterations by direction-buffer parity
+  double rz2[2];          // CG: <r,z> by direction-buffer parity
+  int it2[2];             // CG: iterations by direction-buffer parity
   int iters, maxiter;
   int done;               // nonzero: kernels of the current solve return at once
   int state;              // 0 running, 1 converged (recursive), 2 iteration limit, -1 breakdown
@@ -532,6 +532,9 @@ struct InstScope {
 };
 
 // ------------------------------------------------------- device helpers
+
+// Most partials per sum of a reduction that its consumers fold (solve.hip).
+constexpr int kFoldMax = 2048;
 
 constexpr int kBlock = 256;        // threads per block of the streaming kernels
 constexpr int kMaxGrid = 2048;     // blocks of grid-stride kernels

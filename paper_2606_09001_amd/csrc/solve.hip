@@ -30,6 +30,7 @@
 #include <cstdlib>
 #include <fstream>
 #include <functional>
+#include <initializer_list>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -68,20 +69,25 @@ inline int round8(int64_t g) {
 //   static constexpr int NRED     number of dot products reduced
 // and, with kFold, folds the partial sums of earlier kernels itself (see Fold).
 
-// Scalars from partial sums without a finalize launch.  On systems of a few
-// 100,000 rows a single-workgroup finalize kernel costs 2.7 us of an iteration
-// of ten kernels, almost all of it launch and load latency.  With at most
-// kFoldMax partials per sum every workgroup of the consuming kernel sums them
-// itself: the loads go out before the kernel's own (fold_load), the wave sums
-// are combined after its gathers (fold_total), in one fixed order, so every
-// workgroup holds the same bits.  2048 partials are 16 KB per workgroup from
-// L2; beyond that the finalize kernels stay.
-constexpr int kFoldMax = 2048;
+// CG and BiCGSTAB scalars from partial sums, without finalize kernels.  On
+// systems of a few 100,000 rows a single-workgroup finalize kernel costs 2.7 us
+// (launch and load latency), three or four times per iteration of about ten
+// kernels.  In solves whose reductions have at most kFoldMax partials every
+// workgroup of the consuming kernel sums them itself: at most 16 KB per sum from
+// L2, the loads issued before the kernel's own (fold_load) and the wave sums
+// combined after its gathers (fold_total), in one fixed order, so that every
+// workgroup holds the same bits.  In larger solves the workgroups that would do
+// so are too many (128^3: 8192 of 16 KB and two barriers each, 7.3 against 6.9
+// ms): a launch of k_sum forms the totals first (two per CG iteration where the
+// finalize kernels took three), and the consumers read one value per sum (tot).
+// (Fewer and longer workgroups, several row blocks each, keep the partials few
+// but overlap less: 192^3 mixed 25.8 against 23.6 ms.)
 
 struct NoFold {};
 
 // Sum over the workgroup's threads of np partials: per-thread sum.
-__device__ inline double fold_load(const double* __restrict__ p, int np) {
+__device__ inline double fold_load(const double* __restrict__ p, int np, bool tot) {
+  if (tot) return p[0];
   if (np <= kBlock) {
     const double a = p[min((int)threadIdx.x, np - 1)];
     return (int)threadIdx.x < np ? a : 0.0;
@@ -95,9 +101,11 @@ __device__ inline double fold_load(const double* __restrict__ p, int np) {
   return s;
 }
 
-// Combines NV per-thread sums; every thread gets the totals.  Two barriers.
+// Combines NV per-thread sums; every thread gets the totals.  Two barriers, none
+// where the sums are totals already (tot).
 template <int NV>
-__device__ inline void fold_total(double (&v)[NV]) {
+__device__ inline void fold_total(double (&v)[NV], bool tot) {
+  if (tot) return;
   __shared__ double fold_red[NV][kBlock / 64];
 #pragma unroll
   for (int m = 0; m < NV; ++m) {
@@ -120,45 +128,14 @@ __device__ inline void fold_total(double (&v)[NV]) {
 // A z + beta q (the same vector in exact arithmetic, since q = A p), so the
 // sweep gathers z only; p and q are read at the row itself (q is updated in
 // place by the row's own thread).  p' goes to the second direction buffer.
-// beta is read from the device control block.
-struct OpSpmvXpayDev {
+// beta, the convergence test of the last update and the <r, z> test come from
+// the partials of that update (pu) and of the V-cycle (pz).  Workgroup 0
+// records the outcome; what other workgroups read of the control block
+// (rz2[par], it2[par], pq) is not written in this kernel, and a workgroup that
+// sees `done` set by workgroup 0 would have found the same outcome itself.
+struct OpSpmvXpay {
   using PT = double;
   static constexpr int NRED = 1;
-  const double* v;
-  const double* z;
-  const double* p;
-  double* pn;
-  double* q;
-  const Ctl* ctl;
-  int first;
-  struct Row {
-    double pr, qo, beta;
-  };
-  __device__ PT prod_v(double a, int j) const { return a * z[j]; }
-  __device__ PT prod(int k, int j) const { return prod_v(v[k], j); }
-  __device__ Row row_in(int row) const {
-    if (first) return {z[row], 0.0, 0.0};
-    const double beta = ctl->beta;
-    return {z[row] + beta * p[row], q[row], beta};
-  }
-  __device__ void epi(int row, PT s, const Row& a, double* d) const {
-    pn[row] = a.pr;
-    const double qn = first ? s : s + a.beta * a.qo;
-    q[row] = qn;
-    d[0] += a.pr * qn;
-  }
-};
-
-// The same sweep in a folded solve: beta, the convergence test of the last
-// update and the <r, z> test come from the partials of that update (pu) and of
-// the V-cycle (pz) instead of from finalize kernels.  Workgroup 0 records the
-// outcome; what other workgroups read of the control block (rz2[par], it2[par],
-// pq) is not written in this kernel, and a workgroup that sees `done` set by
-// workgroup 0 would have found the same outcome itself.
-struct OpSpmvFold {
-  using PT = double;
-  static constexpr int NRED = 1;
-  static constexpr bool kFold = true;
   const double* v;
   const double* z;
   const double* p;
@@ -167,7 +144,7 @@ struct OpSpmvFold {
   Ctl* ctl;
   const double* pz;
   const double* pu;
-  int npz, npu, nz, first, par;
+  int npz, npu, nz, tot, first, par;
   struct Fold {
     double s[3], rz, pq, thresh;
     int it, maxiter, flexible;
@@ -180,9 +157,9 @@ struct OpSpmvFold {
   __device__ Row row_in(int row) const { return {z[row], first ? 0.0 : p[row], first ? 0.0 : q[row]}; }
   __device__ Fold fold_in() const {
     Fold f;
-    f.s[0] = fold_load(pz, npz);
-    f.s[1] = nz > 1 ? fold_load(pz + npz, npz) : 0.0;
-    f.s[2] = first ? 0.0 : fold_load(pu, npu);
+    f.s[0] = fold_load(pz, npz, tot);
+    f.s[1] = nz > 1 ? fold_load(pz + npz, npz, tot) : 0.0;
+    f.s[2] = first ? 0.0 : fold_load(pu, npu, tot);
     f.rz = ctl->rz2[par];
     f.pq = ctl->pq;
     f.thresh = ctl->thresh;
@@ -193,7 +170,7 @@ struct OpSpmvFold {
   }
   // beta of this iteration; false when the solve ends here
   __device__ bool fold_out(Fold& f, double& beta) const {
-    fold_total<3>(f.s);
+    fold_total<3>(f.s, tot);
     const double rzn = f.s[0], rr = f.s[2];
     int st = 0, it = f.it;
     if (!first) {
@@ -230,8 +207,8 @@ struct HasFold : std::false_type {};
 template <class Op>
 struct HasFold<Op, std::void_t<typename Op::Fold>> : std::true_type {};
 
-// The folding hooks of a sweep: fin before its own loads, fout and the row
-// epilogue after its row sums (nothing for operators that do not fold).
+// The folding hooks of a sweep: fold_in before its own loads, fold_out and the
+// row epilogue after its row sums (nothing for operators that do not fold).
 template <class Op>
 __device__ inline auto fold_in(const Op& op) {
   if constexpr (HasFold<Op>::value) return op.fold_in();
@@ -450,8 +427,8 @@ __device__ inline void publish_partials(double (&d)[NRED > 0 ? NRED : 1], double
 // entries; the shape sizes it to the matrix's largest row block, so that few
 // of the unconditional loads are clamped duplicates).
 template <int G3, int U, bool NT, class Op>
-__global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                                   Op op, const Ctl* __restrict__ ctl,
+__global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict__ rp,
+                                                   const int* __restrict__ ci, Op op, const Ctl* __restrict__ ctl,
                                                    double* __restrict__ partials) {
   if ((ctl && ctl->done) || n <= 0) return;
   constexpr int RB = kBlock / G3;
@@ -459,9 +436,10 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
   __shared__ int s_rp[RB + 1];
   __shared__ PT s_p[kBlock * U];
   auto fold = fold_in(op);
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
+  const int lr = threadIdx.x / G3, lane = threadIdx.x & (G3 - 1);
   const int r0 = logical_block() * RB;
   for (int t = threadIdx.x; t <= RB; t += kBlock) s_rp[t] = rp[min(r0 + t, n)];
-  const int lr = threadIdx.x / G3, lane = threadIdx.x & (G3 - 1);
   const int row = r0 + lr;
   const typename Op::Row in = op.row_in(min(row, n - 1));
   __syncthreads();
@@ -490,7 +468,6 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
     for (int k = s_rp[lr] - k0 + lane; k < e; k += G3) s += s_p[k];
   }
   s = group_sum<G3>(s);
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
   if (!fold_out(op, fold, beta)) return;
   if (row < n && group_leader<G3>()) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
@@ -538,10 +515,12 @@ __global__ void __launch_bounds__(kBlock) k_vec(int n, const int* __restrict__ r
 // entries (column -1) are masked out of the sum.  Each row sums its entries
 // in stored order (the same fold as a one-lane CSR sweep).
 template <bool NT, class Op>
-__global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ soff, const int* __restrict__ sci,
-                                                 Op op, const Ctl* __restrict__ ctl, double* __restrict__ partials) {
+__global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ soff,
+                                                 const int* __restrict__ sci, Op op, const Ctl* __restrict__ ctl,
+                                                 double* __restrict__ partials) {
   if (n <= 0) return;
   using PT = typename Op::PT;
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
   const int row = logical_block() * kBlock + threadIdx.x;
   const int rc = min(row, n - 1);
   // the wave's 64 rows are one slice: its offsets are scalar loads, which
@@ -567,7 +546,6 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
   PT s = 0;
 #pragma unroll
   for (int j = 0; j < kSellMaxW; ++j) s = j < w && col[j] >= 0 ? s + pv[j] : s;
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
   if (!fold_out(op, fold, beta)) return;
   if (row < n) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
@@ -581,10 +559,12 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
 // entry.  Constant-coefficient operators then cost their vectors: 128^3
 // Poisson, FP64: residual 24 -> 14 us, product 31 -> 23, post-smoother 36 -> 19.
 template <bool NT, bool UNI, class Op>
-__global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__ soff, const int4* __restrict__ slots,
-                                                  Op op, const Ctl* __restrict__ ctl, double* __restrict__ partials) {
+__global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__ soff,
+                                                  const int4* __restrict__ slots, Op op, const Ctl* __restrict__ ctl,
+                                                  double* __restrict__ partials) {
   if (n <= 0) return;
   using PT = typename Op::PT;
+  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
   const int row = logical_block() * kBlock + threadIdx.x;
   const int rc = min(row, n - 1);
   const int sl = __builtin_amdgcn_readfirstlane(rc >> 6), lane = rc & 63;
@@ -617,7 +597,6 @@ __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__
   PT s = 0;
 #pragma unroll
   for (int j = 0; j < kSellMaxW; ++j) s = has[j] ? s + pv[j] : s;
-  double d[Op::NRED > 0 ? Op::NRED : 1] = {}, beta = 0.0;
   if (!fold_out(op, fold, beta)) return;
   if (row < n) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
@@ -648,12 +627,12 @@ void sweep_form(const Shape& sh, int n, const int* rp, const int* ci, const Op& 
   } else if (sh.stream) {
     switch (sh.u) {
       case 4:
-        AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 4, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp,
-                                                ci, op, ctl, partials));
+        AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 4, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n,
+                                                rp, ci, op, ctl, partials));
         break;
       case 8:
-        AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 8, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp,
-                                                ci, op, ctl, partials));
+        AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 8, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n,
+                                                rp, ci, op, ctl, partials));
         break;
       default:
         AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 12, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n,
@@ -707,8 +686,10 @@ inline int vec_grid(int n) { return round8(((int64_t)n + kBlock * kVecPer - 1) /
 __device__ inline int vec_base() { return logical_block() * (kBlock * kVecPer); }
 
 // r = b, x = 0, partial <b, b>.
-__global__ void __launch_bounds__(kBlock) k_cg_init(int n, const double* __restrict__ b, double* __restrict__ r,
-                                                    double* __restrict__ x, double* __restrict__ partials) {
+__global__ void __launch_bounds__(kBlock) k_cg_init(int n, const double* __restrict__ b,
+                                                    double* __restrict__ r, double* __restrict__ x,
+                                                    double* __restrict__ partials) {
+  double d[1] = {0.0};
   const int base = vec_base();
   double bv[kVecPer];
 #pragma unroll
@@ -716,7 +697,6 @@ __global__ void __launch_bounds__(kBlock) k_cg_init(int n, const double* __restr
     const int i = base + threadIdx.x + u * kBlock;
     bv[u] = i < n ? b[i] : 0.0;
   }
-  double d[1] = {0.0};
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
@@ -740,29 +720,47 @@ X0Mode x0_mode(const Hierarchy& H) {
   return H.fp32() ? X0_COPY : X0_NONE;
 }
 
-// x += alpha p ; r -= alpha q ; partial <r, r>; and x0 (see X0Mode).
+// x += alpha p ; r -= alpha q ; partials <r, r> (pu); and x0 (see X0Mode).
+// alpha from the product sweep's partials (pa) and the <r, z> of parity
+// par ^ 1 that it recorded.  Workgroup 0 records <p, q> and a breakdown.
 template <int MODE, class T>
 __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict__ r,
                                                       const double* __restrict__ p, const double* __restrict__ q,
-                                                      const T* __restrict__ sw, T* __restrict__ x0,
-                                                      const Ctl* __restrict__ ctl, double* __restrict__ partials) {
-  if (ctl->done) return;
-  const double alpha = ctl->alpha;
+                                                      const T* __restrict__ sw, T* __restrict__ x0, Ctl* ctl,
+                                                      const double* __restrict__ pa, int npa, int tot,
+                                                      double* __restrict__ pu, int par) {
+  const int done = ctl->done;
+  const double rz = ctl->rz2[par ^ 1];
+  const int iters = ctl->it2[par ^ 1];
   double* __restrict__ x = ctl->x;
+  if (done) return;
+  double f[1] = {fold_load(pa, npa, tot)};
+  double alpha = 0.0, d[1] = {0.0};
   const int base = vec_base();
   double xv[kVecPer], rv[kVecPer], pv[kVecPer], qv[kVecPer];
   T wv[kVecPer];
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
-    const int i = base + threadIdx.x + u * kBlock;
-    const bool ok = i < n;
-    xv[u] = ok ? x[i] : 0.0;
-    rv[u] = ok ? r[i] : 0.0;
-    pv[u] = ok ? p[i] : 0.0;
-    qv[u] = ok ? q[i] : 0.0;
-    if constexpr (MODE == X0_SMOOTHED) wv[u] = ok ? sw[i] : (T)0;
+    const int i = min(base + (int)threadIdx.x + u * kBlock, n - 1);
+    rv[u] = r[i];
+    pv[u] = p[i];
+    qv[u] = q[i];
+    xv[u] = x[i];
+    if constexpr (MODE == X0_SMOOTHED) wv[u] = sw[i];
   }
-  double d[1] = {0.0};
+  fold_total<1>(f, tot);
+  const double pq = f[0];
+  const bool ok = pq > 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctl->pq = pq;
+    if (!ok) {
+      ctl->iters = iters;
+      ctl->state = -1;
+      ctl->done = 1;
+    }
+  }
+  if (!ok) return;
+  alpha = rz / pq;
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
@@ -771,58 +769,6 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict_
       const double ri = rv[u] - alpha * qv[u];
       r[i] = ri;
       if constexpr (MODE == X0_SMOOTHED) x0[i] = wv[u] * (T)ri;
-      if constexpr (MODE == X0_COPY) x0[i] = (T)ri;
-      d[0] += ri * ri;
-    }
-  }
-  publish_partials<1>(d, partials);
-}
-
-// The same update in a folded solve: alpha from the product sweep's partials
-// (pa), <r, z> of parity par ^ 1 as that sweep recorded it; its own partials go
-// to pu.  Workgroup 0 records <p, q> and a breakdown.
-template <int MODE, class T>
-__global__ void __launch_bounds__(kBlock) k_cg_update_fold(int n, double* __restrict__ r, const double* __restrict__ p,
-                                                           const double* __restrict__ q, T* __restrict__ x0, Ctl* ctl,
-                                                           const double* __restrict__ pa, int npa,
-                                                           double* __restrict__ pu, int par) {
-  const int done = ctl->done;
-  const double rz = ctl->rz2[par ^ 1];
-  const int it = ctl->it2[par ^ 1];
-  double* __restrict__ x = ctl->x;
-  if (done) return;
-  double f[1] = {fold_load(pa, npa)};
-  const int base = vec_base();
-  double xv[kVecPer], rv[kVecPer], pv[kVecPer], qv[kVecPer];
-#pragma unroll
-  for (int u = 0; u < kVecPer; ++u) {
-    const int i = min(base + (int)threadIdx.x + u * kBlock, n - 1);
-    rv[u] = r[i];
-    pv[u] = p[i];
-    qv[u] = q[i];
-    xv[u] = x[i];
-  }
-  fold_total<1>(f);
-  const double pq = f[0];
-  const bool ok = pq > 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctl->pq = pq;
-    if (!ok) {
-      ctl->iters = it;
-      ctl->state = -1;
-      ctl->done = 1;
-    }
-  }
-  if (!ok) return;
-  const double alpha = rz / pq;
-  double d[1] = {0.0};
-#pragma unroll
-  for (int u = 0; u < kVecPer; ++u) {
-    const int i = base + threadIdx.x + u * kBlock;
-    if (i < n) {
-      x[i] = xv[u] + alpha * pv[u];
-      const double ri = rv[u] - alpha * qv[u];
-      r[i] = ri;
       if constexpr (MODE == X0_COPY) x0[i] = (T)ri;
       d[0] += ri * ri;
     }
@@ -857,12 +803,12 @@ __global__ void __launch_bounds__(kBlock) k_sw_mul(int n, const T* __restrict__ 
 }
 
 // <r, z> and <z, q> partials after a single-level (direct) preconditioner.
-__global__ void __launch_bounds__(kBlock) k_dots_rz(int n, const double* __restrict__ r, const double* __restrict__ z,
-                                                    const double* __restrict__ q, const Ctl* __restrict__ ctl,
-                                                    double* __restrict__ partials) {
+__global__ void __launch_bounds__(kBlock) k_dots_rz(int n, const double* __restrict__ r,
+                                                    const double* __restrict__ z, const double* __restrict__ q,
+                                                    const Ctl* __restrict__ ctl, double* __restrict__ partials) {
   if (ctl->done) return;
-  const int base = vec_base();
   double d[2] = {0.0, 0.0};
+  const int base = vec_base();
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
@@ -911,14 +857,20 @@ __global__ void __launch_bounds__(kBlock) k_bi_init(int n, const double* __restr
 // p = r on the first iteration of a (re)start, else p = r + beta (p - omega v);
 // with x0, also the next V-cycle's level-0 pre-smoothed iterate x0 = sw o p
 // (cycle precision T), so that its first sweep only forms the residual, or,
-// without sw, p rounded to T.
+// without sw, p rounded to T.  ||r||^2 and <r^, r> of the last full step come
+// from its partials (pf): the stop test, rho and beta = (rho / rho_old)
+// (alpha / omega).  rho goes to ctl->rz (rho, alpha and omega are read here and
+// written by later kernels only).
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restrict__ r,
                                                    const double* __restrict__ v, double* __restrict__ p,
-                                                   const T* __restrict__ sw, T* __restrict__ x0,
-                                                   const Ctl* __restrict__ ctl, int first) {
-  if (ctl->done) return;
-  const double beta = ctl->beta, omega = ctl->omega;
+                                                   const T* __restrict__ sw, T* __restrict__ x0, Ctl* ctl, int first,
+                                                   const double* __restrict__ pf, int npf, int tot) {
+  const int done = ctl->done, iters = ctl->iters, maxiter = ctl->maxiter;
+  const double rho0 = ctl->rho, alpha = ctl->alpha, omega = ctl->omega, thresh = ctl->thresh;
+  if (done) return;
+  double f[2] = {first ? 0.0 : fold_load(pf, npf, tot), first ? 0.0 : fold_load(pf + npf, npf, tot)};
+  double beta = 0.0;
   const int base = vec_base();
   double rv[kVecPer], vv[kVecPer], pv[kVecPer];
   T wv[kVecPer];
@@ -930,6 +882,25 @@ __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restri
     pv[u] = p[i];
     wv[u] = x0 && sw ? sw[i] : (T)1;
   }
+  fold_total<2>(f, tot);
+  const double rr = f[0], rho = first ? rho0 : f[1];
+  int st = 0;
+  if (!first) {
+    if (rr <= thresh) st = 1;
+    else if (!(rr == rr)) st = -1;
+    else if (iters >= maxiter) st = 2;
+    else if (!(rho != 0.0) || !(rho == rho)) st = -1;
+  }
+  beta = first ? 0.0 : (rho / rho0) * (alpha / omega);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctl->rz = rho;
+    if (!first) ctl->rr = rr;
+    if (st) {
+      ctl->state = st;
+      ctl->done = 1;
+    }
+  }
+  if (st) return;
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
@@ -941,29 +912,45 @@ __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restri
   }
 }
 
-// x += alpha y ; s = r - alpha v ; partial <s, s>; with x0 also x0 = sw o s.
+// alpha = rho / <r^, v> (partials pa); x += alpha y ; s = r - alpha v ; partials
+// <s, s> (ps); with x0 also x0 = sw o s.
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_bi_half(int n, const double* __restrict__ y,
                                                     const double* __restrict__ r, const double* __restrict__ v,
                                                     double* __restrict__ sv, const T* __restrict__ sw,
-                                                    T* __restrict__ x0, const Ctl* __restrict__ ctl,
-                                                    double* __restrict__ partials) {
-  if (ctl->done) return;
-  const double alpha = ctl->alpha;
+                                                    T* __restrict__ x0, Ctl* ctl, const double* __restrict__ pa,
+                                                    int npa, int tot, double* __restrict__ ps) {
+  const int done = ctl->done;
+  const double rho = ctl->rz;
   double* __restrict__ x = ctl->x;
+  if (done) return;
+  double f[1] = {fold_load(pa, npa, tot)};
+  double alpha = 0.0, d[1] = {0.0};
   const int base = vec_base();
   double xv[kVecPer], yv[kVecPer], rv[kVecPer], vv[kVecPer];
   T wv[kVecPer];
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = min(base + (int)threadIdx.x + u * kBlock, n - 1);
-    xv[u] = x[i];
     yv[u] = y[i];
     rv[u] = r[i];
     vv[u] = v[i];
+    xv[u] = x[i];
     wv[u] = x0 && sw ? sw[i] : (T)1;
   }
-  double d[1] = {0.0};
+  fold_total<1>(f, tot);
+  const bool ok = f[0] != 0.0 && f[0] == f[0];
+  alpha = rho / f[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctl->rho = rho;
+    if (ok) {
+      ctl->alpha = alpha;
+    } else {
+      ctl->state = -1;
+      ctl->done = 1;
+    }
+  }
+  if (!ok) return;
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
@@ -975,29 +962,51 @@ __global__ void __launch_bounds__(kBlock) k_bi_half(int n, const double* __restr
       d[0] += si * si;
     }
   }
-  publish_partials<1>(d, partials);
+  publish_partials<1>(d, ps);
 }
 
-// x += omega z ; r = s - omega t ; partials <r, r>, <r^, r>.
+// ||s||^2 (ps) ends the solve with x = x + alpha y, which is written already;
+// else omega = <t, s> / <t, t> (pt), x += omega z ; r = s - omega t ; partials
+// <r, r>, <r^, r> (pf).  The iteration is counted here.
 __global__ void __launch_bounds__(kBlock) k_bi_full(int n, const double* __restrict__ z,
                                                     const double* __restrict__ sv, const double* __restrict__ t,
-                                                    const double* __restrict__ rh, double* __restrict__ r,
-                                                    const Ctl* __restrict__ ctl, double* __restrict__ partials) {
-  if (ctl->done) return;
-  const double omega = ctl->omega;
+                                                    const double* __restrict__ rh, double* __restrict__ r, Ctl* ctl,
+                                                    const double* __restrict__ ps, int nps,
+                                                    const double* __restrict__ pt, int npt, int tot, double* __restrict__ pf) {
+  const int done = ctl->done;
+  const double thresh = ctl->thresh;
   double* __restrict__ x = ctl->x;
+  if (done) return;
+  double f[3] = {fold_load(ps, nps, tot), fold_load(pt, npt, tot), fold_load(pt + npt, npt, tot)};
+  double omega = 0.0, d[2] = {0.0, 0.0};
   const int base = vec_base();
   double xv[kVecPer], zv[kVecPer], sl[kVecPer], tv[kVecPer], hv[kVecPer];
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = min(base + (int)threadIdx.x + u * kBlock, n - 1);
-    xv[u] = x[i];
     zv[u] = z[i];
     sl[u] = sv[i];
     tv[u] = t[i];
     hv[u] = rh[i];
+    xv[u] = x[i];
   }
-  double d[2] = {0.0, 0.0};
+  fold_total<3>(f, tot);
+  const double ss = f[0], ts = f[1], tt = f[2];
+  omega = ts / tt;
+  int st = 0;
+  if (ss <= thresh) st = 1;
+  else if (!(ss == ss)) st = -1;
+  else if (!(tt > 0.0) || !(omega != 0.0) || !(omega == omega)) st = -1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctl->rr = ss;
+    ctl->iters += 1;
+    ctl->omega = omega;
+    if (st) {
+      ctl->state = st;
+      ctl->done = 1;
+    }
+  }
+  if (st) return;
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
     const int i = base + threadIdx.x + u * kBlock;
@@ -1009,7 +1018,7 @@ __global__ void __launch_bounds__(kBlock) k_bi_full(int n, const double* __restr
       d[1] += hv[u] * ri;
     }
   }
-  publish_partials<2>(d, partials);
+  publish_partials<2>(d, pf);
 }
 
 // ------------------------------------------------------- finalize kernels
@@ -1052,6 +1061,19 @@ __device__ inline void fold_partials(const double* __restrict__ partials, int np
   }
 }
 
+// Sums of long partial arrays: value blockIdx.x of the launch sums the np
+// entries of its array into out[blockIdx.x].
+struct SumArgs {
+  const double* src[4];
+  int np[4];
+};
+__global__ void __launch_bounds__(kFinBlock) k_sum(SumArgs a, double* __restrict__ out, const Ctl* __restrict__ ctl) {
+  if (ctl->done) return;
+  double t[1];
+  fold_partials<1>(a.src[blockIdx.x], a.np[blockIdx.x], t);
+  if (threadIdx.x == 0) out[blockIdx.x] = t[0];
+}
+
 __global__ void __launch_bounds__(kFinBlock) k_fin_init(Ctl* ctl, const double* __restrict__ partials, int np,
                                                         double tol, int maxiter, int flexible, double* x) {
   double t[1];
@@ -1081,78 +1103,7 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_init(Ctl* ctl, const double* 
   }
 }
 
-__global__ void __launch_bounds__(kFinBlock) k_fin_alpha(Ctl* ctl, const double* __restrict__ partials, int np) {
-  if (ctl->done) return;
-  double t[1];
-  fold_partials<1>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double pq = t[0];
-  ctl->pq = pq;
-  if (!(pq > 0.0)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  } else {
-    ctl->alpha = ctl->rz / pq;
-  }
-}
-
-__global__ void __launch_bounds__(kFinBlock) k_fin_update(Ctl* ctl, const double* __restrict__ partials, int np) {
-  if (ctl->done) return;
-  double t[1];
-  fold_partials<1>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double rr = t[0];
-  ctl->rr = rr;
-  ctl->iters += 1;
-  if (rr <= ctl->thresh) {
-    ctl->state = 1;
-    ctl->done = 1;
-  } else if (!(rr == rr)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  } else if (ctl->iters >= ctl->maxiter) {
-    ctl->state = 2;
-    ctl->done = 1;
-  }
-}
-
-// Plain CG (z = r): <r, z> = ||r||^2, so the update's sum also gives beta.
-__global__ void __launch_bounds__(kFinBlock) k_fin_update_plain(Ctl* ctl, const double* __restrict__ partials,
-                                                                int np) {
-  if (ctl->done) return;
-  double t[1];
-  fold_partials<1>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double rr = t[0];
-  ctl->rr = rr;
-  ctl->iters += 1;
-  int st = 0;
-  if (rr <= ctl->thresh) st = 1;
-  else if (!(rr == rr)) st = -1;
-  else if (ctl->iters >= ctl->maxiter) st = 2;
-  if (st) {
-    ctl->state = st;
-    ctl->done = 1;
-    return;
-  }
-  ctl->beta = rr / ctl->rz;
-  ctl->rz = rr;
-}
-
-// Plain CG, (re)start: <r, z> = ||r||^2 of the right-hand side or of the true
-// residual.
-__global__ void k_plain_start(Ctl* ctl, int restart) {
-  if (ctl->done) return;
-  const double rz = restart ? ctl->trr : ctl->bb;
-  ctl->rz = rz;
-  ctl->beta = 0.0;
-  if (!(rz > 0.0)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  }
-}
-
-// Folded solve, end of a chunk of iterations: the outcome of its last update
+// End of a chunk of iterations: the outcome of its last update
 // (of parity par) for the host; the next product sweep would find the same.
 __global__ void __launch_bounds__(kFinBlock) k_fin_chunk(Ctl* ctl, const double* __restrict__ pu, int np, int par) {
   if (ctl->done) return;
@@ -1166,33 +1117,6 @@ __global__ void __launch_bounds__(kFinBlock) k_fin_chunk(Ctl* ctl, const double*
   const int st = rr <= ctl->thresh ? 1 : !(rr == rr) ? -1 : it >= ctl->maxiter ? 2 : 0;
   if (st) {
     ctl->state = st;
-    ctl->done = 1;
-  }
-}
-
-// beta: standard <r,z>/<r_old,z_old>; flexible (Polak-Ribiere)
-// <z, r - r_old>/<z_old, r_old> = -<z, q>/<p, q>.
-template <int NV>
-__global__ void __launch_bounds__(kFinBlock) k_fin_beta(Ctl* ctl, const double* __restrict__ partials, int np,
-                                                        int first) {
-  if (ctl->done) return;
-  double t[NV];
-  fold_partials<NV>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double rzn = t[0];
-  const double zq = NV > 1 ? t[NV - 1] : 0.0;
-  if (first) {
-    ctl->beta = 0.0;
-  } else if (ctl->flexible) {
-    ctl->beta = -zq / ctl->pq;
-  } else {
-    ctl->beta = rzn / ctl->rz;
-  }
-  ctl->rz = rzn;
-  ctl->rzn = rzn;
-  ctl->zq = zq;
-  if (!(rzn > 0.0)) {
-    ctl->state = -1;
     ctl->done = 1;
   }
 }
@@ -1236,79 +1160,19 @@ __global__ void __launch_bounds__(kFinBlock) k_bfin_init(Ctl* ctl, const double*
   }
 }
 
-// alpha = rho / <r^, v>
-__global__ void __launch_bounds__(kFinBlock) k_bfin_alpha(Ctl* ctl, const double* __restrict__ partials, int np) {
+// End of a chunk of BiCGSTAB iterations: the outcome of its last full step for
+// the host; the next direction update would find the same.
+__global__ void __launch_bounds__(kFinBlock) k_bfin_chunk(Ctl* ctl, const double* __restrict__ pf, int np) {
   if (ctl->done) return;
   double t[1];
-  fold_partials<1>(partials, np, t);
+  fold_partials<1>(pf, np, t);
   if (threadIdx.x != 0) return;
-  const double rv = t[0];
-  if (!(rv != 0.0) || !(rv == rv)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  } else {
-    ctl->alpha = ctl->rho / rv;
-  }
-}
-
-// ||s||^2: the iteration is counted here; a small s ends the solve with
-// x = x + alpha y (already written).
-__global__ void __launch_bounds__(kFinBlock) k_bfin_half(Ctl* ctl, const double* __restrict__ partials, int np) {
-  if (ctl->done) return;
-  double t[1];
-  fold_partials<1>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double ss = t[0];
-  ctl->rr = ss;
-  ctl->iters += 1;
-  if (ss <= ctl->thresh) {
-    ctl->state = 1;
-    ctl->done = 1;
-  } else if (!(ss == ss)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  }
-}
-
-// omega = <t, s> / <t, t>
-__global__ void __launch_bounds__(kFinBlock) k_bfin_omega(Ctl* ctl, const double* __restrict__ partials, int np) {
-  if (ctl->done) return;
-  double t[2];
-  fold_partials<2>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double ts = t[0], tt = t[1];
-  const double om = ts / tt;
-  if (!(tt > 0.0) || !(om != 0.0) || !(om == om)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  } else {
-    ctl->omega = om;
-  }
-}
-
-// ||r||^2 and the next rho = <r^, r>, beta = (rho / rho_old) (alpha / omega).
-__global__ void __launch_bounds__(kFinBlock) k_bfin_full(Ctl* ctl, const double* __restrict__ partials, int np) {
-  if (ctl->done) return;
-  double t[2];
-  fold_partials<2>(partials, np, t);
-  if (threadIdx.x != 0) return;
-  const double rr = t[0], rho = t[1];
+  const double rr = t[0];
   ctl->rr = rr;
-  if (rr <= ctl->thresh) {
-    ctl->state = 1;
+  const int st = rr <= ctl->thresh ? 1 : !(rr == rr) ? -1 : ctl->iters >= ctl->maxiter ? 2 : 0;
+  if (st) {
+    ctl->state = st;
     ctl->done = 1;
-  } else if (!(rr == rr)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  } else if (ctl->iters >= ctl->maxiter) {
-    ctl->state = 2;
-    ctl->done = 1;
-  } else if (!(rho != 0.0) || !(rho == rho)) {
-    ctl->state = -1;
-    ctl->done = 1;
-  } else {
-    ctl->beta = (rho / ctl->rho) * (ctl->alpha / ctl->omega);
-    ctl->rho = rho;
   }
 }
 
@@ -1326,11 +1190,6 @@ __global__ void k_ctl_restart(Ctl* ctl) {
   ctl->it2[0] = ctl->it2[1] = ctl->iters;
 }
 
-void launch_fin_beta(Ctl* ctl, double* partials, int np, int first, int nv, hipStream_t s) {
-  if (nv == 2) hipLaunchKernelGGL(k_fin_beta<2>, dim3(1), dim3(kFinBlock), 0, s, ctl, partials, np, first);
-  else hipLaunchKernelGGL(k_fin_beta<1>, dim3(1), dim3(kFinBlock), 0, s, ctl, partials, np, first);
-}
-
 // ------------------------------------------------------------ V-cycle
 
 // Copies the done flag (0 when there is none) into the instrument record.
@@ -1345,9 +1204,7 @@ struct CycleArgs {
   Ctl* ctl;           // null: no early exit, no reductions
   double* partials;
   int red;            // 0 none, 1 <r,z>, 2 <r,z> and <z,q>
-  int first;
   int x0_ready;       // what the cycle starts from (X0Mode) already written
-  int fold = 0;       // the partials' consumer folds them: no finalize launch
 };
 
 template <class T>
@@ -1399,8 +1256,7 @@ void launch_prolong(Hierarchy& H, Level& L, const T* xc, T* x, const Ctl* ctl, h
 }
 
 // One V-cycle on level-0 rhs a.r0 -> a.z0 (FP64 at the boundary, T inside).
-// With a.red, the level-0 post-smoother emits the <r,z> (and <z,q>) partials
-// and the finalize kernel forms beta.  Extra smoothing sweeps (nu > 1)
+// With a.red, the level-0 post-smoother emits the <r,z> (and <z,q>) partials.  Extra smoothing sweeps (nu > 1)
 // ping-pong through the level's spare buffers.
 // Returns the number of partials per reduced value.
 template <class T>
@@ -1414,8 +1270,9 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_copy_z, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, a.r0, a.z0, ctl);
     if (a.red) {
       const int g = vec_grid(n);
-      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, n, a.r0, a.z0, a.q ? a.q : a.z0, ctl, a.partials);
-      launch_fin_beta(ctl, a.partials, g, a.first, 2, s);
+      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, n, a.r0, a.z0, a.q ? a.q : a.z0, ctl,
+                         a.partials);
+      return g;
     }
     return 0;
   }
@@ -1427,8 +1284,9 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
     }
     if (a.red) {
       const int g = vec_grid(C.n);
-      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, C.n, a.r0, a.z0, a.q ? a.q : a.z0, ctl, a.partials);
-      launch_fin_beta(ctl, a.partials, g, a.first, 2, s);
+      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, C.n, a.r0, a.z0, a.q ? a.q : a.z0, ctl,
+                         a.partials);
+      return g;
     }
     return 0;
   }
@@ -1443,9 +1301,7 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
         hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(H.n)), dim3(kBlock), 0, s, H.n, (const T*)nullptr, a.r0, c, ctl);
       b0 = c;
     }
-    const int np = fused_cycle<T>(H, b0, a.r0, a.z0, a.q, a.red, ctl, a.partials, s);
-    if (a.red && !a.fold) launch_fin_beta(ctl, a.partials, np, a.first, a.red, s);
-    return np;
+    return fused_cycle<T>(H, b0, a.r0, a.z0, a.q, a.red, ctl, a.partials, s);
   }
   T* cx[AMG_MAX_LEVELS];
   T* cr[AMG_MAX_LEVELS];
@@ -1525,7 +1381,6 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
             sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 0>{vv, sw, a.r0, cur, a.z0, nullptr}, ctl,
                   nullptr, s);
         }
-        if (a.red && !a.fold) launch_fin_beta(ctl, a.partials, np, a.first, a.red, s);
         np0 = np;
       } else {
         T* dst = spare[k & 1];
@@ -1857,10 +1712,12 @@ void choose_shapes(Hierarchy& H, hipStream_t s) {
 int64_t partials_region(const Hierarchy& H) {
   int64_t np = std::max<int64_t>(vec_grid(H.n), H.lv[0].shA.grid);
   np = std::max<int64_t>(np, H.lv[0].up.grid);
-  return std::max<int64_t>(np, vec_grid(H.co.n));
+  return std::max<int64_t>(np, vec_grid(std::max(H.co.n, 1)));
 }
 
-int64_t solve_partials_count(const Hierarchy& H) { return partials_region(H) * 4 + 64; }
+// Product, update and V-cycle of CG (1, 1, 2 values); products, half and full
+// step of BiCGSTAB (1, 2, 1, 2).
+int64_t solve_partials_count(const Hierarchy& H) { return partials_region(H) * 6 + 64; }
 
 SolveWork solve_work(Hierarchy& H) {
   return SolveWork{H.r.p, H.z.p, H.p.p, H.z2.p, H.q.p, H.partials.p, H.ctl.p, H.h_ctl, true};
@@ -1997,7 +1854,7 @@ void read_instrument(Hierarchy& H, int* launches, double* total_ms, double* min_
 }
 
 void apply_vcycle(Hierarchy& H, const double* d_r, double* d_z, hipStream_t s) {
-  CycleArgs a{d_r, d_z, nullptr, nullptr, nullptr, 0, 0, 0};
+  CycleArgs a{d_r, d_z, nullptr, nullptr, nullptr, 0, 0};
   vcycle(H, a, s);
   AMG_HIP(hipGetLastError());
 }
@@ -2010,20 +1867,22 @@ void pattern_grad(Hierarchy& H, const double* d_lam, const double* d_x, double* 
 }
 
 template <class T>
-void launch_cg_update(Hierarchy& H, const SolveWork& w, int n, const double* p, hipStream_t s) {
+void launch_cg_update(Hierarchy& H, const SolveWork& w, int n, const double* p, const double* pa, int npa, int tot,
+                      double* pu, int par, hipStream_t s) {
   Level& L0 = H.lv[0];
+  const dim3 g(vec_grid(n)), b(kBlock);
   switch (x0_mode(H)) {
     case X0_SMOOTHED:
-      hipLaunchKernelGGL((k_cg_update<X0_SMOOTHED, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
-                         Bufs<T>::sw(L0), Bufs<T>::x(L0), w.ctl, w.partials);
+      hipLaunchKernelGGL((k_cg_update<X0_SMOOTHED, T>), g, b, 0, s, n, w.r, p, w.q, Bufs<T>::sw(L0),
+                         Bufs<T>::x(L0), w.ctl, pa, npa, tot, pu, par);
       break;
     case X0_COPY:
-      hipLaunchKernelGGL((k_cg_update<X0_COPY, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
-                         (const T*)nullptr, Bufs<T>::x(L0), w.ctl, w.partials);
+      hipLaunchKernelGGL((k_cg_update<X0_COPY, T>), g, b, 0, s, n, w.r, p, w.q, (const T*)nullptr,
+                         Bufs<T>::x(L0), w.ctl, pa, npa, tot, pu, par);
       break;
     default:
-      hipLaunchKernelGGL((k_cg_update<X0_NONE, T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n, w.r, p, w.q,
-                         (const T*)nullptr, (T*)nullptr, w.ctl, w.partials);
+      hipLaunchKernelGGL((k_cg_update<X0_NONE, T>), g, b, 0, s, n, w.r, p, w.q, (const T*)nullptr, (T*)nullptr,
+                         w.ctl, pa, npa, tot, pu, par);
   }
 }
 
@@ -2076,6 +1935,36 @@ void graph_stream(Hierarchy& H) {
   }
 }
 
+// A reduction as its consumer reads it: nv arrays of np partials from p on.
+struct Sums {
+  double* p;
+  int np, nv;
+};
+
+// Where the consumers find the sums of a solve: the partials (folded solves),
+// or their totals at `out`, in the order given (at most four).
+void totals_at(bool tot, std::initializer_list<Sums*> sums, double* out) {
+  if (!tot) return;
+  for (Sums* s : sums) {
+    *s = Sums{out, 1, s->nv};
+    out += s->nv;
+  }
+}
+
+// Launches k_sum for the sums where the solve takes totals, then totals_at.
+void total(bool tot, std::initializer_list<Sums*> sums, double* out, const Ctl* ctl, hipStream_t st) {
+  if (!tot) return;
+  SumArgs a{};
+  int m = 0;
+  for (Sums* s : sums)
+    for (int v = 0; v < s->nv; ++v, ++m) {
+      a.src[m] = s->p + (int64_t)v * s->np;
+      a.np[m] = s->np;
+    }
+  hipLaunchKernelGGL(k_sum, dim3(m), dim3(kFinBlock), 0, st, a, out, ctl);
+  totals_at(tot, sums, out);
+}
+
 amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const double* d_b, double* d_x,
                      double tol, amg_info* info, hipStream_t caller) {
   // hierarchies that fit one compute unit: the whole solve in one launch
@@ -2104,24 +1993,23 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   Ctl* ctl = w.ctl;
   double* part = w.partials;
   const int gv = vec_grid(n);
-  // folded form: no finalize launches, the consuming kernels sum the partials
-  // (each reduction in a region of its own: product, update, V-cycle)
+  const int gu = vec_grid(n);
+  // the partials of the product (part), the update (pu) and the V-cycle (pz)
+  // are summed by the kernels that need them (fold_load)
   const int64_t region = partials_region(H);
+  double* pu = part + region;
+  double* pz = part + 2 * region;
+  const bool tot = region > kFoldMax;
+  double* pt = part + 6 * region;   // totals: product; update and V-cycle
+  Sums start{pz, 0, 1};             // <r, z> as the first product after a (re)start reads it
+  int npz = 0;
   // plain CG with the standard beta: z = r needs no copy and <r, z> = ||r||^2
   // no sum of its own (10^7 unknowns: the copy and the dots were 63 of 320 us
   // per iteration, the unused x0 = sw o r another 34)
   const bool plain = !H.prm.precondition && !flexible;
-  const bool fold = (plain || (multi && H.lf == 0)) && region <= kFoldMax;
-  double* pu = fold ? part + region : part;
-  double* pz = fold ? part + 2 * region : part;
-  int npz = 0;
   double* zv = plain ? w.r : w.z;
-  // partials of ||b||^2 and of the true residual: plain folded solves start
-  // from them (pz), so they stay out of the product sweep's region
-  double* p0 = plain && fold ? pz : part;
-  hipLaunchKernelGGL(k_cg_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, w.r, d_x, p0);
-  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, p0, gv, tol, o.maxiter, flexible,
-                     d_x);
+  hipLaunchKernelGGL(k_cg_init, dim3(gu), dim3(kBlock), 0, s, n, d_b, w.r, d_x, pz);
+  hipLaunchKernelGGL(k_fin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, pz, gu, tol, o.maxiter, flexible, d_x);
   AMG_HIP(hipGetLastError());
   // search directions alternate between two buffers (the fused direction
   // update writes the new p while neighbours still gather the old one)
@@ -2129,45 +2017,38 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   int cur = 0;
   // one PCG iteration: p = z + beta p and q = A p; alpha; x, r update; z = M^-1 r, beta
   auto iteration = [&](int first, int c, hipStream_t st) {
-    int np;
-    if (fold) {
-      const int nz = !first && flexible ? 2 : 1;
-      {
-        InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
-        np = sweep(L0.shA, n, L0.arp(), L0.aci(),
-                   OpSpmvFold{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, plain && !first ? pu : pz, pu,
-                              plain && !first ? gv : npz, gv, nz, first, c}, ctl, part, st);
-      }
-      {
-        InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
-        if (x0_mode(H) == X0_COPY)
-          hipLaunchKernelGGL((k_cg_update_fold<X0_COPY, float>), dim3(gv), dim3(kBlock), 0, st, n, w.r, pb[c ^ 1], w.q,
-                             Bufs<float>::x(L0), ctl, part, np, pu, c);
-        else
-          hipLaunchKernelGGL((k_cg_update_fold<X0_NONE, double>), dim3(gv), dim3(kBlock), 0, st, n, w.r, pb[c ^ 1],
-                             w.q, (double*)nullptr, ctl, part, np, pu, c);
-      }
-      if (!plain) vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, flexible ? 2 : 1, 0, 1, 1}, st);
-      return;
+    const int nv = flexible ? 2 : 1;
+    // what the product reads: the last update's and V-cycle's sums
+    Sums u{pu, gu, 1}, z{pz, npz, nv};
+    if (plain) {
+      totals_at(tot, {&u}, pt + 1);
+      z = u;
+    } else {
+      totals_at(tot, {&u, &z}, pt + 1);
     }
+    if (first) z = start;
+    int np;
     {
       InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
-      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvXpayDev{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, first},
-                 ctl, part, st);
+      np = sweep(L0.shA, n, L0.arp(), L0.aci(),
+                 OpSpmvXpay{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, z.p, u.p, z.np, u.np, z.nv, tot, first, c}, ctl, part,
+                 st);
     }
-    hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(kFinBlock), 0, st, ctl, part, np);
+    Sums a{part, np, 1};
+    total(tot, {&a}, pt, ctl, st);
     {
       InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
-      if (H.fp32()) launch_cg_update<float>(H, w, n, pb[c ^ 1], st);
-      else launch_cg_update<double>(H, w, n, pb[c ^ 1], st);
+      if (H.fp32()) launch_cg_update<float>(H, w, n, pb[c ^ 1], a.p, a.np, tot, pu, c, st);
+      else launch_cg_update<double>(H, w, n, pb[c ^ 1], a.p, a.np, tot, pu, c, st);
     }
+    u = Sums{pu, gu, 1};
     if (plain) {
-      hipLaunchKernelGGL(k_fin_update_plain, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
-      return;
+      total(tot, {&u}, pt + 1, ctl, st);
+    } else {
+      vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, nv, multi ? 1 : 0}, st);
+      z = Sums{pz, npz, nv};
+      total(tot, {&u, &z}, pt + 1, ctl, st);
     }
-    hipLaunchKernelGGL(k_fin_update, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
-    CycleArgs a{w.r, w.z, w.q, ctl, part, flexible ? 2 : 1, 0, multi ? 1 : 0};
-    vcycle(H, a, st);
   };
   // two iterations captured once per direction-buffer parity and replayed
   auto pair = [&](int c) {
@@ -2186,14 +2067,11 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       if (H.fp32()) launch_sw_mul<float>(H, w, n, s);
       else launch_sw_mul<double>(H, w, n, s);
     }
-    if (!plain) {
-      CycleArgs a0{w.r, w.z, w.q, ctl, pz, 1, 1, multi ? 1 : 0, fold ? 1 : 0};
-      npz = vcycle(H, a0, s);
-    } else if (fold) {
-      npz = restarts ? L0.shA.grid : gv;
-    } else {
-      hipLaunchKernelGGL(k_plain_start, dim3(1), dim3(1), 0, s, ctl, restarts ? 1 : 0);
-    }
+    // (plain CG starts from the partials of ||r||^2 that the start or the true
+    // residual left in pz)
+    npz = plain ? (restarts ? L0.shA.grid : gu) : vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, 1, multi ? 1 : 0}, s);
+    start = Sums{pz, npz, 1};
+    total(tot, {&start}, pt + 1, ctl, s);
     int first = 1;
     // Iterations are queued in chunks; between chunks the host reads the
     // control block and sizes the next chunk from the observed decay of
@@ -2216,7 +2094,7 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
         iteration(0, cur, s);
         cur ^= 1;
       }
-      if (fold) hipLaunchKernelGGL(k_fin_chunk, dim3(1), dim3(kFinBlock), 0, s, ctl, pu, gv, cur ^ 1);
+      hipLaunchKernelGGL(k_fin_chunk, dim3(1), dim3(kFinBlock), 0, s, ctl, pu, gu, cur ^ 1);
       AMG_HIP(hipGetLastError());
       read_ctl(w, s);
       if (w.h_ctl->done) break;
@@ -2246,8 +2124,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       break;
     }
     // true residual r = b - A x
-    const int np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpTrueResid{L0.av(), d_x, d_b, w.r}, nullptr, p0, s);
-    hipLaunchKernelGGL(k_fin_trr, dim3(1), dim3(kFinBlock), 0, s, ctl, p0, np);
+    const int np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpTrueResid{L0.av(), d_x, d_b, w.r}, nullptr, pz, s);
+    hipLaunchKernelGGL(k_fin_trr, dim3(1), dim3(kFinBlock), 0, s, ctl, pz, np);
     read_ctl(w, s);
     const Ctl& c = *w.h_ctl;
     if (c.trr <= c.thresh) {
@@ -2328,7 +2206,15 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
     y = p;
     z = sv;
   }
-  const int gv = vec_grid(n);
+  const int gv = vec_grid(n), gu = vec_grid(n);
+  const int64_t region = partials_region(H);
+  double* ps = part + region;       // <s, s>
+  double* pt = part + 2 * region;   // <s, t>, <t, t>
+  double* pf = part + 4 * region;   // <r, r>, <r^, r>
+  const bool tot = region > kFoldMax;
+  double* ptot = part + 6 * region;  // totals
+  Sums full{pf, gu, 2};             // as the direction update reads them
+  totals_at(tot, {&full}, ptot + 4);
   hipLaunchKernelGGL(k_bi_init, dim3(gv), dim3(kBlock), 0, s, n, d_b, r, rh, d_x, part);
   hipLaunchKernelGGL(k_bfin_init, dim3(1), dim3(kFinBlock), 0, s, ctl, part, gv, tol, o.maxiter, d_x);
   AMG_HIP(hipGetLastError());
@@ -2339,43 +2225,45 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
   auto launch_dir = [&](int first, hipStream_t st) {
     Level& L0c = H.lv[0];
     if (H.fp32())
-      hipLaunchKernelGGL(k_bi_dir<float>, dim3(gv), dim3(kBlock), 0, st, n, r, v, p,
+      hipLaunchKernelGGL(k_bi_dir<float>, dim3(gu), dim3(kBlock), 0, st, n, r, v, p,
                          smoothed ? Bufs<float>::sw(L0c) : nullptr,
-                         x0w ? Bufs<float>::x(L0c) : nullptr, ctl, first);
+                         x0w ? Bufs<float>::x(L0c) : nullptr, ctl, first, full.p, full.np, tot);
     else
-      hipLaunchKernelGGL(k_bi_dir<double>, dim3(gv), dim3(kBlock), 0, st, n, r, v, p,
+      hipLaunchKernelGGL(k_bi_dir<double>, dim3(gu), dim3(kBlock), 0, st, n, r, v, p,
                          smoothed ? Bufs<double>::sw(L0c) : nullptr,
-                         x0w ? Bufs<double>::x(L0c) : nullptr, ctl, first);
+                         x0w ? Bufs<double>::x(L0c) : nullptr, ctl, first, full.p, full.np, tot);
   };
-  auto launch_half = [&](hipStream_t st) {
+  auto launch_half = [&](const Sums& a, hipStream_t st) {
     Level& L0c = H.lv[0];
     if (H.fp32())
-      hipLaunchKernelGGL(k_bi_half<float>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv,
+      hipLaunchKernelGGL(k_bi_half<float>, dim3(gu), dim3(kBlock), 0, st, n, y, r, v, sv,
                          smoothed ? Bufs<float>::sw(L0c) : nullptr,
-                         x0w ? Bufs<float>::x(L0c) : nullptr, ctl, part);
+                         x0w ? Bufs<float>::x(L0c) : nullptr, ctl, a.p, a.np, tot, ps);
     else
-      hipLaunchKernelGGL(k_bi_half<double>, dim3(gv), dim3(kBlock), 0, st, n, y, r, v, sv,
-                         smoothed ? Bufs<double>::sw(L0c) : nullptr, x0w ? Bufs<double>::x(L0c) : nullptr, ctl, part);
+      hipLaunchKernelGGL(k_bi_half<double>, dim3(gu), dim3(kBlock), 0, st, n, y, r, v, sv,
+                         smoothed ? Bufs<double>::sw(L0c) : nullptr, x0w ? Bufs<double>::x(L0c) : nullptr, ctl, a.p,
+                         a.np, tot, ps);
   };
   auto iteration = [&](int first, hipStream_t st) {
     launch_dir(first, st);
-    if (prec) vcycle(H, CycleArgs{p, y, nullptr, ctl, part, 0, 0, x0w ? 1 : 0}, st);
+    if (prec) vcycle(H, CycleArgs{p, y, nullptr, ctl, part, 0, x0w ? 1 : 0}, st);
     int np;
     {
       InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
       np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<1>{L0.av(), y, v, rh}, ctl, part, st);
     }
-    hipLaunchKernelGGL(k_bfin_alpha, dim3(1), dim3(kFinBlock), 0, st, ctl, part, np);
-    launch_half(st);
-    hipLaunchKernelGGL(k_bfin_half, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
-    if (prec) vcycle(H, CycleArgs{sv, z, nullptr, ctl, part, 0, 0, x0w ? 1 : 0}, st);
+    Sums a{part, np, 1};
+    total(tot, {&a}, ptot, ctl, st);
+    launch_half(a, st);
+    if (prec) vcycle(H, CycleArgs{sv, z, nullptr, ctl, part, 0, x0w ? 1 : 0}, st);
     {
       InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
-      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<2>{L0.av(), z, t, sv}, ctl, part, st);
+      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<2>{L0.av(), z, t, sv}, ctl, pt, st);
     }
-    hipLaunchKernelGGL(k_bfin_omega, dim3(1), dim3(kFinBlock), 0, st, ctl, part, np);
-    hipLaunchKernelGGL(k_bi_full, dim3(gv), dim3(kBlock), 0, st, n, z, sv, t, rh, r, ctl, part);
-    hipLaunchKernelGGL(k_bfin_full, dim3(1), dim3(kFinBlock), 0, st, ctl, part, gv);
+    Sums h{ps, gu, 1}, tt{pt, np, 2}, f{pf, gu, 2};
+    total(tot, {&h, &tt}, ptot + 1, ctl, st);
+    hipLaunchKernelGGL(k_bi_full, dim3(gu), dim3(kBlock), 0, st, n, z, sv, t, rh, r, ctl, h.p, h.np, tt.p, tt.np, tot, pf);
+    total(tot, {&f}, ptot + 4, ctl, st);
   };
   int restarts = 0;
   amg_status st = AMG_OK;
@@ -2396,6 +2284,7 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
         for (; left > 0; --left) AMG_HIP(hipGraphLaunch(H.gr.bexec, s));
       }
       for (; left > 0; --left) iteration(0, s);
+      hipLaunchKernelGGL(k_bfin_chunk, dim3(1), dim3(kFinBlock), 0, s, ctl, pf, gu);
       AMG_HIP(hipGetLastError());
       read_ctl(H, s);
       if (H.h_ctl->done) break;
