@@ -65,8 +65,17 @@ __device__ inline void mfma_tile_update(double* __restrict__ W, int m, int I, in
 // In-place Cholesky W = L L^T (lower triangle), one workgroup.  Panel of 16
 // columns: column-by-column right-looking factorization restricted to the
 // panel, then a rank-16 update of the trailing lower triangle on MFMA.
-__global__ void __launch_bounds__(kCoBlock) k_cholesky(int m, double* __restrict__ W, int* flags) {
-  W += (int64_t)blockIdx.y * m * m;
+// LDS: the matrix (m <= kLdsCholesky, 128 KB) is factored in LDS, where each of
+// the three dependent steps per column costs an LDS instead of an L2 round trip.
+constexpr int kLdsCholesky = 128;
+
+template <bool LDS>
+__global__ void __launch_bounds__(kCoBlock) k_cholesky(int m, double* __restrict__ Wg, int* flags) {
+  Wg += (int64_t)blockIdx.y * m * m;
+  __shared__ double s_w[LDS ? kLdsCholesky * kLdsCholesky : 1];
+  double* W = LDS ? s_w : Wg;
+  if constexpr (LDS)
+    for (int e = threadIdx.x; e < m * m; e += kCoBlock) s_w[e] = Wg[e];
   const int tid = threadIdx.x;
   const int wave = tid >> 6, nwaves = kCoBlock / 64;
   __shared__ int s_bad;
@@ -112,7 +121,8 @@ __global__ void __launch_bounds__(kCoBlock) k_cholesky(int m, double* __restrict
   // zero the strict upper triangle
   for (int64_t e = tid; e < (int64_t)m * m; e += kCoBlock) {
     int i = (int)(e / m), j = (int)(e % m);
-    if (j > i) W[e] = 0.0;
+    if constexpr (LDS) Wg[e] = j > i ? 0.0 : W[e];
+    else if (j > i) W[e] = 0.0;
   }
   if (tid == 0 && s_bad) atomicOr(flags, 1);
 }
@@ -331,7 +341,10 @@ void coarse_setup(Hierarchy& H, hipStream_t s) {
     hipLaunchKernelGGL(k_lu_inverse_t, dim3((m + kTriWaves - 1) / kTriWaves), dim3(64 * kTriWaves), 0, s, m, C.L.p,
                        C.piv.p, C.inv.p);
   } else {
-    hipLaunchKernelGGL(k_cholesky, dim3(1, S), dim3(kCoBlock), 0, s, m, C.L.p, H.flags.p);
+    if (m <= kLdsCholesky)
+      hipLaunchKernelGGL(k_cholesky<true>, dim3(1, S), dim3(kCoBlock), 0, s, m, C.L.p, H.flags.p);
+    else
+      hipLaunchKernelGGL(k_cholesky<false>, dim3(1, S), dim3(kCoBlock), 0, s, m, C.L.p, H.flags.p);
     hipLaunchKernelGGL(k_tri_inverse, dim3((m + kTriWaves - 1) / kTriWaves, S), dim3(64 * kTriWaves), 0, s, m, C.L.p,
                        C.inv.p);
     hipLaunchKernelGGL(k_transpose, dim3((int)((mm + kBlock - 1) / kBlock), S), dim3(kBlock), 0, s, m, C.inv.p,

@@ -205,9 +205,14 @@ __global__ void k_rows_of(int n, const int* __restrict__ rp, int* __restrict__ r
   for (int k = rp[i]; k < rp[i + 1]; ++k) rowid[k] = i;
 }
 
-__global__ void k_count_cols(int64_t m, const int* __restrict__ ci, int* __restrict__ cnt) {
+// Row pointers of m sorted keys in [0, nc) (m >= 1).
+__global__ void k_rows_of_keys(int64_t m, int nc, const int* __restrict__ keys, int* __restrict__ rp) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < m) atomicAdd(cnt + ci[t], 1);
+  if (t >= m) return;
+  const int k = keys[t], prev = t > 0 ? keys[t - 1] : -1;
+  for (int j = prev + 1; j <= k; ++j) rp[j] = (int)t;
+  if (t == m - 1)
+    for (int j = k + 1; j <= nc; ++j) rp[j] = (int)m;
 }
 
 __global__ void k_gather_i32(int64_t m, const int* __restrict__ perm, const int* __restrict__ a,
@@ -513,14 +518,13 @@ bool build_level(Hierarchy& H, int l, hipStream_t s) {
     // transpose of the pattern of A P: a stable sort of its entries by column
     const int64_t m = L.apnnz;
     Arena::Scope scope;
-    TBuf<int> rowid, iota, keys, cnt;
+    TBuf<int> rowid, iota, keys;
     rowid.alloc(m);
     iota.alloc(m);
     keys.alloc(m);
     L.dperm.alloc(m);
     L.dci.alloc(m);
     L.drp.alloc(nc + 1);
-    cnt.alloc(nc + 1);
     hipLaunchKernelGGL(k_rows_of, dim3(blocks(L.n)), dim3(kBlock), 0, s, L.n, L.aprp.p, rowid.p);
     hipLaunchKernelGGL(k_pos_iota, dim3(blocks(m)), dim3(kBlock), 0, s, m, iota.p);
     int bits = 1;
@@ -528,9 +532,7 @@ bool build_level(Hierarchy& H, int l, hipStream_t s) {
     cub_run([&](void* t, size_t& b) {
       return hipcub::DeviceRadixSort::SortPairs(t, b, L.apci.p, keys.p, iota.p, L.dperm.p, (int)m, 0, bits, s);
     }, s);
-    hipLaunchKernelGGL(k_fill_int, dim3(blocks(nc + 1)), dim3(kBlock), 0, s, (int64_t)nc + 1, 0, cnt.p);
-    hipLaunchKernelGGL(k_count_cols, dim3(blocks(m)), dim3(kBlock), 0, s, m, L.apci.p, cnt.p);
-    cub_run([&](void* t, size_t& b) { return hipcub::DeviceScan::ExclusiveSum(t, b, cnt.p, L.drp.p, nc + 1, s); }, s);
+    hipLaunchKernelGGL(k_rows_of_keys, dim3(blocks(m)), dim3(kBlock), 0, s, m, nc, keys.p, L.drp.p);
     hipLaunchKernelGGL(k_gather_i32, dim3(blocks(m)), dim3(kBlock), 0, s, m, L.dperm.p, rowid.p, L.dci.p);
     if (!build_ell(L.dn, nc, m, L.drp.p, L.dci.p, nullptr, nullptr, s)) return false;
     // sources as entries of A P instead of entries of dn's rows

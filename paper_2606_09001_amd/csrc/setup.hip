@@ -72,8 +72,15 @@ __global__ void k_hash(int n, int64_t nnz, const int* __restrict__ rp, const int
     h ^= splitmix64(((uint64_t)k << 32) ^ (uint32_t)ci[k]);
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n; i += stride)
     h ^= splitmix64(0x5bd1e995ull ^ ((uint64_t)(i + 1) << 33) ^ (uint32_t)rp[i]);
+  // one atomic per workgroup (one per wave serialized 4096 of them: 50 us)
+  __shared__ unsigned long long s_h[kBlock / 64];
   for (int o = 32; o >= 1; o >>= 1) h ^= (uint64_t)__shfl_xor((unsigned long long)h, o, 64);
-  if ((threadIdx.x & 63) == 0 && h) atomicXor(out, (unsigned long long)h);
+  if ((threadIdx.x & 63) == 0) s_h[threadIdx.x >> 6] = h;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / 64; ++w) h ^= s_h[w];
+    atomicXor(out, (unsigned long long)h);
+  }
 }
 
 template <class T>
@@ -281,8 +288,8 @@ __global__ void k_mis_e1(int n, const int* __restrict__ grp, const int* __restri
   e1[i] = r;
 }
 
-// Undecided nodes within distance 2 of a root are excluded; the remaining
-// undecided nodes are counted.
+// Undecided nodes within distance 2 of a root are excluded; *undecided = 1 when
+// some remain.
 __global__ void k_mis_e2(int n, const int* __restrict__ grp, const int* __restrict__ gci,
                          const int8_t* __restrict__ e1, int8_t* __restrict__ state, int* __restrict__ undecided) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -292,8 +299,9 @@ __global__ void k_mis_e2(int n, const int* __restrict__ grp, const int* __restri
     for (int k = grp[i]; k < grp[i + 1] && !r; ++k) r = e1[gci[k]];
     if (r) state[i] = S_EXCL; else und = 1;
   }
+  // only whether any remain is used: plain stores of the same value
   const unsigned long long m = __ballot(und);
-  if ((threadIdx.x & 63) == 0 && m) atomicAdd(undecided, (int)__popcll(m));
+  if ((threadIdx.x & 63) == 0 && m) *undecided = 1;
 }
 
 __global__ void k_is_root(int n, const int8_t* __restrict__ state, int* __restrict__ isroot) {
@@ -340,79 +348,120 @@ __global__ void k_agg_phase3(int n, const int* __restrict__ grp, const int* __re
 
 // ------------------------------------------------------- prolongator
 
-// Number of distinct aggregates touched by row i.
-__global__ void k_p_count(int n, const int* __restrict__ rp, const int* __restrict__ ci, const int* __restrict__ agg,
-                          int* __restrict__ cnt) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > n) return;
-  if (i == n) { cnt[n] = 0; return; }
-  int prev = -1, c = 0;
-  for (;;) {
-    int nxt = INT_MAX;
-    for (int k = rp[i]; k < rp[i + 1]; ++k) {
-      int a = agg[ci[k]];
-      if (a > prev && a < nxt) nxt = a;
-    }
-    if (nxt == INT_MAX) break;
-    ++c;
-    prev = nxt;
-  }
-  cnt[i] = c;
-}
-
+// Prolongator pattern, values and fill map with G = 2^sh lanes per row (lane l:
+// entry l of the row and its aggregate).  An entry leads when no earlier one
+// of the row has its aggregate; the leaders' ranks by aggregate are the sorted
+// columns, and a leader walks the row in stored order for its sums.  Rows of
+// more than G entries repeat the search for the next larger aggregate instead,
+// in the group's first lane.
+//
 // P = (I - omegaP D^-1 A) T: for each touched aggregate J (ascending),
 // s_J = sum of a_ij over j in row i with agg(j) = J in stored order from
-// +0.0, w = omegaP / a_ii, P_iJ = [J == agg(i)] - w*s_J (unfused).
-__global__ void k_p_fill(int n, const int* __restrict__ rp, const int* __restrict__ ci, const double* __restrict__ v,
-                         int vs, const int* __restrict__ diagpos, const int* __restrict__ agg, double omegaP,
-                         const int* __restrict__ prp, int* __restrict__ pci, double* __restrict__ pv) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double w = omegaP / v[(int64_t)diagpos[i] * vs];
-  int ai = agg[i];
-  int pos = prp[i], prev = -1;
-  for (;;) {
-    int nxt = INT_MAX;
-    for (int k = rp[i]; k < rp[i + 1]; ++k) {
-      int a = agg[ci[k]];
-      if (a > prev && a < nxt) nxt = a;
+// +0.0, w = omegaP / a_ii, P_iJ = [J == agg(i)] - w*s_J (unfused).  The map
+// lists, per P entry, the A entries of its sum (pak[pao[e] ..)), and its row.
+// FILL = 0: distinct aggregates per row (cnt[n] = 0); 1: everything else.
+template <int FILL>
+__global__ void __launch_bounds__(kBlock) k_p_rows(int n, int sh, const int* __restrict__ rp,
+                                                   const int* __restrict__ ci, const int* __restrict__ agg,
+                                                   int* __restrict__ cnt, const double* __restrict__ v, int vs,
+                                                   const int* __restrict__ diagpos, double omegaP,
+                                                   const int* __restrict__ prp, int* __restrict__ pci,
+                                                   double* __restrict__ pv, int* __restrict__ pao,
+                                                   int* __restrict__ pak, int* __restrict__ prow) {
+  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int G = 1 << sh, l = (int)(q & (G - 1));
+  const int i = (int)(q >> sh);
+  if (i > n) return;  // (whole groups)
+  if (i == n) {
+    if (!FILL && l == 0) cnt[n] = 0;
+    if (FILL && l == 0) pao[prp[n]] = rp[n];
+    return;
+  }
+  const int k0 = rp[i], len = rp[i + 1] - k0;
+  const double w = FILL ? omegaP / v[(int64_t)diagpos[i] * vs] : 0.0;
+  const int ai = FILL ? agg[i] : 0, pos0 = FILL ? prp[i] : 0;
+  if (len > G) {
+    if (l != 0) return;
+    int prev = -1, c = 0, t = k0;
+    for (;;) {
+      int nxt = INT_MAX;
+      for (int k = k0; k < k0 + len; ++k) {
+        const int a = agg[ci[k]];
+        if (a > prev && a < nxt) nxt = a;
+      }
+      if (nxt == INT_MAX) break;
+      if (FILL) {
+        const int e = pos0 + c;
+        double sJ = 0.0;
+        pao[e] = t;
+        prow[e] = i;
+        pci[e] = nxt;
+        for (int k = k0; k < k0 + len; ++k)
+          if (agg[ci[k]] == nxt) {
+            sJ += v[(int64_t)k * vs];
+            pak[t++] = k;
+          }
+        const double ws = w * sJ;
+        pv[(int64_t)e * vs] = ((nxt == ai) ? 1.0 : 0.0) - ws;
+      }
+      ++c;
+      prev = nxt;
     }
-    if (nxt == INT_MAX) break;
-    double sJ = 0.0;
-    for (int k = rp[i]; k < rp[i + 1]; ++k)
-      if (agg[ci[k]] == nxt) sJ += v[(int64_t)k * vs];
-    double delta = (nxt == ai) ? 1.0 : 0.0;
-    double ws = w * sJ;
-    if (pci) pci[pos] = nxt;
-    pv[(int64_t)pos * vs] = delta - ws;
-    ++pos;
-    prev = nxt;
+    if (!FILL) cnt[i] = c;
+    // entries whose column has no aggregate belong to no P entry
+    if (FILL)
+      for (; t < k0 + len; ++t) pak[t] = -1;
+    return;
   }
-}
-
-// Map of the prolongator fill (thread per row): for each P entry of row i,
-// the A entries of row i whose column lies in that entry's aggregate, in
-// stored order, and the entry's row.
-__global__ void k_pmap_build(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                             const int* __restrict__ agg, const int* __restrict__ prp, const int* __restrict__ pci,
-                             int* __restrict__ pao, int* __restrict__ pak, int* __restrict__ prow) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int t = rp[i];
-  for (int e = prp[i]; e < prp[i + 1]; ++e) {
-    pao[e] = t;
+  const int a = l < len ? agg[ci[k0 + l]] : -1;
+  const double x = FILL && l < len ? v[(int64_t)(k0 + l) * vs] : 0.0;
+  // leader: the first entry of its aggregate; rank among leaders and entries of
+  // smaller aggregates (their number places the leader's part of the map)
+  bool lead = a >= 0;
+  int before = 0;
+  double sJ = 0.0;
+  for (int t = 0; t < len; ++t) {
+    const int b = __shfl(a, t, G);
+    const double y = FILL ? __shfl(x, t, G) : 0.0;
+    if (b == a) {
+      if (t < l) lead = false;
+      sJ += y;
+    }
+    if (b >= 0 && b < a) ++before;
+  }
+  int rank = 0, total = 0;
+  for (int t = 0; t < len; ++t) {
+    const int b = __shfl(lead ? a : -1, t, G);
+    if (b >= 0) {
+      ++total;
+      if (b < a) ++rank;
+    }
+  }
+  if (!FILL) {
+    if (l == 0) cnt[i] = total;
+    return;
+  }
+  int own = 0, same = 0, none = 0, with = 0;  // position of the lane's entry in the map
+  for (int t = 0; t < len; ++t) {
+    const int b = __shfl(a, t, G);
+    if (b == a && t < l) ++same;
+    if (b < 0 && t < l) ++none;
+    if (b >= 0) ++with;
+  }
+  own = a >= 0 ? k0 + before + same : k0 + with + none;
+  if (l < len) pak[own] = a >= 0 ? k0 + l : -1;
+  if (lead) {
+    const int e = pos0 + rank;
+    const double ws = w * sJ;
+    pao[e] = k0 + before;
     prow[e] = i;
-    const int J = pci[e];
-    for (int k = rp[i]; k < rp[i + 1]; ++k)
-      if (agg[ci[k]] == J) pak[t++] = k;
+    pci[e] = a;
+    pv[(int64_t)e * vs] = ((a == ai) ? 1.0 : 0.0) - ws;
   }
-  // entries whose column has no aggregate belong to no P entry
-  for (; t < rp[i + 1]; ++t) pak[t] = -1;
-  if (i == n - 1) pao[prp[n]] = rp[n];
 }
 
 // Prolongator values through the map (entry by system): the same expression
-// and fold as k_p_fill, omega_P = (4/3) / rho.
+// and fold as k_p_rows, omega_P = (4/3) / rho.
 __global__ void k_p_refill(int64_t pnnz, int S, int sh, const int* __restrict__ pao, const int* __restrict__ pak,
                            const int* __restrict__ prow, const int* __restrict__ pci, const double* __restrict__ v,
                            const int* __restrict__ diagpos, const int* __restrict__ agg,
@@ -442,9 +491,15 @@ __global__ void k_iota(int64_t m, int* __restrict__ a) {
   if (t < m) a[t] = (int)t;
 }
 
-__global__ void k_col_count(int64_t m, const int* __restrict__ ci, int* __restrict__ cnt) {
-  int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < m) atomicAdd(cnt + ci[t], 1);
+// Row pointers of m sorted keys in [0, nc): the first position of every key
+// and of the absent keys before it (m >= 1).
+__global__ void k_key_rows(int64_t m, int nc, const int* __restrict__ keys, int* __restrict__ rp) {
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (t >= m) return;
+  const int k = keys[t], prev = t > 0 ? keys[t - 1] : -1;
+  for (int j = prev + 1; j <= k; ++j) rp[j] = (int)t;
+  if (t == m - 1)
+    for (int j = k + 1; j <= nc; ++j) rp[j] = (int)m;
 }
 
 // R = P^T: entry t of R is entry perm[t] of P (stable sort by column keeps
@@ -700,45 +755,44 @@ __global__ void k_spgemm_fill_entries(int nrows, int64_t cnnz, const int* __rest
   cv[e * vs] = acc;
 }
 
-// Product map of C = X Y on C's fixed pattern: number of terms per entry.
-__global__ void k_pm_count(int nrows, int64_t cnnz, const int* __restrict__ crp, const int* __restrict__ cci,
-                           const int* __restrict__ xrp, const int* __restrict__ xci, const int* __restrict__ yrp,
-                           const int* __restrict__ yci, int64_t* __restrict__ cnt) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e > cnnz) return;
-  if (e == cnnz) {
-    cnt[cnnz] = 0;
-    return;
-  }
-  int lo = 0, hi = nrows;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if ((int64_t)crp[mid] <= e) lo = mid; else hi = mid;
-  }
-  const int J = cci[e];
+// Product map of C = X Y on C's fixed pattern (entry e in row crow[e]), with
+// 2^sh lanes per entry: each lane tests every 2^sh-th inner index.  FILL = 0:
+// number of terms per entry (cnt[cnnz] = 0).  FILL = 1: the (x position, y
+// position) pairs in ascending inner index (the order of the fold that forms
+// the entry), placed by the rank of the lane among the step's hits.  (One
+// thread per entry walks rows of up to 330 inner indices alone: 0.6 ms for a
+// coarsest level of 15 rows, 4.4 ms in all for a 100^3 setup.)
+template <int FILL>
+__global__ void __launch_bounds__(kBlock) k_pm(int64_t cnnz, int sh, const int* __restrict__ crow,
+                                               const int* __restrict__ cci, const int* __restrict__ xrp,
+                                               const int* __restrict__ xci, const int* __restrict__ yrp,
+                                               const int* __restrict__ yci, int64_t* __restrict__ cnt,
+                                               const int64_t* __restrict__ off, int2* __restrict__ pairs) {
+  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int G = 1 << sh, l = (int)(q & (G - 1));
+  const int64_t e = q >> sh;
+  if (!FILL && e == cnnz && l == 0) cnt[cnnz] = 0;
+  const bool live = e < cnnz;  // (every lane of the wave takes part in the ballots)
+  const int row = live ? crow[e] : 0, J = live ? cci[e] : 0;
+  const int a0 = live ? xrp[row] : 0, a1 = live ? xrp[row + 1] : 0;
+  const int lane = threadIdx.x & 63, first = lane & ~(G - 1);
+  const unsigned long long group = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << first;
+  int64_t p = FILL && live ? off[e] : 0;
   int64_t c = 0;
-  for (int a = xrp[lo]; a < xrp[lo + 1]; ++a) c += find_col(yci, yrp[xci[a]], yrp[xci[a] + 1], J) >= 0;
-  cnt[e] = c;
-}
-
-// Product map, pass 2: the (x position, y position) pairs of each entry in
-// ascending inner index (the order of the fold that forms the entry).
-__global__ void k_pm_fill(int nrows, int64_t cnnz, const int* __restrict__ crp, const int* __restrict__ cci,
-                          const int* __restrict__ xrp, const int* __restrict__ xci, const int* __restrict__ yrp,
-                          const int* __restrict__ yci, const int64_t* __restrict__ off, int2* __restrict__ pairs) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= cnnz) return;
-  int lo = 0, hi = nrows;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if ((int64_t)crp[mid] <= e) lo = mid; else hi = mid;
+  int steps = (a1 - a0 + G - 1) >> sh;
+  for (int o = 32; o > 0; o >>= 1) steps = max(steps, __shfl_xor(steps, o, 64));
+  for (int t = 0; t < steps; ++t) {
+    const int a = a0 + t * G + l;
+    int f = -1;
+    if (a < a1) {
+      const int k = xci[a];
+      f = find_col(yci, yrp[k], yrp[k + 1], J);
+    }
+    const unsigned long long hits = __ballot(f >= 0) & group;
+    if (FILL && f >= 0) pairs[p + c + __popcll(hits & ((1ull << lane) - 1ull))] = make_int2(a, f);
+    c += __popcll(hits);
   }
-  const int J = cci[e];
-  int64_t p = off[e];
-  for (int a = xrp[lo]; a < xrp[lo + 1]; ++a) {
-    const int q = find_col(yci, yrp[xci[a]], yrp[xci[a] + 1], J);
-    if (q >= 0) pairs[p++] = make_int2(a, q);
-  }
+  if (!FILL && live && l == 0) cnt[e] = c;
 }
 
 // Numeric product through the map (entry by system): the same fold (ascending
@@ -817,62 +871,45 @@ __global__ void k_sell_fill(int n, int ns, const int* __restrict__ rp, const int
   }
 }
 
-// Offset form, pass 1: per slice, the sorted union of its rows' column
-// offsets (col - row); 64 x its size (kSellMaxW + 1 when it overflows).
-__global__ void k_sello_count(int n, int ns, const int* __restrict__ rp, const int* __restrict__ ci,
-                              int* __restrict__ cnt, int* __restrict__ uoff) {
-  const int sl = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sl > ns) return;
-  if (sl == ns) {
-    cnt[ns] = 0;
+// Offset form: the slice's slots are the sorted union of its rows' column
+// offsets (col - row).  One wavefront per slice, lane = row: every lane points
+// at its next entry; the smallest offset over the wave is the next slot, and
+// the lanes that hold it step on.  (A thread per slice walking its 64 rows took
+// 0.43 and 0.67 ms at 100^3 for the two passes.)
+// FILL = 0: cnt = 64 x the number of slots (kSellMaxW + 1 slots when there are
+// more).  FILL = 1: slot records (offset, row mask) and the position map.
+template <int FILL>
+__global__ void __launch_bounds__(kBlock) k_sello_slots(int n, int ns, const int* __restrict__ rp,
+                                                        const int* __restrict__ ci, int* __restrict__ cnt,
+                                                        const int* __restrict__ soff, int4* __restrict__ slots,
+                                                        int* __restrict__ sperm) {
+  const int sl = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (sl >= ns) {
+    if (!FILL && sl == ns && lane == 0) cnt[ns] = 0;
     return;
   }
-  int u[kSellMaxW];
+  const int i = sl * 64 + lane;
+  int k = i < n ? rp[i] : 0;
+  const int k1 = i < n ? rp[i + 1] : 0;
+  const int base = FILL ? soff[sl] : 0;
   int m = 0;
-  bool over = false;
-  const int r1 = min(n, sl * 64 + 64);
-  for (int i = sl * 64; i < r1 && !over; ++i) {
-    for (int k = rp[i]; k < rp[i + 1]; ++k) {
-      const int d = ci[k] - i;
-      int pos = 0;
-      while (pos < m && u[pos] < d) ++pos;
-      if (pos < m && u[pos] == d) continue;
-      if (m == kSellMaxW) {
-        over = true;
-        break;
-      }
-      for (int t = m; t > pos; --t) u[t] = u[t - 1];
-      u[pos] = d;
-      ++m;
+  for (;;) {
+    const int d = k < k1 ? ci[k] - i : INT_MAX;
+    int lo = d;
+    for (int o = 32; o > 0; o >>= 1) lo = min(lo, __shfl_xor(lo, o, 64));
+    if (lo == INT_MAX || m > kSellMaxW) break;
+    const bool mine = d == lo;
+    if (FILL) {
+      const unsigned long long mask = __ballot(mine);
+      sperm[base + m * 64 + lane] = mine ? k : -1;
+      if (lane == 0)
+        slots[(base >> 6) + m] =
+            make_int4(lo, 0, (int)(unsigned)(mask & 0xffffffffull), (int)(unsigned)(mask >> 32));
     }
+    if (mine) ++k;
+    ++m;
   }
-  cnt[sl] = 64 * (over ? kSellMaxW + 1 : m);
-  for (int j = 0; j < kSellMaxW; ++j) uoff[(int64_t)sl * kSellMaxW + j] = j < m ? u[j] : 0;
-}
-
-// Offset form, pass 2: slot records (offset, row mask) and the position map.
-__global__ void k_sello_fill(int n, int ns, const int* __restrict__ rp, const int* __restrict__ ci,
-                             const int* __restrict__ soff, const int* __restrict__ uoff, int4* __restrict__ slots,
-                             int* __restrict__ sperm) {
-  const int sl = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sl >= ns) return;
-  const int base = soff[sl], w = (soff[sl + 1] - base) >> 6;
-  const int* u = uoff + (int64_t)sl * kSellMaxW;
-  for (int p = base; p < base + 64 * w; ++p) sperm[p] = -1;
-  unsigned long long mask[kSellMaxW] = {};
-  const int r1 = min(n, sl * 64 + 64);
-  for (int i = sl * 64; i < r1; ++i) {
-    const int lane = i - sl * 64;
-    for (int k = rp[i]; k < rp[i + 1]; ++k) {
-      const int d = ci[k] - i;
-      int j = 0;
-      while (j < w && u[j] != d) ++j;
-      sperm[base + j * 64 + lane] = k;
-      mask[j] |= 1ull << lane;
-    }
-  }
-  for (int j = 0; j < w; ++j)
-    slots[(base >> 6) + j] = make_int4(u[j], 0, (int)(unsigned)(mask[j] & 0xffffffffull), (int)(unsigned)(mask[j] >> 32));
+  if (!FILL && lane == 0) cnt[sl] = 64 * m;
 }
 
 __global__ void k_sell_vals(int64_t m, const int* __restrict__ sperm, const double* __restrict__ v,
@@ -909,7 +946,7 @@ __global__ void __launch_bounds__(kBlock) k_sell_uniform(int ns, const int* __re
       if (uv32) uv32[(base >> 6) + j] = (float)x0;
     }
   }
-  if (__ballot(bad) && lane == 0) atomicOr(flags, 1);
+  if (__ballot(bad) && lane == 0) *flags = 1;  // (plain stores of the same value)
 }
 
 // ---------------------------------------------------------- host helpers
@@ -938,14 +975,21 @@ int64_t read_i64(const int64_t* d, hipStream_t s) {
 
 // Builds the product map of C = X Y on C's pattern; false (and nothing kept)
 // when its pairs would exceed `budget`.
-bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, const int* xrp, const int* xci,
-                       const int* yrp, const int* yci, int64_t budget, DBuf<int64_t>& off, DBuf<int2>& pairs,
-                       hipStream_t s) {
+bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, int64_t xnnz, const int* xrp,
+                       const int* xci, const int* yrp, const int* yci, int64_t budget, DBuf<int64_t>& off,
+                       DBuf<int2>& pairs, hipStream_t s) {
   Arena::Scope scope;
   TBuf<int64_t> cnt;
+  TBuf<int> crow;
   cnt.alloc(cnnz + 1);
-  hipLaunchKernelGGL(k_pm_count, dim3((unsigned)((cnnz + kBlock) / kBlock)), dim3(kBlock), 0, s, nrows, cnnz, crp, cci,
-                     xrp, xci, yrp, yci, cnt.p);
+  crow.alloc(cnnz);
+  hipLaunchKernelGGL(k_row_ids, dim3(grid_for(nrows)), dim3(kBlock), 0, s, nrows, crp, crow.p);
+  // lanes per entry: about four inner indices each
+  int sh = 0;
+  while (sh < 6 && xnnz > ((int64_t)4 << sh) * nrows) ++sh;
+  const dim3 grid((unsigned)((((cnnz + 1) << sh) + kBlock - 1) / kBlock));
+  hipLaunchKernelGGL(k_pm<0>, grid, dim3(kBlock), 0, s, cnnz, sh, crow.p, cci, xrp, xci, yrp, yci, cnt.p,
+                     (const int64_t*)nullptr, (int2*)nullptr);
   off.alloc(cnnz + 1);
   cub_call([&](void* t, size_t& b) {
     return hipcub::DeviceScan::ExclusiveSum(t, b, cnt.p, off.p, (int)(cnnz + 1), s);
@@ -956,8 +1000,8 @@ bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, 
     return false;
   }
   pairs.alloc(std::max<int64_t>(total, 1));
-  hipLaunchKernelGGL(k_pm_fill, dim3((unsigned)((cnnz + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, nrows, cnnz, crp,
-                     cci, xrp, xci, yrp, yci, off.p, pairs.p);
+  hipLaunchKernelGGL(k_pm<1>, grid, dim3(kBlock), 0, s, cnnz, sh, crow.p, cci, xrp, xci, yrp, yci, (int64_t*)nullptr,
+                     off.p, pairs.p);
   return true;
 }
 
@@ -1102,12 +1146,17 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   for (int sy = 0; sy < S; ++sy) L.omegaPS[sy] = (4.0 / 3.0) / L.rhoS[sy];
   L.rho = L.rhoS[0];
   L.omegaP = L.omegaPS[0];
-  // P
   Arena::Scope scope;
+  // P: lanes per row for twice the mean row length
+  int psh = 0;
+  while (psh < 6 && 2 * L.nnz > ((int64_t)n << psh)) ++psh;
+  const dim3 pg(grid_for(((int64_t)n + 1) << psh));
   if (symbolic) {
     TBuf<int> cnt;
     cnt.alloc(n + 1);
-    hipLaunchKernelGGL(k_p_count, dim3(grid_for(n + 1)), b, 0, s, n, L.rp.p, L.ci.p, L.agg.p, cnt.p);
+    hipLaunchKernelGGL(k_p_rows<0>, pg, b, 0, s, n, psh, L.rp.p, L.ci.p, L.agg.p, cnt.p, (const double*)nullptr, S,
+                       (const int*)nullptr, 0.0, (const int*)nullptr, (int*)nullptr, (double*)nullptr, (int*)nullptr,
+                       (int*)nullptr, (int*)nullptr);
     L.prp.alloc(n + 1);
     exclusive_scan(cnt.p, L.prp.p, n + 1, s);
     L.pnnz = read_int(L.prp.p + n, s);
@@ -1115,13 +1164,11 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     L.pv.alloc(L.pnnz * S);
   }
   if (symbolic) {
-    hipLaunchKernelGGL(k_p_fill, dim3(grid_for(n)), b, 0, s, n, L.rp.p, L.ci.p, L.v.p, S, L.diagpos.p, L.agg.p,
-                       L.omegaPS[0], L.prp.p, L.pci.p, L.pv.p);
     L.pao.alloc(L.pnnz + 1);
     L.pak.alloc(L.nnz);
     L.prow.alloc(L.pnnz);
-    hipLaunchKernelGGL(k_pmap_build, dim3(grid_for(n)), b, 0, s, n, L.rp.p, L.ci.p, L.agg.p, L.prp.p, L.pci.p,
-                       L.pao.p, L.pak.p, L.prow.p);
+    hipLaunchKernelGGL(k_p_rows<1>, pg, b, 0, s, n, psh, L.rp.p, L.ci.p, L.agg.p, (int*)nullptr, L.v.p, S,
+                       L.diagpos.p, L.omegaPS[0], L.prp.p, L.pci.p, L.pv.p, L.pao.p, L.pak.p, L.prow.p);
   }
   if (!symbolic || S > 1)
     hipLaunchKernelGGL(k_p_refill, dim3(sys_grid(L.pnnz, sh)), b, 0, s, L.pnnz, S, sh, L.pao.p, L.pak.p, L.prow.p,
@@ -1130,7 +1177,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   // R = P^T
   const int nc = L.nagg;
   if (symbolic) {
-    TBuf<int> rowid, iota, keys_out, cnt;
+    TBuf<int> rowid, iota, keys_out;
     rowid.alloc(L.pnnz);
     iota.alloc(L.pnnz);
     keys_out.alloc(L.pnnz);
@@ -1143,11 +1190,8 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
       return hipcub::DeviceRadixSort::SortPairs(t, bb, L.pci.p, keys_out.p, iota.p, L.rperm.p, (int)L.pnnz, 0,
                                                 end_bit, s);
     }, s);
-    cnt.alloc(nc + 1);
-    AMG_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int) * (nc + 1), s));
-    hipLaunchKernelGGL(k_col_count, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.pci.p, cnt.p);
     L.rrp.alloc(nc + 1);
-    exclusive_scan(cnt.p, L.rrp.p, nc + 1, s);
+    hipLaunchKernelGGL(k_key_rows, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, nc, keys_out.p, L.rrp.p);
     L.rci.alloc(L.pnnz);
     L.rv.alloc(L.pnnz * S);
     hipLaunchKernelGGL(k_t_cols, dim3(grid_for(L.pnnz)), b, 0, s, L.pnnz, L.rperm.p, rowid.p, L.rci.p);
@@ -1182,7 +1226,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
       hipLaunchKernelGGL(k_spgemm_sym_w<1>, dim3(n), dim3(64), 0, s, n, L.rp.p, L.ci.p, L.prp.p, L.pci.p,
                          L.aprp.p, L.apci.p);
       AMG_HIP(hipGetLastError());
-      apmap = build_product_map(n, L.apnnz, L.aprp.p, L.apci.p, L.rp.p, L.ci.p, L.prp.p, L.pci.p, budget, L.apmo,
+      apmap = build_product_map(n, L.apnnz, L.aprp.p, L.apci.p, L.nnz, L.rp.p, L.ci.p, L.prp.p, L.pci.p, budget, L.apmo,
                                 L.apm, s);
       if (!apmap) {
         L.apmo.release();
@@ -1194,7 +1238,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     hipLaunchKernelGGL(k_spgemm_fill, dim3(grid_for(n)), b, 0, s, n, L.rp.p, L.ci.p, L.v.p, L.prp.p, L.pci.p,
                        L.pv.p, L.aprp.p, L.apci.p, L.apv.p, S);
     AMG_HIP(hipGetLastError());
-    apmap = build_product_map(n, L.apnnz, L.aprp.p, L.apci.p, L.rp.p, L.ci.p, L.prp.p, L.pci.p, budget, L.apmo,
+    apmap = build_product_map(n, L.apnnz, L.aprp.p, L.apci.p, L.nnz, L.rp.p, L.ci.p, L.prp.p, L.pci.p, budget, L.apmo,
                               L.apm, s);
   }
   const int sy0 = symbolic && !wide_ap ? 1 : 0;  // systems formed by the merge above
@@ -1231,7 +1275,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
     hipLaunchKernelGGL(k_spgemm_sym_w<1>, dim3(nc), dim3(64), 0, s, nc, Lr.rrp.p, Lr.rci.p, Lr.aprp.p, Lr.apci.p,
                        C.rp.p, C.ci.p);
     Lr.pmaps = apmap &&
-               build_product_map(nc, C.nnz, C.rp.p, C.ci.p, Lr.rrp.p, Lr.rci.p, Lr.aprp.p, Lr.apci.p, budget,
+               build_product_map(nc, C.nnz, C.rp.p, C.ci.p, Lr.pnnz, Lr.rrp.p, Lr.rci.p, Lr.aprp.p, Lr.apci.p, budget,
                                  Lr.cmo, Lr.cm, s);
     if (!Lr.pmaps) {
       Lr.apmo.release();
@@ -1291,10 +1335,9 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
       cnt.alloc(ns + 1);
       {
         // offset form first: every slice's offsets fit kSellMaxW slots
-        TBuf<int> uoff;
-        uoff.alloc((int64_t)ns * kSellMaxW);
-        hipLaunchKernelGGL(k_sello_count, dim3((ns + kBlock) / kBlock), dim3(kBlock), 0, s, L.n, ns, L.rp.p, L.ci.p,
-                           cnt.p, uoff.p);
+        const dim3 gs((ns + kBlock / 64) / (kBlock / 64));
+        hipLaunchKernelGGL(k_sello_slots<0>, gs, dim3(kBlock), 0, s, L.n, ns, L.rp.p, L.ci.p, cnt.p,
+                           (const int*)nullptr, (int4*)nullptr, (int*)nullptr);
         std::vector<int> h(ns + 1);
         AMG_HIP(hipMemcpyAsync(h.data(), cnt.p, sizeof(int) * (ns + 1), hipMemcpyDeviceToHost, s));
         AMG_HIP(hipStreamSynchronize(s));
@@ -1310,8 +1353,8 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
           L.sslot.alloc(tot / 64 + kSellMaxW);  // padded: a slice loads kSellMaxW records at once
           AMG_HIP(hipMemsetAsync(L.sslot.p, 0, L.sslot.bytes(), s));
           L.sperm.alloc(tot);
-          hipLaunchKernelGGL(k_sello_fill, dim3((ns + kBlock - 1) / kBlock), dim3(kBlock), 0, s, L.n, ns, L.rp.p,
-                             L.ci.p, L.soff.p, uoff.p, L.sslot.p, L.sperm.p);
+          hipLaunchKernelGGL(k_sello_slots<1>, gs, dim3(kBlock), 0, s, L.n, ns, L.rp.p, L.ci.p, (int*)nullptr,
+                             L.soff.p, L.sslot.p, L.sperm.p);
           L.sv.alloc(tot);
           if (H.fp32()) L.sv32.alloc(tot);
           L.sell_len = tot;
@@ -1400,7 +1443,8 @@ void validate_csr(int n, int64_t nnz, const int* d_rp, const int* d_ci, int* d_f
 uint64_t pattern_hash(int n, int64_t nnz, const int* d_rp, const int* d_ci, int* d_flags, int* h_flags,
                       hipStream_t s) {
   AMG_HIP(hipMemsetAsync(d_flags, 0, 8, s));
-  hipLaunchKernelGGL(k_hash, dim3(1024), dim3(kBlock), 0, s, n, nnz, d_rp, d_ci, (unsigned long long*)d_flags);
+  hipLaunchKernelGGL(k_hash, dim3(std::min(grid_for(nnz, 4 * kBlock), 512)), dim3(kBlock), 0, s, n, nnz, d_rp, d_ci,
+                     (unsigned long long*)d_flags);
   AMG_HIP(hipGetLastError());
   sync_flags(d_flags, h_flags, 2, s);
   uint64_t h;
@@ -1485,7 +1529,7 @@ void transpose_csr_pattern(int n, int64_t nnz, const int* rp, const int* ci, DBu
                            DBuf<int>& perm, hipStream_t s) {
   const dim3 b(kBlock);
   Arena::Scope scope;
-  TBuf<int> rowid, iota, keys_out, cnt;
+  TBuf<int> rowid, iota, keys_out;
   rowid.alloc(std::max<int64_t>(nnz, 1));
   iota.alloc(std::max<int64_t>(nnz, 1));
   keys_out.alloc(std::max<int64_t>(nnz, 1));
@@ -1497,11 +1541,8 @@ void transpose_csr_pattern(int n, int64_t nnz, const int* rp, const int* ci, DBu
   cub_call([&](void* t, size_t& bb) {
     return hipcub::DeviceRadixSort::SortPairs(t, bb, ci, keys_out.p, iota.p, perm.p, (int)nnz, 0, end_bit, s);
   }, s);
-  cnt.alloc(n + 1);
-  AMG_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int) * (n + 1), s));
-  hipLaunchKernelGGL(k_col_count, dim3(grid_for(nnz)), b, 0, s, nnz, ci, cnt.p);
   trp.alloc(n + 1);
-  exclusive_scan(cnt.p, trp.p, n + 1, s);
+  hipLaunchKernelGGL(k_key_rows, dim3(grid_for(nnz)), b, 0, s, nnz, n, keys_out.p, trp.p);
   tci.alloc(std::max<int64_t>(nnz, 1));
   hipLaunchKernelGGL(k_t_cols, dim3(grid_for(nnz)), b, 0, s, nnz, perm.p, rowid.p, tci.p);
   AMG_HIP(hipGetLastError());
