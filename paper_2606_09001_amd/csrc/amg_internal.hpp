@@ -165,6 +165,7 @@ struct Shape {
   int u = 8;       // CSR-stream: staged entries per thread (buffer of kBlock*u entries)
   int nt = 0;      // 1: the operator's entry stream is read with nontemporal loads
   int rows_per_block = 256;
+  int w = 8;       // offset form: most slots of a slice
   int grid = 1;
   int max_block_nnz = 0;
 };
@@ -207,6 +208,7 @@ struct Level {
   bool sell = false;
   int sell_form = 0;          // 1: explicit columns, 2: slot offsets
   bool sell_uniform = false;
+  int sell_w = 0;             // most slots (or entries) of a slice
   int64_t sell_len = 0;
   DBuf<int> soff, sci, sperm;
   DBuf<int4> sslot;

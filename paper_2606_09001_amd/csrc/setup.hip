@@ -1360,6 +1360,7 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
           L.sell_len = tot;
           L.sell = true;
           L.sell_form = 2;
+          L.sell_w = wmax;
         }
       }
     }

@@ -558,7 +558,14 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
 // UNI: every slot holds one value (op.v by slot): the sweep reads no value per
 // entry.  Constant-coefficient operators then cost their vectors: 128^3
 // Poisson, FP64: residual 24 -> 14 us, product 31 -> 23, post-smoother 36 -> 19.
-template <bool NT, bool UNI, class Op>
+// W: slots loaded per slice (the matrix's most, 3, 5, 7 or 8).  Loading a slot
+// that no row has costs as much as one that it has: with 8 always, the product
+// sweep of 10^7 tridiagonal unknowns (3 slots) took 110 us, now 85, that of 512^2
+// (5 slots) 8.9, now 8.2; 7-point operators gain 1 %.  (Bytes are not what
+// bounds the 7-point sweeps: storing only the upper triangle of a symmetric
+// operator and reading the mirror values from cache took 169 of 691 MB from the
+// 192^3 product and left it at 107 us.)
+template <bool NT, bool UNI, int W, class Op>
 __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__ soff,
                                                   const int4* __restrict__ slots, Op op, const Ctl* __restrict__ ctl,
                                                   double* __restrict__ partials) {
@@ -574,29 +581,29 @@ __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__
   if (ctl && ctl->done) return;
   auto fold = fold_in(op);
   const typename Op::Row in = op.row_in(rc);
-  typename std::remove_const<typename std::remove_pointer<decltype(op.v)>::type>::type val[kSellMaxW];
+  typename std::remove_const<typename std::remove_pointer<decltype(op.v)>::type>::type val[W];
 #pragma unroll
-  for (int j = 0; j < kSellMaxW; ++j)
+  for (int j = 0; j < W; ++j)
     val[j] = UNI ? op.v[sb + j] : stream_load<NT>(op.v + off + min(j, w - 1) * 64 + lane);
-  // the slice's kSellMaxW records as one block (the array is padded so the
+  // the slice's W records as one block (the array is padded so the
   // last slice's block stays in bounds)
-  int4 rec[kSellMaxW];
+  int4 rec[W];
 #pragma unroll
-  for (int j = 0; j < kSellMaxW; ++j) rec[j] = slots[sb + j];
-  int col[kSellMaxW];
-  bool has[kSellMaxW];
+  for (int j = 0; j < W; ++j) rec[j] = slots[sb + j];
+  int col[W];
+  bool has[W];
 #pragma unroll
-  for (int j = 0; j < kSellMaxW; ++j) {
+  for (int j = 0; j < W; ++j) {
     const unsigned bits = lane < 32 ? (unsigned)rec[j].z : (unsigned)rec[j].w;
     has[j] = j < w && ((bits >> (lane & 31)) & 1u);
     col[j] = has[j] ? rc + rec[j].x : rc;
   }
-  PT pv[kSellMaxW];
+  PT pv[W];
 #pragma unroll
-  for (int j = 0; j < kSellMaxW; ++j) pv[j] = op.prod_v(val[j], col[j]);
+  for (int j = 0; j < W; ++j) pv[j] = op.prod_v(val[j], col[j]);
   PT s = 0;
 #pragma unroll
-  for (int j = 0; j < kSellMaxW; ++j) s = has[j] ? s + pv[j] : s;
+  for (int j = 0; j < W; ++j) s = has[j] ? s + pv[j] : s;
   if (!fold_out(op, fold, beta)) return;
   if (row < n) row_epi(op, row, s, in, beta, d);
   publish_partials<Op::NRED>(d, partials);
@@ -616,12 +623,25 @@ __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__
 template <bool NT, class Op>
 void sweep_form(const Shape& sh, int n, const int* rp, const int* ci, const Op& op, const Ctl* ctl,
                 double* partials, hipStream_t s) {
-  if (sh.stream == 4) {
-    hipLaunchKernelGGL((k_sello<false, true, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp,
-                       reinterpret_cast<const int4*>(ci), op, ctl, partials);
-  } else if (sh.stream == 3) {
-    hipLaunchKernelGGL((k_sello<NT, false, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp,
-                       reinterpret_cast<const int4*>(ci), op, ctl, partials);
+  if (sh.stream >= 3) {
+    const int4* slots = reinterpret_cast<const int4*>(ci);
+#define AMG_SELLO(W)                                                                                              \
+  if (sh.stream == 4)                                                                                             \
+    hipLaunchKernelGGL((k_sello<false, true, W, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, slots, op, ctl,   \
+                       partials);                                                                                 \
+  else                                                                                                            \
+    hipLaunchKernelGGL((k_sello<NT, false, W, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, slots, op, ctl,     \
+                       partials);
+    if (sh.w <= 3) {
+      AMG_SELLO(3)
+    } else if (sh.w <= 5) {
+      AMG_SELLO(5)
+    } else if (sh.w <= 7) {
+      AMG_SELLO(7)
+    } else {
+      AMG_SELLO(8)
+    }
+#undef AMG_SELLO
   } else if (sh.stream == 2) {
     hipLaunchKernelGGL((k_sell<NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, ci, op, ctl, partials);
   } else if (sh.stream) {
@@ -1625,6 +1645,7 @@ void choose_shapes(Hierarchy& H, hipStream_t s) {
     if (L.sell) {
       L.shA = Shape{};
       L.shA.stream = L.sell_uniform ? 4 : L.sell_form == 2 ? 3 : 2;
+      L.shA.w = L.sell_w;
       L.shA.grid = round8(((int64_t)L.n + kBlock - 1) / kBlock);
     } else if (f32) {
       L.shA = pick_shape(H, "A", (int)l, L.rp, L.ci, L.n, nc, [&](int64_t len) {
