@@ -76,7 +76,7 @@ def kernel_source_hash(source="solve.hip"):
 
 _SWEEP = r"k_(?:stream<\d+, |sell<|sello<)[^>]*"
 FINE_KERNELS = {  # tag -> (regex on the demangled name, grid rank: 0 = largest grid = level 0)
-    "spmv_dot_L0": (_SWEEP + r"OpSpmvXpayDev>", 0),
+    "spmv_dot_L0": (_SWEEP + r"OpSpmvXpay>", 0),
     "pre_L0": (_SWEEP + r"OpResid<double, double> >", 0),
     "post_L0": (_SWEEP + r"OpPost<double, double, double, 1> >", 0),
     "restrict_L0": (_SWEEP + r"OpRestrict<double, double> >", 0),

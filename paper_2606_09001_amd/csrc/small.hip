@@ -2,8 +2,8 @@
 // one compute unit: two levels (the fine level and a dense coarsest level),
 // at most 1024 fine rows.  The per-kernel path launches about twenty kernels
 // per iteration, so a 1024-unknown solve is bound by launch and
-// synchronisation latency, not by bytes.  Here one workgroup of 1024 threads
-// (thread i owns fine row i) runs every iteration, restart and the final
+// synchronisation latency, not by bytes.  Here one workgroup of 512 threads
+// (thread i owns fine rows i and i + 512) runs every iteration, restart and the final
 // true-residual check in a single launch:
 //   - the CG vectors and the cycle vectors live in LDS, so every gather of
 //     a sweep is an LDS read;
@@ -11,12 +11,19 @@
 //     (A_0 is applied three times per iteration);
 //   - P_0 and R_0 are staged in LDS once per solve; R_0 is applied with a
 //     group of lanes per coarse row;
-//   - the explicit coarse inverse is read from global memory (L2) by
-//     wavefront column blocks: a wave takes a block of columns, so each
-//     column's loads have a wave-uniform base and are coalesced over rows,
-//     and the block sums are added per row in wave order;
+//   - the explicit coarse inverse lives in registers for the whole solve: a
+//     thread owns two adjacent rows of a block of columns (28 of them in 112
+//     registers, which holds all of an inverse of up to about 165 unknowns;
+//     a larger one's other columns are read from L2 in every cycle), and the
+//     block sums are added per row in block order.  Reading all of it from L2
+//     bounded the solve by the latency of its load rounds (68 of the kernel's
+//     160 us for 18 iterations with a 150 x 150 inverse): 32^2 Poisson to
+//     1e-10 187 us then, 150 now.  A_0's columns are kept two to a register
+//     and b is read again where it is needed, which leaves room for 28
+//     columns without a spill.  16 waves of half as many columns each were
+//     slower (222 us, with the inverse in L2): every barrier costs more;
 //   - dot products are fixed-order block reductions (wave butterfly, then the
-//     16 wave sums in order), so a solve is bitwise reproducible.
+//     8 wave sums in order), so a solve is bitwise reproducible.
 // The method is the one of pcg_solve: PCG from x0 = 0, damped-Jacobi (or L1)
 // V(1,1) cycle with R = P^T and the exact coarse solve, recursive-residual
 // stopping, true-residual verification with at most 5 restarts, flexible
@@ -40,9 +47,9 @@ constexpr int kSN = kST * kSR;   // largest fine level
 constexpr int kSRow = 8;         // entries per row of A_0
 constexpr int kSCoarse = 256;    // largest padded coarsest level
 constexpr int kSPCap = 3200;     // entries of P_0 (and of R_0 = P_0^T) staged in LDS
-constexpr int kSWaves = kST / 64;
-constexpr int kSPairs = kSCoarse / 128;  // row-pair chunks per lane in the inverse product
-constexpr int kSCols = 4;        // inverse columns per step (loads in flight: kSCols x rows per lane)
+constexpr int kSBlocks = 8;      // most column blocks of the inverse
+constexpr int kSHold = 28;       // inverse columns a thread holds in registers (a multiple of 4)
+constexpr int kSCols = 4;        // inverse columns per step beyond those (loads in flight)
 
 struct SmallArgs {
   int n, nc, m, lgR, maxiter, flexible;
@@ -113,8 +120,9 @@ __device__ inline double wg_sum(double v, double* red) {
 
 __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
   __shared__ double s_r[kSN], s_z[kSN], s_p[kSN], s_q[kSN], s_xc[kSN], s_rc[kSN];
-  __shared__ double s_b1[kSCoarse], s_x1[kSCoarse];
-  __shared__ double s_gp[kSWaves][kSCoarse];
+  __shared__ double s_x1[kSCoarse];
+  __shared__ __align__(16) double s_b1[kSCoarse + 4 * kSBlocks];  // zeros past n_c
+  __shared__ double s_gp[2 * kST + kSBlocks];  // at most kST / pairs blocks of 2 pairs rows
   __shared__ double s_red[4][kST / 64];
   __shared__ int s_prp[kSN + 1], s_rrp[kSCoarse + 1];
   __shared__ int s_pci[kSPCap], s_rci[kSPCap];
@@ -132,10 +140,10 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
   }
   // this thread's rows t + q kST: their rows of A_0 in registers (indices
   // clamped into the row; entries past the row's length are masked out of
-  // every sum), their smoother weights, right-hand side and iterate
-  int row[kSR], na[kSR], acol[kSR][kSRow];
+  // every sum), their smoother weights and iterate
+  int row[kSR], na[kSR], acol[kSR][kSRow / 2];   // two 16-bit columns per word
   bool own[kSR];
-  double aval[kSR][kSRow], swi[kSR], bi[kSR], xi[kSR];
+  double aval[kSR][kSRow], swi[kSR], xi[kSR];
 #pragma unroll
   for (int q = 0; q < kSR; ++q) {
     own[q] = t + q * kST < a.n;
@@ -145,11 +153,11 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
 #pragma unroll
     for (int j = 0; j < kSRow; ++j) {
       const int k = ka + min(j, max(na[q] - 1, 0));
-      acol[q][j] = a.aci[k];
+      if (j & 1) acol[q][j / 2] |= a.aci[k] << 16;
+      else acol[q][j / 2] = a.aci[k];
       aval[q][j] = a.av[k];
     }
     swi[q] = a.sw[row[q]];
-    bi[q] = own[q] ? a.b[row[q]] : 0.0;
     xi[q] = 0.0;
   }
   __syncthreads();
@@ -158,23 +166,31 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
     double s = 0.0;
 #pragma unroll
     for (int j = 0; j < kSRow; ++j) {
-      const double pr = aval[q][j] * v[acol[q][j]];
+      const int cw = opaque(acol[q][j / 2]);       // unpacked here, not kept unpacked
+      const double pr = aval[q][j] * v[j & 1 ? cw >> 16 : cw & 0xffff];
       s = j < na[q] ? s + pr : s;
     }
     return s;
   };
   const int gR = 1 << a.lgR;
   const int rrow = t >> a.lgR, rl = t & (gR - 1);
-  // coarse product: wave wv takes columns [c0w, c1w), lane ln the row pairs
-  // (2 ln + 128 r, +1) for r < rpl, one 16-byte load per pair (a compute
-  // unit reads L2 at twice the rate with 16-byte as with 8-byte lane
-  // accesses); the wave index, column range and chunk count are
-  // wave-uniform, so the column loads have scalar base addresses and the
-  // loop has no divergent branches.  The padded order m is a multiple of 16.
-  const int wv = __builtin_amdgcn_readfirstlane(t >> 6), ln = t & 63;
-  const int Lw = (a.nc + kSWaves - 1) / kSWaves;
-  const int c0w = min(wv * Lw, a.nc), c1w = min(c0w + Lw, a.nc);
-  const int rpl = (a.nc + 127) >> 7;
+  // coarse product: thread t takes rows 2 gp, 2 gp + 1 of the columns
+  // [gc, gc + Lc) (one 16-byte load per column, coalesced over gp).  Lc is a
+  // multiple of 4, the same for every block; columns past n_c count as zeros
+  // (s_b1 is zero there), and the padded order m covers an odd n_c's last pair.
+  const int pairs = (a.nc + 1) >> 1;
+  const int nblk = min(kST / pairs, kSBlocks);
+  const int Lc = ((a.nc + 4 * nblk - 1) / (4 * nblk)) * 4;
+  const int gb = min(t / pairs, nblk - 1), gp = t % pairs, gc = gb * Lc;
+  const bool gown = t < nblk * pairs;
+  const double* ginv = a.inv + 2 * gp;
+  double2 hv[kSHold];
+#pragma unroll
+  for (int j = 0; j < kSHold; ++j) {
+    hv[j] = *reinterpret_cast<const double2*>(ginv + (int64_t)min(gc + j, a.nc - 1) * a.m);
+    if (gc + j >= a.nc) hv[j] = double2{0.0, 0.0};
+  }
+  for (int i = a.nc + t; i < kSCoarse + 4 * kSBlocks; i += kST) s_b1[i] = 0.0;
 
   // z = M^-1 r (s_r -> s_z); returns <r, z>, and <z, q> in zq when flexible
   auto vcycle = [&](double& zq) -> double {
@@ -209,44 +225,37 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
     __syncthreads();
     {                                              // x_1 = A_c^-1 b_1
       phase_fence();
-      double acc[kSPairs][2];
+      double acc0 = 0.0, acc1 = 0.0;
+      auto add = [&](const double2& v, double bj) {
+        const double p0 = v.x * bj, p1 = v.y * bj;
+        acc0 = acc0 + p0;
+        acc1 = acc1 + p1;
+      };
 #pragma unroll
-      for (int r = 0; r < kSPairs; ++r) acc[r][0] = acc[r][1] = 0.0;
-      const int jend = opaque(c1w);
-      for (int j0 = c0w; j0 < jend; j0 += kSCols) {
-        // columns past the block's end and pairs past the padded order load
-        // a valid pair (clamped) and are left out of the sums
-        double2 v[kSCols][kSPairs];
+      for (int j = 0; j < kSHold; j += 4) {
+        if (j < Lc) {                              // the same for every thread
 #pragma unroll
-        for (int u = 0; u < kSCols; ++u) {
-          const double* col = a.inv + (int64_t)min(j0 + u, jend - 1) * a.m;
-#pragma unroll
-          for (int r = 0; r < kSPairs; ++r)
-            if (r < rpl) v[u][r] = *reinterpret_cast<const double2*>(col + min(2 * ln + 128 * r, a.m - 2));
-        }
-#pragma unroll
-        for (int u = 0; u < kSCols; ++u) {
-          const double bj = s_b1[min(j0 + u, jend - 1)];
-#pragma unroll
-          for (int r = 0; r < kSPairs; ++r) {
-            if (r < rpl) {
-              const double p0 = v[u][r].x * bj, p1 = v[u][r].y * bj;
-              acc[r][0] = j0 + u < jend ? acc[r][0] + p0 : acc[r][0];
-              acc[r][1] = j0 + u < jend ? acc[r][1] + p1 : acc[r][1];
-            }
-          }
+          for (int u = 0; u < 4; ++u) add(hv[j + u], s_b1[gc + j + u]);
         }
       }
+      const int jend = opaque(Lc);
+      for (int j0 = kSHold; j0 < jend; j0 += kSCols) {
+        double2 v[kSCols];                         // columns past the matrix: its last one, times zero
 #pragma unroll
-      for (int r = 0; r < kSPairs; ++r)
+        for (int u = 0; u < kSCols; ++u)
+          v[u] = *reinterpret_cast<const double2*>(ginv + (int64_t)min(gc + j0 + u, a.nc - 1) * a.m);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-          if (2 * ln + 128 * r + h < a.nc) s_gp[wv][2 * ln + 128 * r + h] = acc[r][h];
+        for (int u = 0; u < kSCols; ++u)
+          if (j0 + (u & ~3) < jend) add(v[u], s_b1[gc + j0 + u]);
+      }
+      if (gown) {
+        s_gp[gb * a.nc + 2 * gp] = acc0;
+        if (2 * gp + 1 < a.nc) s_gp[gb * a.nc + 2 * gp + 1] = acc1;
+      }
       __syncthreads();
-      if (t < a.nc) {                              // the column blocks' sums in wave order
-        double s = 0.0;
-        for (int q = 0; q < kSWaves; ++q)
-          if (q * Lw < a.nc) s += s_gp[q][t];
+      if (t < a.nc) {                              // the column blocks' sums in block order
+        double s = s_gp[t];
+        for (int q = 1; q < nblk; ++q) s += s_gp[q * a.nc + t];
         s_x1[t] = s;
       }
     }
@@ -279,9 +288,10 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
   double bbp = 0.0;
 #pragma unroll
   for (int q = 0; q < kSR; ++q) {
-    if (own[q]) s_r[row[q]] = bi[q];
+    const double bi = own[q] ? a.b[row[q]] : 0.0;
+    if (own[q]) s_r[row[q]] = bi;
     s_q[t + q * kST] = 0.0;
-    bbp += bi[q] * bi[q];
+    bbp += bi * bi;
   }
   const double bb = wg_sum(bbp, s_red[2]);
   const double thresh = (a.tol * a.tol) * bb;
@@ -364,7 +374,7 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
 #pragma unroll
       for (int q = 0; q < kSR; ++q) {
         if (!own[q]) continue;
-        const double ti = bi[q] - arow(q, s_xc);
+        const double ti = a.b[opaque(row[q])] - arow(q, s_xc);
         s_r[row[q]] = ti;
         tp += ti * ti;
       }
