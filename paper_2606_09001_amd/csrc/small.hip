@@ -18,7 +18,8 @@
 //     block sums are added per row in block order.  Reading all of it from L2
 //     bounded the solve by the latency of its load rounds (68 of the kernel's
 //     160 us for 18 iterations with a 150 x 150 inverse): 32^2 Poisson to
-//     1e-10 187 us then, 150 now.  A_0's columns are kept two to a register
+//     1e-10 187 us then, 150 so and 145 with the pre-smoothing done where r
+//     is written and the last two steps of a wave's sum in registers.  A_0's columns are kept two to a register
 //     and b is read again where it is needed, which leaves room for 28
 //     columns without a spill.  16 waves of half as many columns each were
 //     slower (222 us, with the inverse in L2): every barrier costs more;
@@ -92,18 +93,35 @@ __device__ inline double dpp_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// v of this lane plus v of lane ^ STEP (16 or 32): swapping the odd rows
+// (the upper half) of one copy with the even rows (the lower half) of another
+// leaves both partners' values side by side in every lane.
+template <int STEP>
+__device__ inline double swap_sum(double v) {
+  const unsigned lo = __double2loint(v), hi = __double2hiint(v);
+  if constexpr (STEP == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  }
+}
+
 // Sum over the wavefront, every lane gets the same bits: partner sums within
 // quads (lane ^ 1, lane ^ 2), then the mirrored half row and row (lane i with
-// 7 - i and 15 - i of its group), then across rows (lane ^ 16, lane ^ 32).
+// 7 - i and 15 - i of its group), then across rows (lane ^ 16, lane ^ 32, by
+// register swaps: an LDS permutation costs a round trip each).
 // Each step adds two equal-rank partial sums, so all lanes agree.
 __device__ inline double wave_sum_fast(double v) {
   v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   v += dpp_f64<0x141>(v);  // row_half_mirror
   v += dpp_f64<0x140>(v);  // row_mirror
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
-  return v;
+  v = swap_sum<16>(v);
+  return swap_sum<32>(v);
 }
 
 // Sum of v over the workgroup in a fixed order; every thread gets the total.
@@ -192,14 +210,10 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
   }
   for (int i = a.nc + t; i < kSCoarse + 4 * kSBlocks; i += kST) s_b1[i] = 0.0;
 
-  // z = M^-1 r (s_r -> s_z); returns <r, z>, and <z, q> in zq when flexible
+  // z = M^-1 r (s_r, and s_xc = sw o r by its writer, -> s_z); returns <r, z>, and <z, q> in zq when flexible
   auto vcycle = [&](double& zq) -> double {
 #pragma unroll
-    for (int q = 0; q < kSR; ++q)                  // pre-smoothing from zero
-      if (own[q]) s_xc[row[q]] = swi[q] * s_r[row[q]];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kSR; ++q)                  // its residual
+    for (int q = 0; q < kSR; ++q)                  // residual of the pre-smoothed zero
       if (own[q]) s_rc[row[q]] = s_r[row[q]] - arow(q, s_xc);
     __syncthreads();
     {                                              // b_1 = R r_c, gR lanes per coarse row
@@ -289,7 +303,10 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
 #pragma unroll
   for (int q = 0; q < kSR; ++q) {
     const double bi = own[q] ? a.b[row[q]] : 0.0;
-    if (own[q]) s_r[row[q]] = bi;
+    if (own[q]) {
+      s_r[row[q]] = bi;
+      s_xc[row[q]] = swi[q] * bi;                  // pre-smoothing from zero
+    }
     s_q[t + q * kST] = 0.0;
     bbp += bi * bi;
   }
@@ -340,6 +357,7 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
           xi[q] = xi[q] + alpha * s_p[i];
           const double ri = s_r[i] - alpha * qi[q];
           s_r[i] = ri;
+          s_xc[i] = swi[q] * ri;                   // pre-smoothing from zero
           rrp += ri * ri;
         }
         ++iters;
@@ -382,6 +400,9 @@ __global__ void __launch_bounds__(kST) k_pcg_small(SmallArgs a) {
       if (trr <= thresh) break;
       if (state == 1 && restarts < 5 && iters < a.maxiter) {
         ++restarts;
+#pragma unroll
+        for (int q = 0; q < kSR; ++q)              // every read of s_xc lies before wg_sum's barrier
+          if (own[q]) s_xc[row[q]] = swi[q] * s_r[row[q]];
         __syncthreads();
         continue;
       }
