@@ -295,13 +295,34 @@ __device__ inline double pval(RT v) { return (double)ValCvt<RT>::f(v); }
 
 // (A P) entries from the FP32 cycle's own operands (FP32 A, FP32 or bf16 P),
 // accumulated in FP64: through the product map, or by search (thread per row).
-template <class RT>
+// The map's pairs are read four ahead (level 1 of a 128^3 system: one at a time
+// 0.93 ms, so 0.45).
+// With tpos (the entry a_ji of entry a_ij) the map gives A^T P instead: the
+// patterns and the order of the terms are those of A P.
+template <class RT, class T>
 __global__ void k_ap_map(int64_t m, const int64_t* __restrict__ off, const int2* __restrict__ pairs,
-                         const float* __restrict__ av, const RT* __restrict__ pv, double* __restrict__ ap) {
+                         const T* __restrict__ av, const int* __restrict__ tpos, const RT* __restrict__ pv,
+                         double* __restrict__ ap) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= m) return;
   double acc = 0.0;
-  for (int64_t p = off[e]; p < off[e + 1]; ++p) acc += (double)av[pairs[p].x] * pval(pv[pairs[p].y]);
+  const int64_t p1 = off[e + 1];
+  for (int64_t p = off[e]; p < p1; p += 4) {       // four terms' loads in flight, added in order
+    int2 pr[4];
+    int k[4];
+    double a[4], q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pr[u] = pairs[p + u < p1 ? p + u : p1 - 1];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) k[u] = tpos ? tpos[pr[u].x] : pr[u].x;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      a[u] = (double)av[k[u]];
+      q[u] = pval(pv[pr[u].y]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc = p + u < p1 ? acc + a[u] * q[u] : acc;
+  }
   ap[e] = acc;
 }
 
@@ -324,11 +345,12 @@ __global__ void k_ap_search(int n, const int* __restrict__ rp, const int* __rest
   }
 }
 
-// Q = P - S (A P) (thread per row; P's sorted row is a subset of A P's).
+// Q = P - S (A P) (thread per row; P's sorted row is a subset of A P's); q may
+// be ap.
 template <class RT, class T>
 __global__ void k_q_values(int n, const int* __restrict__ prp, const int* __restrict__ pci,
                            const RT* __restrict__ pv, const int* __restrict__ aprp, const int* __restrict__ apci,
-                           const double* __restrict__ ap, const T* __restrict__ sw, double* __restrict__ q) {
+                           const double* ap, const T* __restrict__ sw, double* q) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double w = (double)sw[i];
@@ -343,16 +365,22 @@ __global__ void k_q_values(int n, const int* __restrict__ prp, const int* __rest
 }
 
 // D^T = P - S (A^T P) on the pattern of A P, for a structurally symmetric A
-// with nonsymmetric values: (A^T P)_jK = sum over i in row j of a_ij P_iK.
+// with nonsymmetric values: (A^T P)_jK = sum over i in row j of a_ij P_iK.  Where there is no
+// product map: kDtLanes lanes per row, one entry each at a time, walk the same
+// rows of P together, so every load serves all of them (level 1 of a 128^3
+// convection-diffusion system: a thread per row 4.4 ms, so 1.4 ms, the map's
+// two kernels 0.54 ms).
+constexpr int kDtLanes = 16;
 template <class RT, class T>
 __global__ void k_dt_values(int n, const int* __restrict__ rp, const int* __restrict__ ci, const T* __restrict__ av,
                             const int* __restrict__ tpos, const int* __restrict__ prp, const int* __restrict__ pci,
                             const RT* __restrict__ pv, const int* __restrict__ aprp, const int* __restrict__ apci,
                             const T* __restrict__ sw, double* __restrict__ dt) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
+  const int j = t0 / kDtLanes;
   if (j >= n) return;
   const double w = (double)sw[j];
-  for (int e = aprp[j]; e < aprp[j + 1]; ++e) {
+  for (int e = aprp[j] + t0 % kDtLanes; e < aprp[j + 1]; e += kDtLanes) {
     const int K = apci[e];
     double acc = 0.0, own = 0.0;
     for (int k = rp[j]; k < rp[j + 1]; ++k) {
@@ -583,8 +611,8 @@ void level_values(Hierarchy& H, Level& L, const RT* pv, hipStream_t s) {
   const dim3 b(kBlock);
   if constexpr (std::is_same<T, float>::value) {
     if (L.pmaps)
-      hipLaunchKernelGGL(k_ap_map<RT>, dim3(blocks(L.apnnz)), b, 0, s, L.apnnz, L.apmo.p, L.apm.p, L.v32.p, pv,
-                         L.apt.p);
+      hipLaunchKernelGGL((k_ap_map<RT, T>), dim3(blocks(L.apnnz)), b, 0, s, L.apnnz, L.apmo.p, L.apm.p, L.v32.p,
+                         (const int*)nullptr, pv, L.apt.p);
     else
       hipLaunchKernelGGL(k_ap_search<RT>, dim3(blocks(L.n)), b, 0, s, L.n, L.rp.p, L.ci.p, L.v32.p, L.prp.p, L.pci.p,
                          pv, L.aprp.p, L.apci.p, L.apt.p);
@@ -592,9 +620,14 @@ void level_values(Hierarchy& H, Level& L, const RT* pv, hipStream_t s) {
   }
   hipLaunchKernelGGL((k_q_values<RT, T>), dim3(blocks(L.n)), b, 0, s, L.n, L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p,
                      ap, level_sw<T>(L), L.qv.p);
-  if (L.dtv.p)
-    hipLaunchKernelGGL((k_dt_values<RT, T>), dim3(blocks(L.n)), b, 0, s, L.n, L.rp.p, L.ci.p, level_a<T>(L), L.tpos.p,
-                       L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p, level_sw<T>(L), L.dtv.p);
+  if (L.dtv.p && L.pmaps) {
+    hipLaunchKernelGGL((k_ap_map<RT, T>), dim3(blocks(L.apnnz)), b, 0, s, L.apnnz, L.apmo.p, L.apm.p, level_a<T>(L),
+                       L.tpos.p, pv, L.dtv.p);
+    hipLaunchKernelGGL((k_q_values<RT, T>), dim3(blocks(L.n)), b, 0, s, L.n, L.prp.p, L.pci.p, pv, L.aprp.p,
+                       L.apci.p, L.dtv.p, level_sw<T>(L), L.dtv.p);
+  } else if (L.dtv.p)
+    hipLaunchKernelGGL((k_dt_values<RT, T>), dim3(blocks((int64_t)L.n * kDtLanes)), b, 0, s, L.n, L.rp.p, L.ci.p, level_a<T>(L),
+                       L.tpos.p, L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p, level_sw<T>(L), L.dtv.p);
   hipLaunchKernelGGL((k_ell_values<true, T>), dim3(blocks(L.up.slices, kBlock / 64)), b, 0, s, L.n, L.up.slices,
                      L.up.g, L.up.off.p, L.up.col.p, L.up.src.p, level_a<T>(L), level_sw<T>(L), L.qv.p,
                      ell_v<T>(L.up));

@@ -84,3 +84,28 @@ def test_two_sweep_cycle_nonsymmetric(drop):
     zo = O.vcycle(b)
     z = host(H.apply_vcycle(dev(b)))
     assert np.linalg.norm(z - zo) <= 1e-12 * np.linalg.norm(zo)
+
+
+def test_two_sweep_cycle_nonsymmetric_without_product_map():
+    # six random neighbours per row: a product map of R (A P) would exceed 16
+    # pairs per entry of A, so D's values come from the search through P's rows
+    n, rng = 1500, np.random.default_rng(11)
+    i, j = rng.integers(0, n, 3 * n), rng.integers(0, n, 3 * n)
+    D = np.zeros((n, n))
+    D[i, j] = -rng.uniform(0.2, 1.0, 3 * n)
+    D[j, i] = -rng.uniform(0.2, 1.0, 3 * n)
+    np.fill_diagonal(D, 0.0)
+    np.fill_diagonal(D, 1.0 + np.abs(D).sum(axis=1))
+    rows, cols = np.nonzero(D)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int32)
+    ci, v = cols.astype(np.int32), D[rows, cols]
+    b = M.rhs_normal(n, 8)
+    H, O = pair(rp, ci, v, symmetric=False, solver="bicgstab", max_coarse=12)
+    L = O.level(0)
+    P = np.zeros((n, O.level_sizes(0)["nagg"]))
+    P[np.repeat(np.arange(n), np.diff(L["P_rp"])), L["P_ci"]] = 1.0
+    ap_rows = ((D != 0).astype(float) @ P != 0).sum(axis=1)
+    assert P.sum(axis=1) @ ap_rows > 16 * len(v)
+    zo = O.vcycle(b)
+    z = host(H.apply_vcycle(dev(b)))
+    assert np.linalg.norm(z - zo) <= 1e-12 * np.linalg.norm(zo)
