@@ -55,12 +55,16 @@ def kernel_source(table=None):
     return "solve.hip"
 
 
+def kernel_files(source):
+    return ([source, "fused.hip"] if source == "solve.hip" else [source]) + ["amg_internal.hpp"]
+
+
 def kernel_source_hash(source="solve.hip"):
     """sha256 of the sources that define the profiled kernels (the
-    single-system sweeps in solve.hip, the batched ones in batch.hip, the
-    one-workgroup solve in small.hip), with the shared header."""
+    single-system sweeps in solve.hip and fused.hip, the batched ones in
+    batch.hip, the one-workgroup solve in small.hip), with the shared header."""
     h = hashlib.sha256()
-    for name in (source, "amg_internal.hpp"):
+    for name in kernel_files(source):
         with open(os.path.join(ROOT, "paper_2606_09001_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
@@ -81,10 +85,8 @@ FINE_KERNELS = {  # tag -> (regex on the demangled name, grid rank: 0 = largest 
     "post_L0": (_SWEEP + r"OpPost<double, double, double, 1> >", 0),
     "restrict_L0": (_SWEEP + r"OpRestrict<double, double> >", 0),
     "prolong_L0": (_SWEEP + r"OpProlong<double, double> >", 0),
-    "pre_L1": (_SWEEP + r"OpResid<double, double> >", 1),
-    "post_L1": (_SWEEP + r"OpPost<double, double, double, 0> >", 0),
-    "restrict_L1": (_SWEEP + r"OpRestrict<double, double> >", 1),
-    "prolong_L1": (_SWEEP + r"OpProlong<double, double> >", 1),
+    "down_L1": (r"k_ell<\d+, [^>]*OpDown<double> >", 0),   # two-sweep levels (fused.hip): level 1 first
+    "up_L1": (r"k_ell<\d+, [^>]*OpUp<double, double, 0> >", 0),
 }
 _WIDE = r"k_wide(?:_st)?<\d+, [^>]*"
 # level-0 sweeps of the batched solves (FP64 cycle): rhs_* the right-hand
@@ -240,7 +242,7 @@ def summarize_profiles(a):
                        "write_kib_per_dispatch": write[k]["kib"], "fetch_factor": ff, "write_factor": wf,
                        "traffic_bytes_per_launch": round(traffic), "commands": [a.cmd_fetch, a.cmd_write],
                        "working_avg_us_from_trace": summary.get(k, {}).get("avg_us")}, f, indent=1)
-    txt.append(f"\nkernel source sha256 ({source} + amg_internal.hpp): {src}")
+    txt.append(f"\nkernel source sha256 ({' + '.join(kernel_files(source))}): {src}")
     with open(os.path.join(out_dir, f"{tag}_pmc.txt"), "w") as f:
         f.write("\n".join(txt) + "\n")
     print("\n".join(txt))
