@@ -302,7 +302,8 @@ struct Ctl {
   double rz2[2];          // CG: <r,z> by direction-buffer parity
   int it2[2];             // CG: iterations by direction-buffer parity
   int iters, maxiter;
-  int done;               // nonzero: kernels of the current solve return at once
+  int done;               // nonzero: the solve has ended
+  int gate[2];            // the same, as the kernels between two of its writers read it (see Fold in solve.hip)
   int state;              // 0 running, 1 converged (recursive), 2 iteration limit, -1 breakdown
   int flexible;
   int restarts;           // true-residual restarts (single-workgroup solve)
@@ -503,7 +504,7 @@ void fused_levels(Hierarchy& H, bool build, hipStream_t s);
 // <z, q> partials of `red`; null otherwise: the level's x buffer).  Returns
 // the partials written per reduced value.
 template <class T>
-int fused_cycle(Hierarchy& H, const T* b, const double* r, double* z, const double* q, int red, const Ctl* ctl,
+int fused_cycle(Hierarchy& H, const T* b, const double* r, double* z, const double* q, int red, const int* stop,
                 double* partials, hipStream_t s);
 double fused_bytes(const Hierarchy& H, int kid, int level);
 // small.hip
@@ -523,13 +524,12 @@ void set_instrument(Hierarchy& H, int kid, int level);
 void read_instrument(Hierarchy& H, int* launches, double* total_ms, double* min_ms, double* max_ms);
 
 // Records an event pair around a launch when (kernel, level) is instrumented,
-// and, before the pair, the solve's done flag: a launch that starts with the
-// flag set returns at once and is left out of the statistics.
+// and, before the pair, the flag the launch tests: one that starts with it set returns at once and is left out of the statistics.
 struct InstScope {
   Hierarchy& H;
   hipStream_t s;
   bool on;
-  InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const Ctl* ctl);
+  InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const int* stop);
   ~InstScope();
 };
 

@@ -97,14 +97,14 @@ struct OpUp {
 
 template <int G, class Op>
 __global__ void __launch_bounds__(kBlock) k_ell(int n, int slices, const int* __restrict__ off,
-                                                const int* __restrict__ col, Op op, const Ctl* __restrict__ ctl,
+                                                const int* __restrict__ col, Op op, const int* __restrict__ stop,
                                                 double* __restrict__ partials) {
   using T = typename Op::PT;
   const int lane = threadIdx.x & 63;
   const int sl = __builtin_amdgcn_readfirstlane(block_of_xcd() * (kBlock / 64) + (int)(threadIdx.x >> 6));
   const int sc = min(sl, slices - 1);
   const int o0 = off[sc], o1 = off[sc + 1];
-  const int done = ctl ? ctl->done : 0;
+  const int done = stop ? *stop : 0;
   if (done) return;
   const int w = sl < slices ? (o1 - o0) >> 6 : 0;
   const int row = sl * (64 / G) + lane / G;
@@ -140,14 +140,14 @@ __global__ void __launch_bounds__(kBlock) k_ell(int n, int slices, const int* __
 }
 
 template <class Op>
-int ell_sweep(const Ell& E, const Op& op, const Ctl* ctl, double* partials, hipStream_t s) {
+int ell_sweep(const Ell& E, const Op& op, const int* stop, double* partials, hipStream_t s) {
 #define AMG_ELL_G(GG) \
   case GG: hipLaunchKernelGGL((k_ell<GG, Op>), dim3(E.grid), dim3(kBlock), 0, s, E.n, E.slices, E.off.p, E.col.p, op, \
-                              ctl, partials); break;
+                              stop, partials); break;
   switch (E.g) {
     AMG_ELL_G(1) AMG_ELL_G(2) AMG_ELL_G(4) AMG_ELL_G(8) AMG_ELL_G(16) AMG_ELL_G(32)
     default: hipLaunchKernelGGL((k_ell<64, Op>), dim3(E.grid), dim3(kBlock), 0, s, E.n, E.slices, E.off.p, E.col.p, op,
-                                ctl, partials);
+                                stop, partials);
   }
 #undef AMG_ELL_G
   return E.grid;
@@ -158,10 +158,10 @@ int ell_sweep(const Ell& E, const Op& op, const Ctl* ctl, double* partials, hipS
 template <int WPR, class T>
 __global__ void __launch_bounds__(kBlock) k_dense(int rows, int cols, int ld, const T* __restrict__ X,
                                                   const T* __restrict__ b, T* __restrict__ x,
-                                                  const Ctl* __restrict__ ctl) {
+                                                  const int* __restrict__ stop) {
   __shared__ T s_w[kBlock / 64];
   constexpr int L = 64 * WPR, U = 8;
-  const int done = ctl ? ctl->done : 0;
+  const int done = stop ? *stop : 0;
   const int wave = threadIdx.x >> 6;
   const int row = WPR == 1 ? blockIdx.x * (kBlock / 64) + wave : blockIdx.x;
   const int t = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
@@ -748,50 +748,50 @@ void fused_levels(Hierarchy& H, bool build, hipStream_t s) {
 }
 
 template <class T>
-int fused_cycle(Hierarchy& H, const T* b0, const double* r, double* z, const double* q, int red, const Ctl* ctl,
+int fused_cycle(Hierarchy& H, const T* b0, const double* r, double* z, const double* q, int red, const int* stop,
                 double* partials, hipStream_t s) {
   const Tail& t = H.tail;
   const int lf = H.lf, nl = (int)H.lv.size();
   auto rhs = [&](int l) { return l == lf && b0 ? b0 : (const T*)level_b<T>(H.lv[l]); };
   for (int l = lf; l < t.lb; ++l) {
     Level& L = H.lv[l];
-    InstScope is(H, KID_RESTRICT, l, s, ctl);
-    ell_sweep(L.dn, OpDown<T>{ell_v<T>(L.dn), rhs(l), level_b<T>(H.lv[l + 1])}, ctl, nullptr, s);
+    InstScope is(H, KID_RESTRICT, l, s, stop);
+    ell_sweep(L.dn, OpDown<T>{ell_v<T>(L.dn), rhs(l), level_b<T>(H.lv[l + 1])}, stop, nullptr, s);
   }
   {
-    InstScope is(H, KID_COARSE, nl - 1, s, ctl);
+    InstScope is(H, KID_COARSE, nl - 1, s, stop);
     T* x = level_x<T>(H.lv[t.lx]);
     // long rows take a workgroup each
     if (t.cols > 1024)
       hipLaunchKernelGGL((k_dense<4, T>), dim3(t.rows), dim3(kBlock), 0, s, t.rows, t.cols, t.ld, tail_x<T>(t),
-                         rhs(t.lb), x, ctl);
+                         rhs(t.lb), x, stop);
     else
       hipLaunchKernelGGL((k_dense<1, T>), dim3(blocks(t.rows, kBlock / 64)), dim3(kBlock), 0, s, t.rows, t.cols, t.ld,
-                         tail_x<T>(t), rhs(t.lb), x, ctl);
+                         tail_x<T>(t), rhs(t.lb), x, stop);
   }
   int np = 0;
   for (int l = t.lx - 1; l >= lf; --l) {
     Level& L = H.lv[l];
-    InstScope is(H, KID_POST, l, s, ctl);
+    InstScope is(H, KID_POST, l, s, stop);
     const T* v = ell_v<T>(L.up);
     const T* b = rhs(l);
     const T* e = level_x<T>(H.lv[l + 1]);
     if (l > 0)
-      ell_sweep(L.up, OpUp<T, T, 0>{v, b, e, level_x<T>(L), L.n, nullptr, nullptr}, ctl, nullptr, s);
+      ell_sweep(L.up, OpUp<T, T, 0>{v, b, e, level_x<T>(L), L.n, nullptr, nullptr}, stop, nullptr, s);
     else if (red == 2)
-      np = ell_sweep(L.up, OpUp<T, double, 2>{v, b, e, z, L.n, r, q}, ctl, partials, s);
+      np = ell_sweep(L.up, OpUp<T, double, 2>{v, b, e, z, L.n, r, q}, stop, partials, s);
     else if (red == 1)
-      np = ell_sweep(L.up, OpUp<T, double, 1>{v, b, e, z, L.n, r, q}, ctl, partials, s);
+      np = ell_sweep(L.up, OpUp<T, double, 1>{v, b, e, z, L.n, r, q}, stop, partials, s);
     else
-      ell_sweep(L.up, OpUp<T, double, 0>{v, b, e, z, L.n, r, q}, ctl, nullptr, s);
+      ell_sweep(L.up, OpUp<T, double, 0>{v, b, e, z, L.n, r, q}, stop, nullptr, s);
   }
   AMG_HIP(hipGetLastError());
   return np;
 }
 
-template int fused_cycle<double>(Hierarchy&, const double*, const double*, double*, const double*, int, const Ctl*,
+template int fused_cycle<double>(Hierarchy&, const double*, const double*, double*, const double*, int, const int*,
                                  double*, hipStream_t);
-template int fused_cycle<float>(Hierarchy&, const float*, const double*, double*, const double*, int, const Ctl*,
+template int fused_cycle<float>(Hierarchy&, const float*, const double*, double*, const double*, int, const int*,
                                 double*, hipStream_t);
 
 // Algorithmic bytes of a launch on a two-sweep level (stored entries and

@@ -130,9 +130,17 @@ __device__ inline void fold_total(double (&v)[NV], bool tot) {
 // place by the row's own thread).  p' goes to the second direction buffer.
 // beta, the convergence test of the last update and the <r, z> test come from
 // the partials of that update (pu) and of the V-cycle (pz).  Workgroup 0
-// records the outcome; what other workgroups read of the control block
-// (rz2[par], it2[par], pq) is not written in this kernel, and a workgroup that
-// sees `done` set by workgroup 0 would have found the same outcome itself.
+// records the outcome.
+//
+// No kernel writes a field of the control block that it reads.  This holds for
+// the stop flag too: the waves of a workgroup read it one by one, and one that
+// left on a flag set meanwhile would leave the others waiting for LDS contents
+// it never wrote (row pointers, partial sums).  So a kernel that ends the solve
+// tests one flag and writes the next, and passes on what it found set:
+//   CG        product  done -> gate[0],  update  gate[0] -> done
+//   BiCGSTAB  direction  done -> gate[0],  half step  gate[0] -> gate[1],
+//             full step  gate[1] -> done
+// and the kernels in between test the flag that was written last.
 struct OpSpmvXpay {
   using PT = double;
   static constexpr int NRED = 1;
@@ -188,10 +196,14 @@ struct OpSpmvXpay {
       if (st) {
         ctl->iters = it;
         ctl->state = st;
-        ctl->done = 1;
       }
+      ctl->gate[0] = st != 0;
     }
     return st == 0;
+  }
+  // the sweep found the solve ended
+  __device__ void ended() const {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->gate[0] = 1;
   }
   __device__ void epi_fold(int row, PT s, const Row& a, double beta, double* d) const {
     const double pr = first ? a.z : a.z + beta * a.p;
@@ -208,7 +220,8 @@ template <class Op>
 struct HasFold<Op, std::void_t<typename Op::Fold>> : std::true_type {};
 
 // The folding hooks of a sweep: fold_in before its own loads, fold_out and the
-// row epilogue after its row sums (nothing for operators that do not fold).
+// row epilogue after its row sums (nothing for operators that do not fold),
+// and sweep_ended, the test of its stop flag.
 template <class Op>
 __device__ inline auto fold_in(const Op& op) {
   if constexpr (HasFold<Op>::value) return op.fold_in();
@@ -218,6 +231,12 @@ template <class Op, class F>
 __device__ inline bool fold_out(const Op& op, F& f, double& beta) {
   if constexpr (HasFold<Op>::value) return op.fold_out(f, beta);
   else return true;
+}
+template <class Op>
+__device__ inline bool sweep_ended(const Op& op, const int* __restrict__ stop) {
+  if (!stop || !*stop) return false;
+  if constexpr (HasFold<Op>::value) op.ended();
+  return true;
 }
 template <class Op>
 __device__ inline void row_epi(const Op& op, int row, typename Op::PT s, const typename Op::Row& in, double beta,
@@ -428,9 +447,9 @@ __device__ inline void publish_partials(double (&d)[NRED > 0 ? NRED : 1], double
 // of the unconditional loads are clamped duplicates).
 template <int G3, int U, bool NT, class Op>
 __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict__ rp,
-                                                   const int* __restrict__ ci, Op op, const Ctl* __restrict__ ctl,
+                                                   const int* __restrict__ ci, Op op, const int* __restrict__ stop,
                                                    double* __restrict__ partials) {
-  if ((ctl && ctl->done) || n <= 0) return;
+  if (n <= 0 || sweep_ended(op, stop)) return;
   constexpr int RB = kBlock / G3;
   using PT = typename Op::PT;
   __shared__ int s_rp[RB + 1];
@@ -475,8 +494,8 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
 
 template <int G, class Op>
 __global__ void __launch_bounds__(kBlock) k_vec(int n, const int* __restrict__ rp, const int* __restrict__ ci, Op op,
-                                                const Ctl* __restrict__ ctl, double* __restrict__ partials) {
-  if ((ctl && ctl->done) || n <= 0) return;
+                                                const int* __restrict__ stop, double* __restrict__ partials) {
+  if (n <= 0 || sweep_ended(op, stop)) return;
   using PT = typename Op::PT;
   constexpr int RB = kBlock / G;
   const int lr = threadIdx.x / G, lane = threadIdx.x & (G - 1);
@@ -516,7 +535,7 @@ __global__ void __launch_bounds__(kBlock) k_vec(int n, const int* __restrict__ r
 // in stored order (the same fold as a one-lane CSR sweep).
 template <bool NT, class Op>
 __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ soff,
-                                                 const int* __restrict__ sci, Op op, const Ctl* __restrict__ ctl,
+                                                 const int* __restrict__ sci, Op op, const int* __restrict__ stop,
                                                  double* __restrict__ partials) {
   if (n <= 0) return;
   using PT = typename Op::PT;
@@ -529,7 +548,7 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
   const int sl = __builtin_amdgcn_readfirstlane(rc >> 6), lane = rc & 63;
   const int off = soff[sl];
   const int w = (soff[sl + 1] - off) >> 6;
-  if (ctl && ctl->done) return;
+  if (sweep_ended(op, stop)) return;
   auto fold = fold_in(op);
   const typename Op::Row in = op.row_in(rc);
   int col[kSellMaxW];
@@ -567,7 +586,7 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, const int* __restrict__ 
 // 192^3 product and left it at 107 us.)
 template <bool NT, bool UNI, int W, class Op>
 __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__ soff,
-                                                  const int4* __restrict__ slots, Op op, const Ctl* __restrict__ ctl,
+                                                  const int4* __restrict__ slots, Op op, const int* __restrict__ stop,
                                                   double* __restrict__ partials) {
   if (n <= 0) return;
   using PT = typename Op::PT;
@@ -578,7 +597,7 @@ __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__
   const int off = soff[sl];
   const int w = (soff[sl + 1] - off) >> 6;
   const int sb = off >> 6;
-  if (ctl && ctl->done) return;
+  if (sweep_ended(op, stop)) return;
   auto fold = fold_in(op);
   const typename Op::Row in = op.row_in(rc);
   typename std::remove_const<typename std::remove_pointer<decltype(op.v)>::type>::type val[W];
@@ -621,16 +640,16 @@ __global__ void __launch_bounds__(kBlock) k_sello(int n, const int* __restrict__
   }
 
 template <bool NT, class Op>
-void sweep_form(const Shape& sh, int n, const int* rp, const int* ci, const Op& op, const Ctl* ctl,
+void sweep_form(const Shape& sh, int n, const int* rp, const int* ci, const Op& op, const int* stop,
                 double* partials, hipStream_t s) {
   if (sh.stream >= 3) {
     const int4* slots = reinterpret_cast<const int4*>(ci);
 #define AMG_SELLO(W)                                                                                              \
   if (sh.stream == 4)                                                                                             \
-    hipLaunchKernelGGL((k_sello<false, true, W, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, slots, op, ctl,   \
+    hipLaunchKernelGGL((k_sello<false, true, W, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, slots, op, stop,   \
                        partials);                                                                                 \
   else                                                                                                            \
-    hipLaunchKernelGGL((k_sello<NT, false, W, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, slots, op, ctl,     \
+    hipLaunchKernelGGL((k_sello<NT, false, W, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, slots, op, stop,     \
                        partials);
     if (sh.w <= 3) {
       AMG_SELLO(3)
@@ -643,24 +662,24 @@ void sweep_form(const Shape& sh, int n, const int* rp, const int* ci, const Op& 
     }
 #undef AMG_SELLO
   } else if (sh.stream == 2) {
-    hipLaunchKernelGGL((k_sell<NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, ci, op, ctl, partials);
+    hipLaunchKernelGGL((k_sell<NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, ci, op, stop, partials);
   } else if (sh.stream) {
     switch (sh.u) {
       case 4:
         AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 4, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n,
-                                                rp, ci, op, ctl, partials));
+                                                rp, ci, op, stop, partials));
         break;
       case 8:
         AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 8, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n,
-                                                rp, ci, op, ctl, partials));
+                                                rp, ci, op, stop, partials));
         break;
       default:
         AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_stream<G, 12, NT, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n,
-                                                rp, ci, op, ctl, partials));
+                                                rp, ci, op, stop, partials));
         break;
     }
   } else {
-    AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_vec<G, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, ci, op, ctl,
+    AMG_DISPATCH_G(sh.g, hipLaunchKernelGGL((k_vec<G, Op>), dim3(sh.grid), dim3(kBlock), 0, s, n, rp, ci, op, stop,
                                             partials));
   }
 }
@@ -668,10 +687,10 @@ void sweep_form(const Shape& sh, int n, const int* rp, const int* ci, const Op& 
 // One sweep over a CSR matrix with operator `op`; returns the grid size
 // (= number of partials written per reduced value).
 template <class Op>
-int sweep(const Shape& sh, int n, const int* rp, const int* ci, const Op& op, const Ctl* ctl, double* partials,
+int sweep(const Shape& sh, int n, const int* rp, const int* ci, const Op& op, const int* stop, double* partials,
           hipStream_t s) {
-  if (sh.nt) sweep_form<true>(sh, n, rp, ci, op, ctl, partials, s);
-  else sweep_form<false>(sh, n, rp, ci, op, ctl, partials, s);
+  if (sh.nt) sweep_form<true>(sh, n, rp, ci, op, stop, partials, s);
+  else sweep_form<false>(sh, n, rp, ci, op, stop, partials, s);
   return sh.grid;
 }
 
@@ -681,8 +700,8 @@ int sweep(const Shape& sh, int n, const int* rp, const int* ci, const Op& op, co
 // column i = row i, coalesced across threads.
 template <class T, class BT, class OT>
 __global__ void __launch_bounds__(kBlock) k_coarse(int n, int m, const T* __restrict__ inv, const BT* __restrict__ b,
-                                                   OT* __restrict__ x, const Ctl* __restrict__ ctl) {
-  if (ctl && ctl->done) return;
+                                                   OT* __restrict__ x, const int* __restrict__ stop) {
+  if (stop && *stop) return;
   __shared__ T sb[kBlock];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   T s = 0;
@@ -742,18 +761,22 @@ X0Mode x0_mode(const Hierarchy& H) {
 
 // x += alpha p ; r -= alpha q ; partials <r, r> (pu); and x0 (see X0Mode).
 // alpha from the product sweep's partials (pa) and the <r, z> of parity
-// par ^ 1 that it recorded.  Workgroup 0 records <p, q> and a breakdown.
+// par ^ 1 that it recorded.  Workgroup 0 records <p, q> and the end of the
+// solve (found by the product, or a breakdown here).
 template <int MODE, class T>
 __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict__ r,
                                                       const double* __restrict__ p, const double* __restrict__ q,
                                                       const T* __restrict__ sw, T* __restrict__ x0, Ctl* ctl,
                                                       const double* __restrict__ pa, int npa, int tot,
                                                       double* __restrict__ pu, int par) {
-  const int done = ctl->done;
+  const int ended = ctl->gate[0];
   const double rz = ctl->rz2[par ^ 1];
   const int iters = ctl->it2[par ^ 1];
   double* __restrict__ x = ctl->x;
-  if (done) return;
+  if (ended) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->done = 1;
+    return;
+  }
   double f[1] = {fold_load(pa, npa, tot)};
   double alpha = 0.0, d[1] = {0.0};
   const int base = vec_base();
@@ -798,8 +821,8 @@ __global__ void __launch_bounds__(kBlock) k_cg_update(int n, double* __restrict_
 
 // z = r (the identity preconditioner of plain CG).
 __global__ void __launch_bounds__(kBlock) k_copy_z(int n, const double* __restrict__ r, double* __restrict__ z,
-                                                   const Ctl* __restrict__ ctl) {
-  if (ctl && ctl->done) return;
+                                                   const int* __restrict__ stop) {
+  if (stop && *stop) return;
   const int base = vec_base();
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
@@ -812,8 +835,8 @@ __global__ void __launch_bounds__(kBlock) k_copy_z(int n, const double* __restri
 // solve or restart).
 template <class T>
 __global__ void __launch_bounds__(kBlock) k_sw_mul(int n, const T* __restrict__ sw, const double* __restrict__ r,
-                                                   T* __restrict__ x0, const Ctl* __restrict__ ctl) {
-  if (ctl && ctl->done) return;
+                                                   T* __restrict__ x0, const int* __restrict__ stop) {
+  if (stop && *stop) return;
   const int base = vec_base();
 #pragma unroll
   for (int u = 0; u < kVecPer; ++u) {
@@ -825,8 +848,8 @@ __global__ void __launch_bounds__(kBlock) k_sw_mul(int n, const T* __restrict__ 
 // <r, z> and <z, q> partials after a single-level (direct) preconditioner.
 __global__ void __launch_bounds__(kBlock) k_dots_rz(int n, const double* __restrict__ r,
                                                     const double* __restrict__ z, const double* __restrict__ q,
-                                                    const Ctl* __restrict__ ctl, double* __restrict__ partials) {
-  if (ctl->done) return;
+                                                    const int* __restrict__ stop, double* __restrict__ partials) {
+  if (stop && *stop) return;
   double d[2] = {0.0, 0.0};
   const int base = vec_base();
 #pragma unroll
@@ -888,7 +911,10 @@ __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restri
                                                    const double* __restrict__ pf, int npf, int tot) {
   const int done = ctl->done, iters = ctl->iters, maxiter = ctl->maxiter;
   const double rho0 = ctl->rho, alpha = ctl->alpha, omega = ctl->omega, thresh = ctl->thresh;
-  if (done) return;
+  if (done) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->gate[0] = 1;
+    return;
+  }
   double f[2] = {first ? 0.0 : fold_load(pf, npf, tot), first ? 0.0 : fold_load(pf + npf, npf, tot)};
   double beta = 0.0;
   const int base = vec_base();
@@ -915,10 +941,8 @@ __global__ void __launch_bounds__(kBlock) k_bi_dir(int n, const double* __restri
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->rz = rho;
     if (!first) ctl->rr = rr;
-    if (st) {
-      ctl->state = st;
-      ctl->done = 1;
-    }
+    if (st) ctl->state = st;
+    ctl->gate[0] = st != 0;
   }
   if (st) return;
 #pragma unroll
@@ -940,10 +964,13 @@ __global__ void __launch_bounds__(kBlock) k_bi_half(int n, const double* __restr
                                                     double* __restrict__ sv, const T* __restrict__ sw,
                                                     T* __restrict__ x0, Ctl* ctl, const double* __restrict__ pa,
                                                     int npa, int tot, double* __restrict__ ps) {
-  const int done = ctl->done;
+  const int ended = ctl->gate[0];
   const double rho = ctl->rz;
   double* __restrict__ x = ctl->x;
-  if (done) return;
+  if (ended) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->gate[1] = 1;
+    return;
+  }
   double f[1] = {fold_load(pa, npa, tot)};
   double alpha = 0.0, d[1] = {0.0};
   const int base = vec_base();
@@ -963,12 +990,9 @@ __global__ void __launch_bounds__(kBlock) k_bi_half(int n, const double* __restr
   alpha = rho / f[0];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->rho = rho;
-    if (ok) {
-      ctl->alpha = alpha;
-    } else {
-      ctl->state = -1;
-      ctl->done = 1;
-    }
+    if (ok) ctl->alpha = alpha;
+    else ctl->state = -1;
+    ctl->gate[1] = !ok;
   }
   if (!ok) return;
 #pragma unroll
@@ -993,10 +1017,13 @@ __global__ void __launch_bounds__(kBlock) k_bi_full(int n, const double* __restr
                                                     const double* __restrict__ rh, double* __restrict__ r, Ctl* ctl,
                                                     const double* __restrict__ ps, int nps,
                                                     const double* __restrict__ pt, int npt, int tot, double* __restrict__ pf) {
-  const int done = ctl->done;
+  const int ended = ctl->gate[1];
   const double thresh = ctl->thresh;
   double* __restrict__ x = ctl->x;
-  if (done) return;
+  if (ended) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->done = 1;
+    return;
+  }
   double f[3] = {fold_load(ps, nps, tot), fold_load(pt, npt, tot), fold_load(pt + npt, npt, tot)};
   double omega = 0.0, d[2] = {0.0, 0.0};
   const int base = vec_base();
@@ -1087,8 +1114,8 @@ struct SumArgs {
   const double* src[4];
   int np[4];
 };
-__global__ void __launch_bounds__(kFinBlock) k_sum(SumArgs a, double* __restrict__ out, const Ctl* __restrict__ ctl) {
-  if (ctl->done) return;
+__global__ void __launch_bounds__(kFinBlock) k_sum(SumArgs a, double* __restrict__ out, const int* __restrict__ stop) {
+  if (*stop) return;
   double t[1];
   fold_partials<1>(a.src[blockIdx.x], a.np[blockIdx.x], t);
   if (threadIdx.x == 0) out[blockIdx.x] = t[0];
@@ -1212,16 +1239,16 @@ __global__ void k_ctl_restart(Ctl* ctl) {
 
 // ------------------------------------------------------------ V-cycle
 
-// Copies the done flag (0 when there is none) into the instrument record.
-__global__ void k_snap_done(const Ctl* ctl, int* dst) {
-  if (threadIdx.x == 0) dst[0] = ctl ? ctl->done : 0;
+// Copies the stop flag (0 when there is none) into the instrument record.
+__global__ void k_snap_done(const int* stop, int* dst) {
+  if (threadIdx.x == 0) dst[0] = stop ? *stop : 0;
 }
 
 struct CycleArgs {
   const double* r0;   // level-0 right-hand side (CG residual), FP64
   double* z0;         // level-0 result, FP64
   const double* q;    // CG q (flexible reduction), may be null
-  Ctl* ctl;           // null: no early exit, no reductions
+  const int* stop;    // flag to return on (null: none, and no reductions)
   double* partials;
   int red;            // 0 none, 1 <r,z>, 2 <r,z> and <z,q>
   int x0_ready;       // what the cycle starts from (X0Mode) already written
@@ -1254,24 +1281,24 @@ struct Bufs<float> {
 };
 
 template <class T>
-void launch_restrict(Hierarchy& H, Level& L, const T* r, T* bc, const T* swc, T* xc, const Ctl* ctl, hipStream_t s) {
+void launch_restrict(Hierarchy& H, Level& L, const T* r, T* bc, const T* swc, T* xc, const int* stop, hipStream_t s) {
   if constexpr (std::is_same<T, double>::value) {
-    sweep(L.shR, L.nagg, L.rrp.p, L.rci.p, OpRestrict<double, T>{L.rv.p, r, bc, swc, xc}, ctl, nullptr, s);
+    sweep(L.shR, L.nagg, L.rrp.p, L.rci.p, OpRestrict<double, T>{L.rv.p, r, bc, swc, xc}, stop, nullptr, s);
   } else if (H.bf16()) {
-    sweep(L.shR, L.nagg, L.rrp.p, L.rci.p, OpRestrict<uint16_t, T>{L.rbf.p, r, bc, swc, xc}, ctl, nullptr, s);
+    sweep(L.shR, L.nagg, L.rrp.p, L.rci.p, OpRestrict<uint16_t, T>{L.rbf.p, r, bc, swc, xc}, stop, nullptr, s);
   } else {
-    sweep(L.shR, L.nagg, L.rrp.p, L.rci.p, OpRestrict<float, T>{L.rv32.p, r, bc, swc, xc}, ctl, nullptr, s);
+    sweep(L.shR, L.nagg, L.rrp.p, L.rci.p, OpRestrict<float, T>{L.rv32.p, r, bc, swc, xc}, stop, nullptr, s);
   }
 }
 
 template <class T>
-void launch_prolong(Hierarchy& H, Level& L, const T* xc, T* x, const Ctl* ctl, hipStream_t s) {
+void launch_prolong(Hierarchy& H, Level& L, const T* xc, T* x, const int* stop, hipStream_t s) {
   if constexpr (std::is_same<T, double>::value) {
-    sweep(L.shP, L.n, L.prp.p, L.pci.p, OpProlong<double, T>{L.pv.p, xc, x}, ctl, nullptr, s);
+    sweep(L.shP, L.n, L.prp.p, L.pci.p, OpProlong<double, T>{L.pv.p, xc, x}, stop, nullptr, s);
   } else if (H.bf16()) {
-    sweep(L.shP, L.n, L.prp.p, L.pci.p, OpProlong<uint16_t, T>{L.pbf.p, xc, x}, ctl, nullptr, s);
+    sweep(L.shP, L.n, L.prp.p, L.pci.p, OpProlong<uint16_t, T>{L.pbf.p, xc, x}, stop, nullptr, s);
   } else {
-    sweep(L.shP, L.n, L.prp.p, L.pci.p, OpProlong<float, T>{L.pv32.p, xc, x}, ctl, nullptr, s);
+    sweep(L.shP, L.n, L.prp.p, L.pci.p, OpProlong<float, T>{L.pv32.p, xc, x}, stop, nullptr, s);
   }
 }
 
@@ -1283,14 +1310,14 @@ template <class T>
 int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
   const int nl = (int)H.lv.size();
   Coarse& C = H.co;
-  Ctl* ctl = a.ctl;
+  const int* stop = a.stop;
   if (!H.prm.precondition) {
     // plain CG: z = r
     const int n = H.n;
-    hipLaunchKernelGGL(k_copy_z, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, a.r0, a.z0, ctl);
+    hipLaunchKernelGGL(k_copy_z, dim3(vec_grid(n)), dim3(kBlock), 0, s, n, a.r0, a.z0, stop);
     if (a.red) {
       const int g = vec_grid(n);
-      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, n, a.r0, a.z0, a.q ? a.q : a.z0, ctl,
+      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, n, a.r0, a.z0, a.q ? a.q : a.z0, stop,
                          a.partials);
       return g;
     }
@@ -1298,13 +1325,13 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
   }
   if (nl == 1) {
     {
-      InstScope is(H, KID_COARSE, 0, s, a.ctl);
+      InstScope is(H, KID_COARSE, 0, s, stop);
       hipLaunchKernelGGL((k_coarse<double, double, double>), dim3((C.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                         C.n, C.m, C.inv.p, a.r0, a.z0, ctl);
+                         C.n, C.m, C.inv.p, a.r0, a.z0, stop);
     }
     if (a.red) {
       const int g = vec_grid(C.n);
-      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, C.n, a.r0, a.z0, a.q ? a.q : a.z0, ctl,
+      hipLaunchKernelGGL(k_dots_rz, dim3(g), dim3(kBlock), 0, s, C.n, a.r0, a.z0, a.q ? a.q : a.z0, stop,
                          a.partials);
       return g;
     }
@@ -1318,10 +1345,10 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
     } else {
       T* c = Bufs<T>::x(H.lv[0]);
       if (!a.x0_ready)
-        hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(H.n)), dim3(kBlock), 0, s, H.n, (const T*)nullptr, a.r0, c, ctl);
+        hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(H.n)), dim3(kBlock), 0, s, H.n, (const T*)nullptr, a.r0, c, stop);
       b0 = c;
     }
-    return fused_cycle<T>(H, b0, a.r0, a.z0, a.q, a.red, ctl, a.partials, s);
+    return fused_cycle<T>(H, b0, a.r0, a.z0, a.q, a.red, stop, a.partials, s);
   }
   T* cx[AMG_MAX_LEVELS];
   T* cr[AMG_MAX_LEVELS];
@@ -1337,48 +1364,48 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
     {
       // pre-smoothing from zero: x = sw o b was written by the producer of b
       // (CG update on level 0, restriction below), so only r = b - A x remains
-      InstScope is(H, KID_PRE, l, s, a.ctl);
+      InstScope is(H, KID_PRE, l, s, stop);
       if (l == 0 && !a.x0_ready)
-        sweep(L.shA, L.n, L.arp(), L.aci(), OpPre<T, double>{Bufs<T>::v(L), Bufs<T>::sw(L), a.r0, cx[l], cr[l]}, ctl,
+        sweep(L.shA, L.n, L.arp(), L.aci(), OpPre<T, double>{Bufs<T>::v(L), Bufs<T>::sw(L), a.r0, cx[l], cr[l]}, stop,
               nullptr, s);
       else if (l == 0)
-        sweep(L.shA, L.n, L.arp(), L.aci(), OpResid<T, double>{Bufs<T>::v(L), a.r0, cx[l], cr[l]}, ctl, nullptr, s);
+        sweep(L.shA, L.n, L.arp(), L.aci(), OpResid<T, double>{Bufs<T>::v(L), a.r0, cx[l], cr[l]}, stop, nullptr, s);
       else
-        sweep(L.shA, L.n, L.arp(), L.aci(), OpResid<T, T>{Bufs<T>::v(L), Bufs<T>::b(L), cx[l], cr[l]}, ctl, nullptr,
+        sweep(L.shA, L.n, L.arp(), L.aci(), OpResid<T, T>{Bufs<T>::v(L), Bufs<T>::b(L), cx[l], cr[l]}, stop, nullptr,
               s);
     }
     for (int k = 1; k < npre; ++k) {
       if (l == 0)
         sweep(L.shA, L.n, L.arp(), L.aci(),
-              OpSweep<T, double>{Bufs<T>::v(L), Bufs<T>::sw(L), a.r0, cx[l], cr[l], sx[l], sr[l]}, ctl, nullptr, s);
+              OpSweep<T, double>{Bufs<T>::v(L), Bufs<T>::sw(L), a.r0, cx[l], cr[l], sx[l], sr[l]}, stop, nullptr, s);
       else
         sweep(L.shA, L.n, L.arp(), L.aci(),
-              OpSweep<T, T>{Bufs<T>::v(L), Bufs<T>::sw(L), Bufs<T>::b(L), cx[l], cr[l], sx[l], sr[l]}, ctl, nullptr,
+              OpSweep<T, T>{Bufs<T>::v(L), Bufs<T>::sw(L), Bufs<T>::b(L), cx[l], cr[l], sx[l], sr[l]}, stop, nullptr,
               s);
       std::swap(cx[l], sx[l]);
       std::swap(cr[l], sr[l]);
     }
     {
-      InstScope is(H, KID_RESTRICT, l, s, a.ctl);
+      InstScope is(H, KID_RESTRICT, l, s, stop);
       Level& Ln = H.lv[l + 1];
       const bool last = (l + 1 == lf);  // the two-sweep levels start from b
       launch_restrict<T>(H, L, cr[l], Bufs<T>::b(Ln), last ? nullptr : Bufs<T>::sw(Ln),
-                         last ? nullptr : Bufs<T>::x(Ln), ctl, s);
+                         last ? nullptr : Bufs<T>::x(Ln), stop, s);
     }
   }
   T* res = Bufs<T>::x(H.lv[lf]);
   int np0 = 0;
   if (H.S == 1) {
-    fused_cycle<T>(H, nullptr, nullptr, nullptr, nullptr, 0, ctl, nullptr, s);
+    fused_cycle<T>(H, nullptr, nullptr, nullptr, nullptr, 0, stop, nullptr, s);
   } else {  // several systems: no dense tail (lf is the coarsest level)
     hipLaunchKernelGGL((k_coarse<T, T, T>), dim3((C.n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, C.n, C.m,
-                       Bufs<T>::inv(C), Bufs<T>::b(H.lv[lf]), res, ctl);
+                       Bufs<T>::inv(C), Bufs<T>::b(H.lv[lf]), res, stop);
   }
   for (int l = lf - 1; l >= 0; --l) {
     Level& L = H.lv[l];
     {
-      InstScope is(H, KID_PROLONG, l, s, a.ctl);
-      launch_prolong<T>(H, L, res, cx[l], ctl, s);
+      InstScope is(H, KID_PROLONG, l, s, stop);
+      launch_prolong<T>(H, L, res, cx[l], stop, s);
     }
     // free T buffers of this level after restriction: cr[l] and sx[l]
     T* cur = cx[l];
@@ -1390,26 +1417,26 @@ int vcycle_impl(Hierarchy& H, const CycleArgs& a, hipStream_t s) {
       if (l == 0 && last) {
         int np = 0;
         {
-          InstScope is(H, KID_POST, l, s, a.ctl);
+          InstScope is(H, KID_POST, l, s, stop);
           if (a.red == 2)
-            np = sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 2>{vv, sw, a.r0, cur, a.z0, a.q}, ctl,
+            np = sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 2>{vv, sw, a.r0, cur, a.z0, a.q}, stop,
                        a.partials, s);
           else if (a.red == 1)
-            np = sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 1>{vv, sw, a.r0, cur, a.z0, a.q}, ctl,
+            np = sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 1>{vv, sw, a.r0, cur, a.z0, a.q}, stop,
                        a.partials, s);
           else
-            sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 0>{vv, sw, a.r0, cur, a.z0, nullptr}, ctl,
+            sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, double, 0>{vv, sw, a.r0, cur, a.z0, nullptr}, stop,
                   nullptr, s);
         }
         np0 = np;
       } else {
         T* dst = spare[k & 1];
-        InstScope is(H, KID_POST, l, s, a.ctl);
+        InstScope is(H, KID_POST, l, s, stop);
         if (l == 0)
-          sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, T, 0>{vv, sw, a.r0, cur, dst, nullptr}, ctl, nullptr,
+          sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, double, T, 0>{vv, sw, a.r0, cur, dst, nullptr}, stop, nullptr,
                 s);
         else
-          sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, T, T, 0>{vv, sw, Bufs<T>::b(L), cur, dst, nullptr}, ctl,
+          sweep(L.shA, L.n, L.arp(), L.aci(), OpPost<T, T, T, 0>{vv, sw, Bufs<T>::b(L), cur, dst, nullptr}, stop,
                 nullptr, s);
         spare[k & 1] = cur;
         cur = dst;
@@ -1476,11 +1503,11 @@ std::vector<int> host_copy(const DBuf<int>& d, int64_t count) {
 
 // ================================================================ public
 
-InstScope::InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const Ctl* ctl) : H(h), s(st) {
+InstScope::InstScope(Hierarchy& h, int kid, int level, hipStream_t st, const int* stop) : H(h), s(st) {
   on = H.inst.kernel == kid && (H.inst.level == level || H.inst.level < 0) &&
        2 * (H.inst.used + 1) <= (int)H.inst.ev.size();
   if (on) {
-    hipLaunchKernelGGL(k_snap_done, dim3(1), dim3(64), 0, s, ctl, H.inst.was_done.p + H.inst.used);
+    hipLaunchKernelGGL(k_snap_done, dim3(1), dim3(64), 0, s, stop, H.inst.was_done.p + H.inst.used);
     AMG_HIP(hipEventRecord(H.inst.ev[2 * H.inst.used], s));
   }
 }
@@ -1913,7 +1940,7 @@ void launch_sw_mul(Hierarchy& H, const SolveWork& w, int n, hipStream_t s) {
   const X0Mode m = x0_mode(H);
   if (m == X0_NONE) return;
   hipLaunchKernelGGL((k_sw_mul<T>), dim3(vec_grid(n)), dim3(kBlock), 0, s, n,
-                     m == X0_COPY ? (const T*)nullptr : Bufs<T>::sw(L0), w.r, Bufs<T>::x(L0), w.ctl);
+                     m == X0_COPY ? (const T*)nullptr : Bufs<T>::sw(L0), w.r, Bufs<T>::x(L0), &w.ctl->done);
 }
 
 void read_ctl(const SolveWork& w, hipStream_t s) {
@@ -1973,7 +2000,7 @@ void totals_at(bool tot, std::initializer_list<Sums*> sums, double* out) {
 }
 
 // Launches k_sum for the sums where the solve takes totals, then totals_at.
-void total(bool tot, std::initializer_list<Sums*> sums, double* out, const Ctl* ctl, hipStream_t st) {
+void total(bool tot, std::initializer_list<Sums*> sums, double* out, const int* stop, hipStream_t st) {
   if (!tot) return;
   SumArgs a{};
   int m = 0;
@@ -1982,7 +2009,7 @@ void total(bool tot, std::initializer_list<Sums*> sums, double* out, const Ctl* 
       a.src[m] = s->p + (int64_t)v * s->np;
       a.np[m] = s->np;
     }
-  hipLaunchKernelGGL(k_sum, dim3(m), dim3(kFinBlock), 0, st, a, out, ctl);
+  hipLaunchKernelGGL(k_sum, dim3(m), dim3(kFinBlock), 0, st, a, out, stop);
   totals_at(tot, sums, out);
 }
 
@@ -2012,6 +2039,8 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
     }
   }
   Ctl* ctl = w.ctl;
+  const int* done = &ctl->done;      // (device addresses)
+  const int* gate = &ctl->gate[0];
   double* part = w.partials;
   const int gv = vec_grid(n);
   const int gu = vec_grid(n);
@@ -2050,25 +2079,25 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
     if (first) z = start;
     int np;
     {
-      InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
+      InstScope is(H, KID_SPMV_DOT, 0, st, done);
       np = sweep(L0.shA, n, L0.arp(), L0.aci(),
-                 OpSpmvXpay{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, z.p, u.p, z.np, u.np, z.nv, tot, first, c}, ctl, part,
+                 OpSpmvXpay{L0.av(), zv, pb[c], pb[c ^ 1], w.q, ctl, z.p, u.p, z.np, u.np, z.nv, tot, first, c}, done, part,
                  st);
     }
     Sums a{part, np, 1};
-    total(tot, {&a}, pt, ctl, st);
+    total(tot, {&a}, pt, gate, st);
     {
-      InstScope is(H, KID_CG_UPDATE, 0, st, ctl);
+      InstScope is(H, KID_CG_UPDATE, 0, st, gate);
       if (H.fp32()) launch_cg_update<float>(H, w, n, pb[c ^ 1], a.p, a.np, tot, pu, c, st);
       else launch_cg_update<double>(H, w, n, pb[c ^ 1], a.p, a.np, tot, pu, c, st);
     }
     u = Sums{pu, gu, 1};
     if (plain) {
-      total(tot, {&u}, pt + 1, ctl, st);
+      total(tot, {&u}, pt + 1, done, st);
     } else {
-      vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, nv, multi ? 1 : 0}, st);
+      vcycle(H, CycleArgs{w.r, w.z, w.q, done, pz, nv, multi ? 1 : 0}, st);
       z = Sums{pz, npz, nv};
-      total(tot, {&u, &z}, pt + 1, ctl, st);
+      total(tot, {&u, &z}, pt + 1, done, st);
     }
   };
   // two iterations captured once per direction-buffer parity and replayed
@@ -2090,9 +2119,9 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
     }
     // (plain CG starts from the partials of ||r||^2 that the start or the true
     // residual left in pz)
-    npz = plain ? (restarts ? L0.shA.grid : gu) : vcycle(H, CycleArgs{w.r, w.z, w.q, ctl, pz, 1, multi ? 1 : 0}, s);
+    npz = plain ? (restarts ? L0.shA.grid : gu) : vcycle(H, CycleArgs{w.r, w.z, w.q, done, pz, 1, multi ? 1 : 0}, s);
     start = Sums{pz, npz, 1};
-    total(tot, {&start}, pt + 1, ctl, s);
+    total(tot, {&start}, pt + 1, done, s);
     int first = 1;
     // Iterations are queued in chunks; between chunks the host reads the
     // control block and sizes the next chunk from the observed decay of
@@ -2212,6 +2241,8 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
     s = H.gr.gs;
   }
   Ctl* ctl = H.ctl.p;
+  const int* done = &ctl->done;      // (device addresses)
+  const int* gate = &ctl->gate[0];
   double* part = H.partials.p;
   double* r = H.r.p;
   double* p = H.p.p;
@@ -2267,24 +2298,24 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
   };
   auto iteration = [&](int first, hipStream_t st) {
     launch_dir(first, st);
-    if (prec) vcycle(H, CycleArgs{p, y, nullptr, ctl, part, 0, x0w ? 1 : 0}, st);
+    if (prec) vcycle(H, CycleArgs{p, y, nullptr, gate, part, 0, x0w ? 1 : 0}, st);
     int np;
     {
-      InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
-      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<1>{L0.av(), y, v, rh}, ctl, part, st);
+      InstScope is(H, KID_SPMV_DOT, 0, st, gate);
+      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<1>{L0.av(), y, v, rh}, gate, part, st);
     }
     Sums a{part, np, 1};
-    total(tot, {&a}, ptot, ctl, st);
+    total(tot, {&a}, ptot, gate, st);
     launch_half(a, st);
-    if (prec) vcycle(H, CycleArgs{sv, z, nullptr, ctl, part, 0, x0w ? 1 : 0}, st);
+    if (prec) vcycle(H, CycleArgs{sv, z, nullptr, gate + 1, part, 0, x0w ? 1 : 0}, st);
     {
-      InstScope is(H, KID_SPMV_DOT, 0, st, ctl);
-      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<2>{L0.av(), z, t, sv}, ctl, pt, st);
+      InstScope is(H, KID_SPMV_DOT, 0, st, gate + 1);
+      np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<2>{L0.av(), z, t, sv}, gate + 1, pt, st);
     }
     Sums h{ps, gu, 1}, tt{pt, np, 2}, f{pf, gu, 2};
-    total(tot, {&h, &tt}, ptot + 1, ctl, st);
+    total(tot, {&h, &tt}, ptot + 1, gate + 1, st);
     hipLaunchKernelGGL(k_bi_full, dim3(gu), dim3(kBlock), 0, st, n, z, sv, t, rh, r, ctl, h.p, h.np, tt.p, tt.np, tot, pf);
-    total(tot, {&f}, ptot + 4, ctl, st);
+    total(tot, {&f}, ptot + 4, done, st);
   };
   int restarts = 0;
   amg_status st = AMG_OK;
@@ -2346,7 +2377,7 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
     if (state == 1 && restarts < 5 && c.iters < c.maxiter) {
       ++restarts;
       hipLaunchKernelGGL(k_bi_restart, dim3(1), dim3(1), 0, s, ctl);
-      hipLaunchKernelGGL(k_copy_z, dim3(gv), dim3(kBlock), 0, s, n, r, rh, (const Ctl*)nullptr);
+      hipLaunchKernelGGL(k_copy_z, dim3(gv), dim3(kBlock), 0, s, n, r, rh, (const int*)nullptr);
       continue;
     }
     st = AMG_NOT_CONVERGED;
