@@ -250,7 +250,8 @@ amg_status amg_pattern_grad_batched(amg_handle h, const double* d_lambda, const 
                                     double* d_grad_val, hipStream_t stream);
 
 /* One V-cycle z = M^-1 r on the fine level (FP64 in and out, the handle's
- * cycle precision inside): the preconditioner as an operator. */
+ * cycle precision inside): the preconditioner as an operator.  d_z may be
+ * d_r (in place); buffers that overlap otherwise are not supported. */
 amg_status amg_apply_vcycle(amg_handle h, const double* d_r, double* d_z, hipStream_t stream);
 
 /* Allocation-free PCG solve, for callers that cannot allocate device memory

@@ -1902,6 +1902,14 @@ void read_instrument(Hierarchy& H, int* launches, double* total_ms, double* min_
 }
 
 void apply_vcycle(Hierarchy& H, const double* d_r, double* d_z, hipStream_t s) {
+  // In place: the two-sweep level 0 of the FP64 cycle and the dense product of a
+  // single level gather r while other workgroups write z, so they read a copy
+  // (the four-sweep level 0 reads r only at the row it writes; the FP32 cycle
+  // rounds r into a buffer of its own).
+  if (d_z == d_r && H.prm.precondition && (H.lv.size() == 1 || (H.lf == 0 && !H.fp32()))) {
+    hipLaunchKernelGGL(k_copy_z, dim3(vec_grid(H.n)), dim3(kBlock), 0, s, H.n, d_r, H.z.p, (const int*)nullptr);
+    d_r = H.z.p;
+  }
   CycleArgs a{d_r, d_z, nullptr, nullptr, nullptr, 0, 0};
   vcycle(H, a, s);
   AMG_HIP(hipGetLastError());
