@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "amg_internal.hpp"
+#include "sizes.hpp"
 
 namespace amg {
 namespace {
@@ -376,23 +377,24 @@ __global__ void k_dt_values(int n, const int* __restrict__ rp, const int* __rest
                             const int* __restrict__ tpos, const int* __restrict__ prp, const int* __restrict__ pci,
                             const RT* __restrict__ pv, const int* __restrict__ aprp, const int* __restrict__ apci,
                             const T* __restrict__ sw, double* __restrict__ dt) {
-  const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = t0 / kDtLanes;
-  if (j >= n) return;
-  const double w = (double)sw[j];
-  for (int e = aprp[j] + t0 % kDtLanes; e < aprp[j + 1]; e += kDtLanes) {
-    const int K = apci[e];
-    double acc = 0.0, own = 0.0;
-    for (int k = rp[j]; k < rp[j + 1]; ++k) {
-      const int i = ci[k];
-      for (int t = prp[i]; t < prp[i + 1]; ++t)
-        if (pci[t] == K) {
-          const double p = pval(pv[t]);
-          acc += (double)av[tpos[k]] * p;
-          if (i == j) own = p;
-        }
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t0 < (int64_t)n * kDtLanes; t0 += stride) {
+    const int j = (int)(t0 / kDtLanes), l = (int)(t0 % kDtLanes);
+    const double w = (double)sw[j];
+    for (int e = aprp[j] + l; e < aprp[j + 1]; e += kDtLanes) {
+      const int K = apci[e];
+      double acc = 0.0, own = 0.0;
+      for (int k = rp[j]; k < rp[j + 1]; ++k) {
+        const int i = ci[k];
+        for (int t = prp[i]; t < prp[i + 1]; ++t)
+          if (pci[t] == K) {
+            const double p = pval(pv[t]);
+            acc += (double)av[tpos[k]] * p;
+            if (i == j) own = p;
+          }
+      }
+      dt[e] = own - w * acc;
     }
-    dt[e] = own - w * acc;
   }
 }
 
@@ -626,8 +628,9 @@ void level_values(Hierarchy& H, Level& L, const RT* pv, hipStream_t s) {
     hipLaunchKernelGGL((k_q_values<RT, T>), dim3(blocks(L.n)), b, 0, s, L.n, L.prp.p, L.pci.p, pv, L.aprp.p,
                        L.apci.p, L.dtv.p, level_sw<T>(L), L.dtv.p);
   } else if (L.dtv.p)
-    hipLaunchKernelGGL((k_dt_values<RT, T>), dim3(blocks((int64_t)L.n * kDtLanes)), b, 0, s, L.n, L.rp.p, L.ci.p, level_a<T>(L),
-                       L.tpos.p, L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p, level_sw<T>(L), L.dtv.p);
+    hipLaunchKernelGGL((k_dt_values<RT, T>), dim3(stride_grid((int64_t)L.n * kDtLanes, kBlock)), b, 0, s, L.n,
+                       L.rp.p, L.ci.p, level_a<T>(L), L.tpos.p, L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p,
+                       level_sw<T>(L), L.dtv.p);
   hipLaunchKernelGGL((k_ell_values<true, T>), dim3(blocks(L.up.slices, kBlock / 64)), b, 0, s, L.n, L.up.slices,
                      L.up.g, L.up.off.p, L.up.col.p, L.up.src.p, level_a<T>(L), level_sw<T>(L), L.qv.p,
                      ell_v<T>(L.up));

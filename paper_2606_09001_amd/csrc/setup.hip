@@ -14,6 +14,7 @@
 #include <cstring>
 
 #include "amg_internal.hpp"
+#include "sizes.hpp"
 
 namespace amg {
 namespace {
@@ -361,17 +362,11 @@ __global__ void k_agg_phase3(int n, const int* __restrict__ grp, const int* __re
 // lists, per P entry, the A entries of its sum (pak[pao[e] ..)), and its row.
 // FILL = 0: distinct aggregates per row (cnt[n] = 0); 1: everything else.
 template <int FILL>
-__global__ void __launch_bounds__(kBlock) k_p_rows(int n, int sh, const int* __restrict__ rp,
-                                                   const int* __restrict__ ci, const int* __restrict__ agg,
-                                                   int* __restrict__ cnt, const double* __restrict__ v, int vs,
-                                                   const int* __restrict__ diagpos, double omegaP,
-                                                   const int* __restrict__ prp, int* __restrict__ pci,
-                                                   double* __restrict__ pv, int* __restrict__ pao,
-                                                   int* __restrict__ pak, int* __restrict__ prow) {
-  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int G = 1 << sh, l = (int)(q & (G - 1));
-  const int i = (int)(q >> sh);
-  if (i > n) return;  // (whole groups)
+__device__ inline void p_row(int i, int l, int G, int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                             const int* __restrict__ agg, int* __restrict__ cnt, const double* __restrict__ v, int vs,
+                             const int* __restrict__ diagpos, double omegaP, const int* __restrict__ prp,
+                             int* __restrict__ pci, double* __restrict__ pv, int* __restrict__ pao,
+                             int* __restrict__ pak, int* __restrict__ prow) {
   if (i == n) {
     if (!FILL && l == 0) cnt[n] = 0;
     if (FILL && l == 0) pao[prp[n]] = rp[n];
@@ -460,24 +455,40 @@ __global__ void __launch_bounds__(kBlock) k_p_rows(int n, int sh, const int* __r
   }
 }
 
+template <int FILL>
+__global__ void __launch_bounds__(kBlock) k_p_rows(int n, int sh, const int* __restrict__ rp,
+                                                   const int* __restrict__ ci, const int* __restrict__ agg,
+                                                   int* __restrict__ cnt, const double* __restrict__ v, int vs,
+                                                   const int* __restrict__ diagpos, double omegaP,
+                                                   const int* __restrict__ prp, int* __restrict__ pci,
+                                                   double* __restrict__ pv, int* __restrict__ pao,
+                                                   int* __restrict__ pak, int* __restrict__ prow) {
+  const int64_t items = ((int64_t)n + 1) << sh;  // (whole groups)
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < items; q += (int64_t)gridDim.x * blockDim.x)
+    p_row<FILL>((int)(q >> sh), (int)(q & ((1 << sh) - 1)), 1 << sh, n, rp, ci, agg, cnt, v, vs, diagpos, omegaP, prp,
+                pci, pv, pao, pak, prow);
+}
+
 // Prolongator values through the map (entry by system): the same expression
 // and fold as k_p_rows, omega_P = (4/3) / rho.
 __global__ void k_p_refill(int64_t pnnz, int S, int sh, const int* __restrict__ pao, const int* __restrict__ pak,
                            const int* __restrict__ prow, const int* __restrict__ pci, const double* __restrict__ v,
                            const int* __restrict__ diagpos, const int* __restrict__ agg,
                            const double* __restrict__ rho, double* __restrict__ pv) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t e = t >> sh;
-  const int y = (int)(t & ((1 << sh) - 1));
-  if (e >= pnnz || y >= S) return;
-  const int i = prow[e];
-  const double w = ((4.0 / 3.0) / rho[y]) / v[(int64_t)diagpos[i] * S + y];
-  double sJ = 0.0;
-  for (int q = pao[e]; q < pao[e + 1]; ++q)
-    if (pak[q] >= 0) sJ += v[(int64_t)pak[q] * S + y];
-  const double delta = (pci[e] == agg[i]) ? 1.0 : 0.0;
-  const double ws = w * sJ;
-  pv[e * S + y] = delta - ws;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < pnnz << sh; t += stride) {
+    const int64_t e = t >> sh;
+    const int y = (int)(t & ((1 << sh) - 1));
+    if (y >= S) continue;
+    const int i = prow[e];
+    const double w = ((4.0 / 3.0) / rho[y]) / v[(int64_t)diagpos[i] * S + y];
+    double sJ = 0.0;
+    for (int q = pao[e]; q < pao[e + 1]; ++q)
+      if (pak[q] >= 0) sJ += v[(int64_t)pak[q] * S + y];
+    const double delta = (pci[e] == agg[i]) ? 1.0 : 0.0;
+    const double ws = w * sJ;
+    pv[e * S + y] = delta - ws;
+  }
 }
 
 __global__ void k_row_ids(int n, const int* __restrict__ rp, int* __restrict__ rowid) {
@@ -506,10 +517,12 @@ __global__ void k_key_rows(int64_t m, int nc, const int* __restrict__ keys, int*
 // source rows ascending inside each row of R).
 __global__ void k_r_fill(int64_t m, int S, int sh, const int* __restrict__ perm, const double* __restrict__ pv,
                          double* __restrict__ rv) {
-  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t t = q >> sh;
-  const int y = (int)(q & ((1 << sh) - 1));
-  if (t < m && y < S) rv[t * S + y] = pv[(int64_t)perm[t] * S + y];
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < m << sh; q += stride) {
+    const int64_t t = q >> sh;
+    const int y = (int)(q & ((1 << sh) - 1));
+    if (y < S) rv[t * S + y] = pv[(int64_t)perm[t] * S + y];
+  }
 }
 
 // Columns of a transposed pattern: entry t holds the source row of entry perm[t].
@@ -768,31 +781,35 @@ __global__ void __launch_bounds__(kBlock) k_pm(int64_t cnnz, int sh, const int* 
                                                const int* __restrict__ xci, const int* __restrict__ yrp,
                                                const int* __restrict__ yci, int64_t* __restrict__ cnt,
                                                const int64_t* __restrict__ off, int2* __restrict__ pairs) {
-  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int G = 1 << sh, l = (int)(q & (G - 1));
-  const int64_t e = q >> sh;
-  if (!FILL && e == cnnz && l == 0) cnt[cnnz] = 0;
-  const bool live = e < cnnz;  // (every lane of the wave takes part in the ballots)
-  const int row = live ? crow[e] : 0, J = live ? cci[e] : 0;
-  const int a0 = live ? xrp[row] : 0, a1 = live ? xrp[row + 1] : 0;
-  const int lane = threadIdx.x & 63, first = lane & ~(G - 1);
-  const unsigned long long group = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << first;
-  int64_t p = FILL && live ? off[e] : 0;
-  int64_t c = 0;
-  int steps = (a1 - a0 + G - 1) >> sh;
-  for (int o = 32; o > 0; o >>= 1) steps = max(steps, __shfl_xor(steps, o, 64));
-  for (int t = 0; t < steps; ++t) {
-    const int a = a0 + t * G + l;
-    int f = -1;
-    if (a < a1) {
-      const int k = xci[a];
-      f = find_col(yci, yrp[k], yrp[k + 1], J);
+  // (every lane of a workgroup takes the same strides)
+  const int64_t items = (cnnz + 1) << sh;
+  for (int64_t q0 = blockIdx.x * (int64_t)kBlock; q0 < items; q0 += (int64_t)gridDim.x * kBlock) {
+    const int64_t q = q0 + threadIdx.x;
+    const int G = 1 << sh, l = (int)(q & (G - 1));
+    const int64_t e = q >> sh;
+    if (!FILL && e == cnnz && l == 0) cnt[cnnz] = 0;
+    const bool live = e < cnnz;  // (every lane of the wave takes part in the ballots)
+    const int row = live ? crow[e] : 0, J = live ? cci[e] : 0;
+    const int a0 = live ? xrp[row] : 0, a1 = live ? xrp[row + 1] : 0;
+    const int lane = threadIdx.x & 63, first = lane & ~(G - 1);
+    const unsigned long long group = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << first;
+    int64_t p = FILL && live ? off[e] : 0;
+    int64_t c = 0;
+    int steps = (a1 - a0 + G - 1) >> sh;
+    for (int o = 32; o > 0; o >>= 1) steps = max(steps, __shfl_xor(steps, o, 64));
+    for (int t = 0; t < steps; ++t) {
+      const int a = a0 + t * G + l;
+      int f = -1;
+      if (a < a1) {
+        const int k = xci[a];
+        f = find_col(yci, yrp[k], yrp[k + 1], J);
+      }
+      const unsigned long long hits = __ballot(f >= 0) & group;
+      if (FILL && f >= 0) pairs[p + c + __popcll(hits & ((1ull << lane) - 1ull))] = make_int2(a, f);
+      c += __popcll(hits);
     }
-    const unsigned long long hits = __ballot(f >= 0) & group;
-    if (FILL && f >= 0) pairs[p + c + __popcll(hits & ((1ull << lane) - 1ull))] = make_int2(a, f);
-    c += __popcll(hits);
+    if (!FILL && live && l == 0) cnt[e] = c;
   }
-  if (!FILL && live && l == 0) cnt[e] = c;
 }
 
 // Numeric product through the map (entry by system): the same fold (ascending
@@ -801,26 +818,28 @@ __global__ void __launch_bounds__(kBlock) k_pm(int64_t cnnz, int sh, const int* 
 __global__ void k_pm_apply(int64_t cnnz, int S, int sh, const int64_t* __restrict__ off,
                            const int2* __restrict__ pairs, const double* __restrict__ xv,
                            const double* __restrict__ yv, double* __restrict__ cv) {
-  const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t e = q >> sh;
-  const int y = (int)(q & ((1 << sh) - 1));
-  if (e >= cnnz || y >= S) return;
-  double acc = 0.0;
-  const int64_t p0 = off[e], p1 = off[e + 1];
-  // 4 terms in flight: unconditional loads at clamped positions, the adds
-  // masked and in order
-  constexpr int U = 4;
-  for (int64_t p = p0; p < p1; p += U) {
-    int2 t[U];
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < cnnz << sh; q += stride) {
+    const int64_t e = q >> sh;
+    const int y = (int)(q & ((1 << sh) - 1));
+    if (y >= S) continue;
+    double acc = 0.0;
+    const int64_t p0 = off[e], p1 = off[e + 1];
+    // 4 terms in flight: unconditional loads at clamped positions, the adds
+    // masked and in order
+    constexpr int U = 4;
+    for (int64_t p = p0; p < p1; p += U) {
+      int2 t[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = pairs[min(p + u, p1 - 1)];
-    double prod[U];
+      for (int u = 0; u < U; ++u) t[u] = pairs[min(p + u, p1 - 1)];
+      double prod[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) prod[u] = xv[(int64_t)t[u].x * S + y] * yv[(int64_t)t[u].y * S + y];
+      for (int u = 0; u < U; ++u) prod[u] = xv[(int64_t)t[u].x * S + y] * yv[(int64_t)t[u].y * S + y];
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc = p + u < p1 ? acc + prod[u] : acc;
+      for (int u = 0; u < U; ++u) acc = p + u < p1 ? acc + prod[u] : acc;
+    }
+    cv[e * S + y] = acc;
   }
-  cv[e * S + y] = acc;
 }
 
 // ------------------------------------------------------ precision copies
@@ -987,7 +1006,7 @@ bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, 
   // lanes per entry: about four inner indices each
   int sh = 0;
   while (sh < 6 && xnnz > ((int64_t)4 << sh) * nrows) ++sh;
-  const dim3 grid((unsigned)((((cnnz + 1) << sh) + kBlock - 1) / kBlock));
+  const dim3 grid(stride_grid((cnnz + 1) << sh, kBlock));
   hipLaunchKernelGGL(k_pm<0>, grid, dim3(kBlock), 0, s, cnnz, sh, crow.p, cci, xrp, xci, yrp, yci, cnt.p,
                      (const int64_t*)nullptr, (int2*)nullptr);
   off.alloc(cnnz + 1);
@@ -1018,7 +1037,7 @@ int sys_shift(int S) {
   while ((1 << sh) < S) ++sh;
   return sh;
 }
-unsigned sys_grid(int64_t items, int sh) { return (unsigned)std::max<int64_t>(1, ((items << sh) + kBlock - 1) / kBlock); }
+unsigned sys_grid(int64_t items, int sh) { return stride_grid(items << sh, kBlock); }
 
 void level_numerics(Hierarchy& H, Level& L, hipStream_t s) {
   const int S = H.S, sh = sys_shift(S);
@@ -1150,7 +1169,7 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   // P: lanes per row for twice the mean row length
   int psh = 0;
   while (psh < 6 && 2 * L.nnz > ((int64_t)n << psh)) ++psh;
-  const dim3 pg(grid_for(((int64_t)n + 1) << psh));
+  const dim3 pg(stride_grid(((int64_t)n + 1) << psh, kBlock));
   if (symbolic) {
     TBuf<int> cnt;
     cnt.alloc(n + 1);
@@ -1569,7 +1588,7 @@ void transpose_pattern(Hierarchy& H, hipStream_t s) {
 // Values of A^T in its entry order from A's current values.
 void transpose_values(Hierarchy& H, hipStream_t s) {
   const Level& L = H.lv[0];
-  hipLaunchKernelGGL(k_r_fill, dim3(grid_for(L.nnz)), dim3(kBlock), 0, s, L.nnz, 1, 0, H.tperm.p, L.v.p, H.tval.p);
+  hipLaunchKernelGGL(k_r_fill, dim3(sys_grid(L.nnz, 0)), dim3(kBlock), 0, s, L.nnz, 1, 0, H.tperm.p, L.v.p, H.tval.p);
   AMG_HIP(hipGetLastError());
 }
 
