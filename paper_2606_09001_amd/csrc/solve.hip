@@ -1759,13 +1759,16 @@ void choose_shapes(Hierarchy& H, hipStream_t s) {
 // Partials per reduced value of the largest reducing grid of a solve on H.
 int64_t partials_region(const Hierarchy& H) {
   int64_t np = std::max<int64_t>(vec_grid(H.n), H.lv[0].shA.grid);
-  np = std::max<int64_t>(np, H.lv[0].up.grid);
+  if (H.lf == 0) np = std::max<int64_t>(np, H.lv[0].up.grid);
   return std::max<int64_t>(np, vec_grid(std::max(H.co.n, 1)));
 }
 
 // Product, update and V-cycle of CG (1, 1, 2 values); products, half and full
-// step of BiCGSTAB (1, 2, 1, 2).
-int64_t solve_partials_count(const Hierarchy& H) { return partials_region(H) * 6 + 64; }
+// step of BiCGSTAB (1, 2, 1, 2); the totals behind them.  (The allocation-free
+// CG solve admits a system by this count.)
+int64_t solve_partials_count(const Hierarchy& H) {
+  return partials_region(H) * (H.prm.solver == AMG_SOLVER_PCG ? 4 : 6) + 64;
+}
 
 SolveWork solve_work(Hierarchy& H) {
   return SolveWork{H.r.p, H.z.p, H.p.p, H.z2.p, H.q.p, H.partials.p, H.ctl.p, H.h_ctl, true};
@@ -2058,7 +2061,7 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   double* pu = part + region;
   double* pz = part + 2 * region;
   const bool tot = region > kFoldMax;
-  double* pt = part + 6 * region;   // totals: product; update and V-cycle
+  double* pt = part + 4 * region;   // totals: product; update and V-cycle
   Sums start{pz, 0, 1};             // <r, z> as the first product after a (re)start reads it
   int npz = 0;
   // plain CG with the standard beta: z = r needs no copy and <r, z> = ||r||^2
