@@ -172,7 +172,7 @@ struct Shape {
 
 // Sliced rows with G lanes per row: a slice is the 64/G rows of one wavefront;
 // lane l of the wave holds entries l%G, l%G + G, ... of row l/G, so step t of
-// the slice is one coalesced 64-lane load at off[s] + 64 t.  Every slice is
+// the slice is one coalesced 64-lane load at 64 (off[s] + t).  Every slice is
 // padded to its longest row (column -1).  src names the source of each entry
 // for value refreshes.
 struct Ell {

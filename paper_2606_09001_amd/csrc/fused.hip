@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kBlock) k_ell(int n, int slices, const int* __
   const int o0 = off[sc], o1 = off[sc + 1];
   const int done = stop ? *stop : 0;
   if (done) return;
-  const int w = sl < slices ? (o1 - o0) >> 6 : 0;
+  const int w = sl < slices ? o1 - o0 : 0;
   const int row = sl * (64 / G) + lane / G;
   const typename Op::Row in = op.row_in(min(row, n - 1));
   T s = 0;
@@ -116,7 +116,7 @@ __global__ void __launch_bounds__(kBlock) k_ell(int n, int slices, const int* __
     T a[kEllU], x[kEllU];
 #pragma unroll
     for (int u = 0; u < kEllU; ++u) {
-      const int p = o0 + min(t0 + u, w - 1) * 64 + lane;
+      const int p = (o0 + min(t0 + u, w - 1)) * 64 + lane;
       c[u] = col[p];
       a[u] = op.v[p];
     }
@@ -245,8 +245,10 @@ __global__ void k_tpos(int n, const int* __restrict__ rp, const int* __restrict_
   }
 }
 
-// Slice widths: 64 x the steps of the slice's longest row.  A row's entries
-// are those of row i of the first pattern, then of the second (when given).
+// Slice widths: the steps of the slice's longest row (in all at most the number
+// of entries, so their sum fits 32 bits where 64 times it need not).  A row's
+// entries are those of row i of the first pattern, then of the second (when
+// given).
 __global__ void k_ell_width(int n, int slices, int g, const int* __restrict__ rp1, const int* __restrict__ rp2,
                             int* __restrict__ cnt) {
   const int sl = blockIdx.x * blockDim.x + threadIdx.x;
@@ -258,7 +260,7 @@ __global__ void k_ell_width(int n, int slices, int g, const int* __restrict__ rp
   const int rows = 64 / g, r1 = min(n, (sl + 1) * rows);
   int w = 0;
   for (int i = sl * rows; i < r1; ++i) w = max(w, rp1[i + 1] - rp1[i] + (rp2 ? rp2[i + 1] - rp2[i] : 0));
-  cnt[sl] = 64 * ((w + g - 1) / g);
+  cnt[sl] = (w + g - 1) / g;
 }
 
 // Columns and sources: an entry of the first pattern has source k >= 0 and
@@ -271,7 +273,7 @@ __global__ void __launch_bounds__(kBlock) k_ell_fill(int n, int slices, int g, c
   const int sl = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (sl >= slices) return;
   const int row = sl * (64 / g) + lane / g;
-  const int o = off[sl], w = (off[sl + 1] - o) >> 6;
+  const int o = off[sl] * 64, w = off[sl + 1] - off[sl];
   const int k1 = row < n ? rp1[row] : 0, n1 = row < n ? rp1[row + 1] - k1 : 0;
   const int k2 = row < n && rp2 ? rp2[row] : 0, n2 = row < n && rp2 ? rp2[row + 1] - k2 : 0;
   for (int t = 0; t < w; ++t) {
@@ -409,7 +411,7 @@ __global__ void __launch_bounds__(kBlock) k_ell_values(int n, int slices, int g,
   const int sl = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (sl >= slices) return;
   const int row = sl * (64 / g) + lane / g;
-  const int o = off[sl], w = (off[sl + 1] - o) >> 6;
+  const int o = off[sl] * 64, w = off[sl + 1] - off[sl];
   const double si = A && row < n ? (double)sw[row] : 0.0;
   for (int t = 0; t < w; ++t) {
     const int p = o + t * 64 + lane;
@@ -510,17 +512,16 @@ bool build_ell(Ell& E, int n, int64_t nnz, const int* rp1, const int* ci1, const
   cub_run([&](void* t, size_t& b) {
     return hipcub::DeviceScan::ExclusiveSum(t, b, cnt.p, E.off.p, E.slices + 1, s);
   }, s);
-  int total = 0;
-  AMG_HIP(hipMemcpyAsync(&total, E.off.p + E.slices, sizeof(int), hipMemcpyDeviceToHost, s));
+  int steps = 0;
+  AMG_HIP(hipMemcpyAsync(&steps, E.off.p + E.slices, sizeof(int), hipMemcpyDeviceToHost, s));
   AMG_HIP(hipStreamSynchronize(s));
-  // (64 entries of padding per slice always pass: rows shorter than a step)
-  if (total < 0 || (int64_t)total > 2 * nnz + 64 * (int64_t)E.slices) return false;
-  E.len = total;
+  if (!ell_fits(steps, nnz, E.slices)) return false;
+  E.len = 64 * (int64_t)steps;
   int g = blocks(E.slices, kBlock / 64);
   if (g >= 64) g = (g + 7) / 8 * 8;
   E.grid = g;
-  E.col.alloc(std::max(total, 1));
-  E.src.alloc(std::max(total, 1));
+  E.col.alloc(std::max<int64_t>(E.len, 1));
+  E.src.alloc(std::max<int64_t>(E.len, 1));
   hipLaunchKernelGGL(k_ell_fill, dim3(blocks(E.slices, kBlock / 64)), dim3(kBlock), 0, s, n, E.slices, E.g, E.off.p,
                      rp1, ci1, rp2, ci2, E.col.p, E.src.p);
   AMG_HIP(hipGetLastError());

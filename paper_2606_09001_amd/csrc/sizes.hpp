@@ -16,4 +16,12 @@ inline unsigned stride_grid(int64_t items, int block) {
   return (unsigned)std::min(most, std::max<int64_t>(1, (items + block - 1) / block));
 }
 
+// Whether sliced rows (struct Ell) of `steps` steps of 64 entries are kept:
+// padding at most doubles the nnz entries (64 per slice always pass: rows
+// shorter than a step), and positions fit 32 bits.
+inline bool ell_fits(int64_t steps, int64_t nnz, int64_t slices) {
+  const int64_t len = 64 * steps;
+  return len <= 2 * nnz + 64 * slices && len <= INT32_MAX;
+}
+
 }  // namespace amg

@@ -27,6 +27,19 @@ def test_stride_grid(tmp_path):
             assert g == max(1, -(-t // 256))
 
 
+def test_ell_fits(tmp_path):
+    M = 1 << 30
+    cases = [(1, 1, 1), (2 * M // 64, M - 1, 1), (67_108_864, 80_000_000, 1_250_000), (67_108_865, M - 1, 0),
+             (67_108_864 + 100, 100, 100), (33_554_431, M - 1, 0), (33_554_432, M - 1, 1 << 20), (5, 128, 2), (7, 128, 2)]
+    out = _run(tmp_path, "\n".join(f'std::printf("%d\\n", (int)ell_fits({s}, {z}, {k}));' for s, z, k in cases))
+    want = [int(64 * s <= 2 * z + 64 * k and 64 * s < 1 << 31) for s, z, k in cases]
+    assert out == want
+    # (64 times the steps of the third and fifth case is 2^32 and a little more: 0 and 6,400 in 32 bits)
+    assert want[2] == 0 and want[4] == 0
+    text = open(os.path.join(CSRC, "fused.hip")).read()
+    assert "cnt[sl] = (w + g - 1) / g;" in text and "ell_fits(steps, nnz, E.slices)" in text
+
+
 @pytest.mark.parametrize("name,kernel", [("setup.hip", k) for k in ("k_pm", "k_pm_apply", "k_p_rows", "k_p_refill",
                                                                     "k_r_fill")] + [("fused.hip", "k_dt_values")])
 def test_kernels_with_lanes_per_entry_take_strides(name, kernel):
