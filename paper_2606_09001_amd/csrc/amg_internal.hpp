@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "amg355.h"
+#include "arena.hpp"
 
 namespace amg {
 
@@ -32,46 +33,16 @@ struct Error : std::runtime_error {
 
 // --------------------------------------------------------------- memory
 
-// Device memory handed out from a few slabs.  A setup makes over 200 buffers;
-// each its own hipMalloc and synchronizing hipFree they took 19 of the 45 ms of
-// a cold 100^3 setup and solve.  A hierarchy's buffers live in its own arena
-// until it is destroyed or set up again; a setup's temporaries in a second one
-// that is used as a stack (Arena::Scope) and freed when the setup returns.  All
-// work of a setup is on one stream, so memory taken back is reused in order.
-class Arena {
- public:
-  Arena() = default;
-  Arena(const Arena&) = delete;
-  Arena& operator=(const Arena&) = delete;
-  ~Arena() { free_all(); }
-  // 256-byte aligned; slabs grow with what is already held (2 to 256 MB, or
-  // the request itself)
-  void* get(size_t bytes) {
-    bytes = (bytes + 255) & ~(size_t)255;
-    for (Slab& s : slabs_)
-      if (s.cap - s.used >= bytes) {
-        void* q = s.p + s.used;
-        s.used += bytes;
-        return q;
-      }
-    size_t held = 0;
-    for (const Slab& s : slabs_) held += s.cap;
-    const size_t cap = std::max(bytes, std::min(std::max(held, kMinSlab), kMaxSlab));
-    Slab s;
-    AMG_HIP(hipMalloc((void**)&s.p, cap));
-    s.cap = cap;
-    s.used = bytes;
-    slabs_.push_back(s);
-    return s.p;
+struct DeviceMem {
+  static char* take(size_t bytes) {
+    char* p = nullptr;
+    AMG_HIP(hipMalloc((void**)&p, bytes));
+    return p;
   }
-  void reset() {
-    for (Slab& s : slabs_) s.used = 0;
-  }
-  void free_all() {
-    for (Slab& s : slabs_) (void)hipFree(s.p);
-    slabs_.clear();
-  }
+  static void give(char* p) { (void)hipFree(p); }
+};
 
+struct Arena : ArenaOf<DeviceMem> {
   // The thread's arenas while a setup runs (null otherwise).
   struct Current {
     Arena* keep = nullptr;
@@ -86,47 +57,27 @@ class Arena {
     Use(Arena* keep, Arena* scratch) : before(current()) { current() = Current{keep, scratch}; }
     ~Use() { current() = before; }
   };
-  // Takes back, on leaving, what was taken from the thread's scratch arena.
-  struct Scope {
-    Arena* a = current().scratch;
-    std::vector<size_t> used;
-    Scope() {
-      if (a)
-        for (const Slab& s : a->slabs_) used.push_back(s.used);
-    }
-    ~Scope() {
-      if (a)
-        for (size_t i = 0; i < a->slabs_.size(); ++i) a->slabs_[i].used = i < used.size() ? used[i] : 0;
-    }
-  };
-
- private:
-  static constexpr size_t kMinSlab = (size_t)2 << 20, kMaxSlab = (size_t)256 << 20;
-  struct Slab {
-    char* p = nullptr;
-    size_t cap = 0, used = 0;
-  };
-  std::vector<Slab> slabs_;
 };
 
-// Device buffer: from the thread's arena while a setup runs, else allocated
-// by itself.
+// Device buffer: from the thread's arena while a setup runs (given back to it on
+// release), else allocated by itself.
 template <class T>
 struct DBuf {
   T* p = nullptr;
   int64_t n = 0;
-  bool own = false;
+  Arena* home = nullptr;
   DBuf() = default;
   DBuf(const DBuf&) = delete;
   DBuf& operator=(const DBuf&) = delete;
-  DBuf(DBuf&& o) noexcept : p(o.p), n(o.n), own(o.own) { o.p = nullptr; o.n = 0; }
+  DBuf(DBuf&& o) noexcept : p(o.p), n(o.n), home(o.home) { o.p = nullptr; o.n = 0; }
   DBuf& operator=(DBuf&& o) noexcept {
-    if (this != &o) { release(); p = o.p; n = o.n; own = o.own; o.p = nullptr; o.n = 0; }
+    if (this != &o) { release(); p = o.p; n = o.n; home = o.home; o.p = nullptr; o.n = 0; }
     return *this;
   }
   ~DBuf() { release(); }
   void release() {
-    if (p && own) (void)hipFree(p);
+    if (p && home) home->put(p, bytes());
+    else if (p) (void)hipFree(p);
     p = nullptr;
     n = 0;
   }
@@ -135,18 +86,17 @@ struct DBuf {
     if (count == n && p) return;
     release();
     if (count > 0) {
-      own = a == nullptr;
       if (a) p = static_cast<T*>(a->get(sizeof(T) * (size_t)count));
       else AMG_HIP(hipMalloc(&p, sizeof(T) * (size_t)count));
+      home = a;
     }
     n = count;
   }
   size_t bytes() const { return sizeof(T) * (size_t)n; }
 };
 
-// Temporary device buffer of a setup step (declared inside an Arena::Scope).
-// Outside a setup it is a buffer of its own, whose hipFree waits for the
-// device.
+// Temporary device buffer of a setup step.  Outside a setup it is a buffer of
+// its own, whose hipFree waits for the device.
 template <class T>
 struct TBuf : DBuf<T> {
   void alloc(int64_t count) { this->alloc_from(Arena::current().scratch, count); }
@@ -181,6 +131,14 @@ struct Ell {
   DBuf<int> off, col, src;
   DBuf<double> v;
   DBuf<float> v32;
+  void release() {
+    grid = 0;
+    off.release();
+    col.release();
+    src.release();
+    v.release();
+    v32.release();
+  }
 };
 
 struct Level {
@@ -264,11 +222,11 @@ struct Level {
   // Two-sweep form of the level's V(1,1) cycle (fused.hip): dn = R (I - A S)
   // takes b_l to b_{l+1}; up = [2S - S A S | (I - S A) P] takes (b_l, x_{l+1})
   // to x_l.  qv: (I - S A) P on the pattern of A P; dtv: dn transposed on that
-  // pattern (empty when it equals qv); dperm: entry of dn's rows -> entry of
-  // A P; tpos: position of (j, i) for entry (i, j) of A (nonsymmetric values)
+  // pattern (empty when it equals qv); tpos: position of (j, i) for entry
+  // (i, j) of A (nonsymmetric values)
   Ell up, dn;
   DBuf<double> qv, dtv, apt;
-  DBuf<int> drp, dci, dperm, tpos;
+  DBuf<int> tpos;
 };
 
 // The coarse end of the two-sweep cycle as one dense matrix: x_lx = X b_lb.
@@ -375,6 +333,7 @@ struct Graphs {
 };
 
 struct Hierarchy {
+  Arena arena;  // buffers of the levels, the coarsest solve and the solve workspace (which go before it)
   amg_params prm{};
   Instr inst;
   Batch bt;
@@ -382,7 +341,6 @@ struct Hierarchy {
   int S = 1;   // systems sharing the pattern (values interleaved [nnz][S])
   int n = 0;
   int64_t nnz = 0;
-  Arena arena;  // buffers of the levels, the coarsest solve and the solve workspace
   std::vector<Level> lv;
   Coarse co;
   // levels lf .. run the two-sweep cycle (lf = number of levels: none)

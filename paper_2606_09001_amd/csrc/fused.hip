@@ -488,7 +488,6 @@ template <class F>
 void cub_run(F&& f, hipStream_t s) {
   size_t tmp = 0;
   AMG_HIP(f(nullptr, tmp));
-  Arena::Scope scope;
   TBuf<unsigned char> buf;
   buf.alloc((int64_t)std::max<size_t>(tmp, 1));
   AMG_HIP(f(buf.p, tmp));
@@ -504,7 +503,6 @@ bool build_ell(Ell& E, int n, int64_t nnz, const int* rp1, const int* ci1, const
   while (E.g < 64 && avg > 6.0 * E.g) E.g <<= 1;
   const int rows = 64 / E.g;
   E.slices = (n + rows - 1) / rows;
-  Arena::Scope scope;
   TBuf<int> cnt;
   cnt.alloc(E.slices + 1);
   E.off.alloc(E.slices + 1);
@@ -532,7 +530,7 @@ bool build_ell(Ell& E, int n, int64_t nnz, const int* rp1, const int* ci1, const
 // symmetric: CG takes A = A^T; BiCGSTAB may be given any A.
 bool nonsym_values(const Hierarchy& H) { return !H.prm.symmetric || H.prm.solver != AMG_SOLVER_PCG; }
 
-bool build_level(Hierarchy& H, int l, hipStream_t s) {
+bool build_level_pattern(Hierarchy& H, int l, hipStream_t s) {
   Level& L = H.lv[l];
   const int nc = L.nagg;
   if (L.nnz + L.apnnz >= (int64_t)1 << 30) return false;
@@ -548,26 +546,37 @@ bool build_level(Hierarchy& H, int l, hipStream_t s) {
   {
     // transpose of the pattern of A P: a stable sort of its entries by column
     const int64_t m = L.apnnz;
-    Arena::Scope scope;
-    TBuf<int> rowid, iota, keys;
+    TBuf<int> rowid, iota, keys, dperm, dci, drp;
     rowid.alloc(m);
     iota.alloc(m);
     keys.alloc(m);
-    L.dperm.alloc(m);
-    L.dci.alloc(m);
-    L.drp.alloc(nc + 1);
+    dperm.alloc(m);   // entry of dn's rows -> entry of A P
+    dci.alloc(m);
+    drp.alloc(nc + 1);
     hipLaunchKernelGGL(k_rows_of, dim3(blocks(L.n)), dim3(kBlock), 0, s, L.n, L.aprp.p, rowid.p);
     hipLaunchKernelGGL(k_pos_iota, dim3(blocks(m)), dim3(kBlock), 0, s, m, iota.p);
     int bits = 1;
     while ((1ll << bits) < (long long)nc) ++bits;
     cub_run([&](void* t, size_t& b) {
-      return hipcub::DeviceRadixSort::SortPairs(t, b, L.apci.p, keys.p, iota.p, L.dperm.p, (int)m, 0, bits, s);
+      return hipcub::DeviceRadixSort::SortPairs(t, b, L.apci.p, keys.p, iota.p, dperm.p, (int)m, 0, bits, s);
     }, s);
-    hipLaunchKernelGGL(k_rows_of_keys, dim3(blocks(m)), dim3(kBlock), 0, s, m, nc, keys.p, L.drp.p);
-    hipLaunchKernelGGL(k_gather_i32, dim3(blocks(m)), dim3(kBlock), 0, s, m, L.dperm.p, rowid.p, L.dci.p);
-    if (!build_ell(L.dn, nc, m, L.drp.p, L.dci.p, nullptr, nullptr, s)) return false;
+    hipLaunchKernelGGL(k_rows_of_keys, dim3(blocks(m)), dim3(kBlock), 0, s, m, nc, keys.p, drp.p);
+    hipLaunchKernelGGL(k_gather_i32, dim3(blocks(m)), dim3(kBlock), 0, s, m, dperm.p, rowid.p, dci.p);
+    if (!build_ell(L.dn, nc, m, drp.p, dci.p, nullptr, nullptr, s)) return false;
     // sources as entries of A P instead of entries of dn's rows
-    hipLaunchKernelGGL(k_src_perm, dim3(blocks(L.dn.len)), dim3(kBlock), 0, s, L.dn.len, L.dperm.p, L.dn.src.p);
+    hipLaunchKernelGGL(k_src_perm, dim3(blocks(L.dn.len)), dim3(kBlock), 0, s, L.dn.len, dperm.p, L.dn.src.p);
+  }
+  return true;
+}
+
+// The level's two-sweep form; false (and nothing kept) where it is not taken.
+bool build_level(Hierarchy& H, int l, hipStream_t s) {
+  Level& L = H.lv[l];
+  if (!build_level_pattern(H, l, s)) {
+    L.up.release();
+    L.dn.release();
+    L.tpos.release();
+    return false;
   }
   L.qv.alloc(L.apnnz);
   if (nonsym_values(H)) L.dtv.alloc(L.apnnz);

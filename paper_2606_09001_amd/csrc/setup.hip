@@ -974,7 +974,6 @@ template <class F>
 void cub_call(F&& f, hipStream_t s) {
   size_t tmp = 0;
   AMG_HIP(f(nullptr, tmp));
-  Arena::Scope scope;
   TBuf<unsigned char> buf;
   buf.alloc((int64_t)std::max<size_t>(tmp, 1));
   AMG_HIP(f(buf.p, tmp));
@@ -997,7 +996,6 @@ int64_t read_i64(const int64_t* d, hipStream_t s) {
 bool build_product_map(int nrows, int64_t cnnz, const int* crp, const int* cci, int64_t xnnz, const int* xrp,
                        const int* xci, const int* yrp, const int* yci, int64_t budget, DBuf<int64_t>& off,
                        DBuf<int2>& pairs, hipStream_t s) {
-  Arena::Scope scope;
   TBuf<int64_t> cnt;
   TBuf<int> crow;
   cnt.alloc(cnnz + 1);
@@ -1077,7 +1075,6 @@ void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
     return;
   }
   // general path: emit (i,j) and (j,i) for every strong entry, sort, unique
-  Arena::Scope scope;
   TBuf<int> cnt, off;
   cnt.alloc(L.n + 1);
   off.alloc(L.n + 1);
@@ -1114,7 +1111,6 @@ void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
 // Returns the number of aggregates.
 int aggregate(Hierarchy& H, Level& L, hipStream_t s) {
   const int n = L.n;
-  Arena::Scope scope;
   TBuf<int8_t> state, e1;
   TBuf<unsigned long long> m1;
   state.alloc(n);
@@ -1165,7 +1161,6 @@ void transfer_and_galerkin(Hierarchy& H, size_t l, bool symbolic, hipStream_t s)
   for (int sy = 0; sy < S; ++sy) L.omegaPS[sy] = (4.0 / 3.0) / L.rhoS[sy];
   L.rho = L.rhoS[0];
   L.omegaP = L.omegaPS[0];
-  Arena::Scope scope;
   // P: lanes per row for twice the mean row length
   int psh = 0;
   while (psh < 6 && 2 * L.nnz > ((int64_t)n << psh)) ++psh;
@@ -1345,7 +1340,6 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
   if (H.S != 1) return;
   for (size_t l = 0; l < H.lv.size(); ++l) {
     Level& L = H.lv[l];
-    Arena::Scope scope;
     if (build) {
       L.sell = false;
       L.sell_form = 0;
@@ -1539,6 +1533,7 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   H.small_checked = false;
   small_solve_ok(H);
   AMG_HIP(hipStreamSynchronize(s));
+  H.arena.trim();
 }
 
 // Pattern of A^T by a stable radix sort of the entries by column: entry t of
@@ -1548,7 +1543,6 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
 void transpose_csr_pattern(int n, int64_t nnz, const int* rp, const int* ci, DBuf<int>& trp, DBuf<int>& tci,
                            DBuf<int>& perm, hipStream_t s) {
   const dim3 b(kBlock);
-  Arena::Scope scope;
   TBuf<int> rowid, iota, keys_out;
   rowid.alloc(std::max<int64_t>(nnz, 1));
   iota.alloc(std::max<int64_t>(nnz, 1));

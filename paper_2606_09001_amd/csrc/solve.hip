@@ -1598,7 +1598,6 @@ double time_shape(const Shape& sh, int n, const int* rp, const int* ci, const Op
 template <class MakeOp>
 Shape pick_shape(Hierarchy& H, const char* kind, int level, const DBuf<int>& rpd, const DBuf<int>& cid, int n,
                  int ncols, MakeOp make_op, hipStream_t s) {
-  Arena::Scope scope;
   const std::vector<int> rp = host_copy(rpd, n + 1);
   Shape rule = make_shape(rp, n);
   if (!H.prm.autotune || n == 0) return rule;
