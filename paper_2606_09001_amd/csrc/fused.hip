@@ -669,11 +669,27 @@ void tail_values(Hierarchy& H, hipStream_t s) {
   const int nl = (int)H.lv.size();
   const int top = std::max(H.lf, 1);
   int lx = nl - 1, n = H.co.n, ld = H.co.m;
-  int64_t need = (int64_t)n * n;
-  for (int l = nl - 2; l >= top && H.lv[l].n <= kDenseRows; --l)
-    need = std::max(need, (int64_t)H.lv[l].n * H.lv[l].n);
-  need = std::max(need, kDenseE);
-  for (auto& w : t.w) w.alloc(need);
+  // the products written below, by the buffer they go to (none of a hierarchy
+  // whose end is the coarsest inverse itself)
+  int64_t need[3] = {};
+  {
+    int at = 0, l = lx;
+    int64_t m = n;
+    auto writes = [&](int w, int64_t count) { need[w] = std::max(need[w], count); };
+    if (!H.prm.symmetric) {
+      writes(at, m * m);
+      at ^= 1;
+    }
+    for (; l - 1 >= top && H.lv[l - 1].n <= kDenseRows; --l) {
+      const int64_t k = H.lv[l - 1].n;
+      writes(2, k * m);
+      writes(at, k * k);
+      at ^= 1;
+      m = k;
+    }
+    if (l - 1 >= H.lf && m * H.lv[l - 1].n <= kDenseE) writes(at, m * H.lv[l - 1].n);
+  }
+  for (int w = 0; w < 3; ++w) t.w[w].alloc(need[w]);
   const double* X = H.co.inv.p;
   int at = 0;
   if (!H.prm.symmetric) {
