@@ -34,10 +34,13 @@ struct Error : std::runtime_error {
 // --------------------------------------------------------------- memory
 
 struct DeviceMem {
-  static char* take(size_t bytes) {
+  static char* take(size_t bytes, bool must) {
     char* p = nullptr;
-    AMG_HIP(hipMalloc((void**)&p, bytes));
-    return p;
+    const hipError_t e = hipMalloc((void**)&p, bytes);
+    if (e == hipSuccess) return p;
+    (void)hipGetLastError();  // (sticks to the thread otherwise, and fails the next launch check)
+    if (e == hipErrorOutOfMemory && !must) return nullptr;
+    throw Error(e == hipErrorOutOfMemory ? AMG_ERR_OOM : AMG_ERR_HIP, std::string("hipMalloc: ") + hipGetErrorString(e));
   }
   static void give(char* p) { (void)hipFree(p); }
 };

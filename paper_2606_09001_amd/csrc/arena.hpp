@@ -1,5 +1,5 @@
 // Device memory handed out from a few slabs.  No HIP in here: Mem supplies
-//   static char* take(size_t bytes)  (throws)
+//   static char* take(size_t bytes, bool must)  null when out of memory, unless `must` (then it throws)
 //   static void give(char* p)
 // and the CPU tests run it over host memory.
 #pragma once
@@ -27,7 +27,7 @@ class ArenaOf {
   }
   // 256-byte aligned: a hole that something given back has left, the end of a
   // slab, or a new slab.  Slabs grow with what is already held (2 to 256 MB, or
-  // the request itself).
+  // the request itself); where that cannot be had, one of the request's size.
   void* get(size_t bytes) {
     bytes = round(bytes);
     for (Slab& s : slabs_) {
@@ -49,8 +49,9 @@ class ArenaOf {
     slabs_.emplace_back();
     Slab& s = slabs_.back();
     try {
-      s.p = Mem::take(cap);
-      s.cap = cap;
+      s.p = cap > bytes ? Mem::take(cap, false) : nullptr;
+      s.cap = s.p ? cap : bytes;
+      if (!s.p) s.p = Mem::take(bytes, true);
     } catch (...) {
       slabs_.pop_back();
       throw;

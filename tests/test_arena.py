@@ -16,8 +16,11 @@ HEAD = r"""
 struct Host {
   static inline std::map<char*, size_t> live;
   static inline size_t held = 0, limit = ~(size_t)0, base = (size_t)1 << 40;
-  static char* take(size_t b) {
-    if (held + b > limit) throw 1;
+  static char* take(size_t b, bool must) {
+    if (held + b > limit) {
+      if (must) throw 1;
+      return nullptr;
+    }
     char* p = (char*)base;
     base += b + 4096;
     live[p] = b;
@@ -90,6 +93,23 @@ def test_memory_given_back_is_used_again(tmp_path):
     CHECK(a.get(1000) != p);
     a.reset();
     CHECK(a.get(1000) == p);
+  }
+  CHECK(Host::live.empty());
+""")
+
+
+def test_a_slab_that_cannot_be_had_leaves_the_request(tmp_path):
+    _run(tmp_path, r"""
+  Host::limit = (size_t)100 << 20;
+  {
+    A a;
+    CHECK(a.get((size_t)60 << 20));
+    CHECK(a.get((size_t)10 << 20));       // a slab would be 60 MB: the request itself
+    CHECK(a.held() == (size_t)70 << 20);
+    CHECK(a.get((size_t)30 << 20));
+    bool thrown = false;
+    try { a.get(256); } catch (int) { thrown = true; }
+    CHECK(thrown && a.held() == (size_t)100 << 20);
   }
   CHECK(Host::live.empty());
 """)
