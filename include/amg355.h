@@ -84,7 +84,7 @@ typedef struct {
   int flexible;        /* -1 (default): flexible beta iff the cycle is not FP64 or nu_pre != nu_post (the
                           preconditioner is then not a fixed symmetric operator); 0 standard; 1 flexible */
   int symmetric;       /* 1 (default): A = A^T, the adjoint reuses A's hierarchy and the coarsest level
-                          gets a Cholesky factorization.  0: A may be nonsymmetric (needs
+                          gets a Cholesky factorization (the levels above it use A as it is stored).  0: A may be nonsymmetric (needs
                           solver = AMG_SOLVER_BICGSTAB): LU with partial pivoting on the coarsest level;
                           the adjoint forms A^T and builds its hierarchy on first use */
   int check_every;     /* PCG iterations queued between convergence checks (default 0 = automatic) */

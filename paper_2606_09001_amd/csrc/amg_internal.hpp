@@ -349,6 +349,9 @@ struct Hierarchy {
   // levels lf .. run the two-sweep cycle (lf = number of levels: none)
   int lf = 1 << 30;
   Tail tail;
+  // whether A's pattern, and A's current values to rounding, are symmetric
+  // (looked at where the two-sweep levels would rest on it)
+  bool pattern_sym = true, values_sym = true;
   // solve workspace (level 0, FP64); BiCGSTAB adds r^, v, y, s, t
   DBuf<double> r, z, p, z2, q;
   DBuf<double> rh, bv, by, bs, bt2;

@@ -527,21 +527,28 @@ bool build_ell(Ell& E, int n, int64_t nnz, const int* rp1, const int* ci1, const
 }
 
 // D's values need the transposed entries of A unless the values are
-// symmetric: CG takes A = A^T; BiCGSTAB may be given any A.
-bool nonsym_values(const Hierarchy& H) { return !H.prm.symmetric || H.prm.solver != AMG_SOLVER_PCG; }
+// symmetric: BiCGSTAB may be given any A, and a CG handle's values (also the
+// preconditioner of another solver) are looked at.
+bool nonsym_values(const Hierarchy& H) {
+  return !H.prm.symmetric || H.prm.solver != AMG_SOLVER_PCG || !H.values_sym;
+}
+
+// Position of every entry's transpose; false when one is absent.
+bool build_tpos(Hierarchy& H, Level& L, hipStream_t s) {
+  L.tpos.alloc(L.nnz);
+  hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, (int64_t)1, 0, H.flags.p);
+  hipLaunchKernelGGL(k_tpos, dim3(blocks(L.n)), dim3(kBlock), 0, s, L.n, L.rp.p, L.ci.p, L.tpos.p, H.flags.p);
+  AMG_HIP(hipGetLastError());
+  AMG_HIP(hipMemcpyAsync(H.h_flags, H.flags.p, sizeof(int), hipMemcpyDeviceToHost, s));
+  AMG_HIP(hipStreamSynchronize(s));
+  return H.h_flags[0] == 0;
+}
 
 bool build_level_pattern(Hierarchy& H, int l, hipStream_t s) {
   Level& L = H.lv[l];
   const int nc = L.nagg;
   if (L.nnz + L.apnnz >= (int64_t)1 << 30) return false;
-  if (nonsym_values(H)) {
-    L.tpos.alloc(L.nnz);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, (int64_t)1, 0, H.flags.p);
-    hipLaunchKernelGGL(k_tpos, dim3(blocks(L.n)), dim3(kBlock), 0, s, L.n, L.rp.p, L.ci.p, L.tpos.p, H.flags.p);
-    AMG_HIP(hipMemcpyAsync(H.h_flags, H.flags.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    AMG_HIP(hipStreamSynchronize(s));
-    if (H.h_flags[0]) return false;  // structurally nonsymmetric
-  }
+  if (nonsym_values(H) && !build_tpos(H, L, s)) return false;  // structurally nonsymmetric
   if (!build_ell(L.up, L.n, L.nnz + L.apnnz, L.rp.p, L.ci.p, L.aprp.p, L.apci.p, s)) return false;
   {
     // transpose of the pattern of A P: a stable sort of its entries by column
@@ -621,6 +628,7 @@ template <class T, class RT>
 void level_values(Hierarchy& H, Level& L, const RT* pv, hipStream_t s) {
   const double* ap = L.apv.p;
   const dim3 b(kBlock);
+  const bool ns = nonsym_values(H);
   if constexpr (std::is_same<T, float>::value) {
     if (L.pmaps)
       hipLaunchKernelGGL((k_ap_map<RT, T>), dim3(blocks(L.apnnz)), b, 0, s, L.apnnz, L.apmo.p, L.apm.p, L.v32.p,
@@ -632,12 +640,12 @@ void level_values(Hierarchy& H, Level& L, const RT* pv, hipStream_t s) {
   }
   hipLaunchKernelGGL((k_q_values<RT, T>), dim3(blocks(L.n)), b, 0, s, L.n, L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p,
                      ap, level_sw<T>(L), L.qv.p);
-  if (L.dtv.p && L.pmaps) {
+  if (ns && L.pmaps) {
     hipLaunchKernelGGL((k_ap_map<RT, T>), dim3(blocks(L.apnnz)), b, 0, s, L.apnnz, L.apmo.p, L.apm.p, level_a<T>(L),
                        L.tpos.p, pv, L.dtv.p);
     hipLaunchKernelGGL((k_q_values<RT, T>), dim3(blocks(L.n)), b, 0, s, L.n, L.prp.p, L.pci.p, pv, L.aprp.p,
                        L.apci.p, L.dtv.p, level_sw<T>(L), L.dtv.p);
-  } else if (L.dtv.p)
+  } else if (ns)
     hipLaunchKernelGGL((k_dt_values<RT, T>), dim3(stride_grid((int64_t)L.n * kDtLanes, kBlock)), b, 0, s, L.n,
                        L.rp.p, L.ci.p, level_a<T>(L), L.tpos.p, L.prp.p, L.pci.p, pv, L.aprp.p, L.apci.p,
                        level_sw<T>(L), L.dtv.p);
@@ -646,7 +654,7 @@ void level_values(Hierarchy& H, Level& L, const RT* pv, hipStream_t s) {
                      ell_v<T>(L.up));
   hipLaunchKernelGGL((k_ell_values<false, T>), dim3(blocks(L.dn.slices, kBlock / 64)), b, 0, s, L.nagg, L.dn.slices,
                      L.dn.g, L.dn.off.p, L.dn.col.p, L.dn.src.p, (const T*)nullptr, (const T*)nullptr,
-                     L.dtv.p ? L.dtv.p : L.qv.p, ell_v<T>(L.dn));
+                     ns ? L.dtv.p : L.qv.p, ell_v<T>(L.dn));
   AMG_HIP(hipGetLastError());
 }
 
@@ -699,7 +707,8 @@ void tail_values(Hierarchy& H, hipStream_t s) {
     at ^= 1;
   }
   int lb = lx, cols = n;
-  auto dt = [](const Level& L) { return L.dtv.p ? L.dtv.p : L.qv.p; };
+  const bool ns = nonsym_values(H);
+  auto dt = [ns](const Level& L) { return ns ? L.dtv.p : L.qv.p; };
   while (lx - 1 >= top && H.lv[lx - 1].n <= kDenseRows) {
     Level& L = H.lv[lx - 1];
     double* Y = t.w[at].p;
@@ -772,6 +781,15 @@ void fused_levels(Hierarchy& H, bool build, hipStream_t s) {
       }
     }
   }
+  // values that were symmetric when the levels were built and are not any more
+  // (the pattern is symmetric then, on every level)
+  if (!build && nonsym_values(H))
+    for (int l = H.lf; l < nl - 1; ++l) {
+      Level& L = H.lv[l];
+      if (L.tpos.p) continue;
+      if (!build_tpos(H, L, s)) throw Error(AMG_ERR_HIP, "coarse pattern is not symmetric");
+      L.dtv.alloc(L.apnnz);
+    }
   if (H.fp32()) all_values<float>(H, s);
   else all_values<double>(H, s);
 }

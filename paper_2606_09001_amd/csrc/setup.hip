@@ -19,7 +19,7 @@
 namespace amg {
 namespace {
 
-enum : int { F_BAD = 1, F_ZERO_DIAG = 2, F_NONSYM = 4, F_NOAGG = 8, F_MISMATCH = 16 };
+enum : int { F_BAD = 1, F_ZERO_DIAG = 2, F_NONSYM = 4, F_NOAGG = 8, F_MISMATCH = 16, F_ASYM = 32 };
 enum : int8_t { S_UND = 0, S_ROOT = 1, S_EXCL = 2 };
 
 inline int grid_for(int64_t items, int per_block = kBlock) {
@@ -546,6 +546,30 @@ __device__ inline int find_col(const int* __restrict__ ci, int lo, int hi, int J
   return -1;
 }
 
+// Whether A = A^T to rounding: |a_ij - a_ji| within 64 units in the last place
+// of sqrt(a_ii a_jj) (1.4e-14: what assembling A may leave, and less than a
+// cycle's rounding).  8 lanes per row; flags F_ASYM, and F_NONSYM for an entry
+// without its mirror (looked for on both sides only with `pattern`).  A value
+// refresh of 128^3 7-point rows spends 0.11 of its 2.7 ms here.
+constexpr int kSymLanes = 8;
+__global__ void __launch_bounds__(kBlock) k_sym_values(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                       const double* __restrict__ v, const double* __restrict__ dinv,
+                                                       int pattern, int* flags) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  int found = 0;
+  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < (int64_t)n * kSymLanes; q += stride) {
+    const int i = (int)(q / kSymLanes), k1 = rp[i + 1];
+    for (int k = rp[i] + (int)(q % kSymLanes); k < k1; k += kSymLanes) {
+      const int j = ci[k];
+      if (j == i || (j < i && !pattern)) continue;
+      const int m = find_col(ci, rp[j], rp[j + 1], i);
+      if (m < 0) found |= F_NONSYM;
+      else if (j > i && !(fabs(v[k] - v[m]) * sqrt(fabs(dinv[i] * dinv[j])) <= 64 * 0x1p-52)) found |= F_ASYM;
+    }
+  }
+  if (found) atomicOr(flags, found);
+}
+
 // Smallest column > prev in the sorted list [lo, hi), or INT_MAX.
 __device__ inline int next_col(const int* __restrict__ ci, int lo, int hi, int prev) {
   int a = lo, b = hi;
@@ -1037,7 +1061,15 @@ int sys_shift(int S) {
 }
 unsigned sys_grid(int64_t items, int sh) { return stride_grid(items << sh, kBlock); }
 
-void level_numerics(Hierarchy& H, Level& L, hipStream_t s) {
+// CG's cycle takes A = A^T in its two-sweep levels (fused.hip).
+bool rests_on_symmetry(const Hierarchy& H) {
+  return H.S == 1 && H.prm.precondition && H.prm.symmetric && H.prm.solver == AMG_SOLVER_PCG && H.prm.nu_pre == 1 &&
+         H.prm.nu_post == 1;
+}
+
+// Level l's numerics; on level 0 also H.values_sym (with `build` H.pattern_sym).
+void level_numerics(Hierarchy& H, size_t l, bool build, hipStream_t s) {
+  Level& L = H.lv[l];
   const int S = H.S, sh = sys_shift(S);
   L.diagpos.alloc(L.n);
   L.dinv.alloc((int64_t)L.n * S);
@@ -1051,10 +1083,17 @@ void level_numerics(Hierarchy& H, Level& L, hipStream_t s) {
                      L.sw.p, H.fp32() ? L.sw32.p : nullptr, H.prm.omega, (int)(H.prm.smoother == AMG_SMOOTHER_L1),
                      H.flags.p, reinterpret_cast<unsigned long long*>(L.drho.p));
   AMG_HIP(hipGetLastError());
+  const bool look = l == 0 && rests_on_symmetry(H) && (build || (H.pattern_sym && H.lf + 1 < (int)H.lv.size()));
+  if (look)
+    hipLaunchKernelGGL(k_sym_values, dim3(stride_grid((int64_t)L.n * kSymLanes, kBlock)), dim3(kBlock), 0, s, L.n,
+                       L.rp.p, L.ci.p, L.v.p, L.dinv.p, (int)build, H.flags.p);
+  AMG_HIP(hipGetLastError());
   L.rhoS.resize(S);
   AMG_HIP(hipMemcpyAsync(L.rhoS.data(), L.drho.p, sizeof(double) * S, hipMemcpyDeviceToHost, s));
   sync_flags(H.flags.p, H.h_flags, 1, s);
   if (H.h_flags[0] & F_ZERO_DIAG) throw Error(AMG_ERR_ZERO_DIAG, "zero diagonal");
+  if (look && build) H.pattern_sym = !(H.h_flags[0] & F_NONSYM);
+  if (look) H.values_sym = H.pattern_sym && !(H.h_flags[0] & F_ASYM);
 }
 
 void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
@@ -1490,6 +1529,7 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   H.lv.clear();
   H.co = Coarse();
   H.tail = Tail();
+  H.pattern_sym = H.values_sym = true;
   for (DBuf<double>* b : {&H.r, &H.z, &H.p, &H.z2, &H.q, &H.partials}) b->release();
   H.ctl.release();
   H.arena.reset();
@@ -1509,7 +1549,7 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   }
   for (size_t l = 0;; ++l) {
     Level& L = H.lv[l];
-    level_numerics(H, L, s);
+    level_numerics(H, l, true, s);
     bool last = L.n <= H.prm.max_coarse || (int)(l + 1) >= H.prm.max_levels || !H.prm.precondition;
     if (!last) {
       strength_graph(H, L, s);
@@ -1604,7 +1644,7 @@ void refresh_hierarchy(Hierarchy& H, const double* d_val, hipStream_t s) {
   Level& L0 = H.lv[0];
   AMG_HIP(hipMemcpyAsync(L0.v.p, d_val, L0.v.bytes(), hipMemcpyDeviceToDevice, s));
   for (size_t l = 0; l < H.lv.size(); ++l) {
-    level_numerics(H, H.lv[l], s);
+    level_numerics(H, l, false, s);
     if (l + 1 == H.lv.size()) break;
     transfer_and_galerkin(H, l, false, s);
   }
