@@ -1092,14 +1092,15 @@ inline int wide_v(int W, int elem_bytes, int vmax) {
 inline int wide_lanes(int W, int V) { return pow2_ceil((W + V - 1) / V); }
 
 // br > 0: staged kernel with br rows per block; 0: direct kernel; the split
-// kernel instead of either where rows are few and long (wide_parts).
+// kernel instead of either where rows are few and long (wide_parts) and the
+// operator reduces nothing, unless split is false.
 template <int V, class Op>
 int wsweep_v(int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op,
-             const BatchHead* head, double* partials, hipStream_t s) {
+             const BatchHead* head, double* partials, hipStream_t s, bool split) {
   const int LWv = wide_lanes(W, V);
   int grid = 0;
   if constexpr (Op::NRED == 0) {
-    const int parts = wide_parts(n, nnz, kBlock / LWv);
+    const int parts = split ? wide_parts(n, nnz, kBlock / LWv) : 1;
     if (parts > 1) {
       const int rows = kBlock / LWv / parts;
       grid = std::min((n + rows - 1) / rows, kWGrid);
@@ -1135,14 +1136,14 @@ int wsweep_v(int spx, int br, int n, int64_t nnz, int W, const int* rp, const in
 // operator aligned to 16 bytes unless vmax = 1).
 template <class Op>
 int wsweep(int vmax, int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op,
-           const BatchHead* head, double* partials, hipStream_t s) {
+           const BatchHead* head, double* partials, hipStream_t s, bool split = true) {
   constexpr int eb = (int)sizeof(typename Op::GT);
   const int v = wide_v(W, eb, vmax);
   if constexpr (eb == 4) {
-    if (v == 4) return wsweep_v<4>(spx, br, n, nnz, W, rp, ci, op, head, partials, s);
+    if (v == 4) return wsweep_v<4>(spx, br, n, nnz, W, rp, ci, op, head, partials, s, split);
   }
-  if (v >= 2) return wsweep_v<2>(spx, br, n, nnz, W, rp, ci, op, head, partials, s);
-  return wsweep_v<1>(spx, br, n, nnz, W, rp, ci, op, head, partials, s);
+  if (v >= 2) return wsweep_v<2>(spx, br, n, nnz, W, rp, ci, op, head, partials, s, split);
+  return wsweep_v<1>(spx, br, n, nnz, W, rp, ci, op, head, partials, s, split);
 }
 
 std::vector<int> host_rows(const DBuf<int>& rp, int n) {
@@ -1338,12 +1339,12 @@ void read_batch(Hierarchy& H, int W, hipStream_t s) {
 // operands and the fastest is kept and recorded in the tuning cache.
 
 template <class Op>
-double time_wide(int Vc, int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op, hipStream_t s,
-                 hipEvent_t e0, hipEvent_t e1) {
-  wsweep(Vc, spx, br, n, nnz, W, rp, ci, op, nullptr, nullptr, s);
+double time_wide(int Vc, int spx, int br, int n, int64_t nnz, int W, const int* rp, const int* ci, const Op& op,
+                 hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  wsweep(Vc, spx, br, n, nnz, W, rp, ci, op, nullptr, nullptr, s, false);
   AMG_HIP(hipEventRecord(e0, s));
   constexpr int reps = 3;
-  for (int r = 0; r < reps; ++r) wsweep(Vc, spx, br, n, nnz, W, rp, ci, op, nullptr, nullptr, s);
+  for (int r = 0; r < reps; ++r) wsweep(Vc, spx, br, n, nnz, W, rp, ci, op, nullptr, nullptr, s, false);
   AMG_HIP(hipEventRecord(e1, s));
   AMG_HIP(hipEventSynchronize(e1));
   float ms = 0.f;
@@ -1361,19 +1362,25 @@ std::vector<int> spx_candidates() {
 }
 
 // Picks the kernel form (staged with `br` rows per block, or direct) and the
-// stream count of one wide sweep; returns the stream count and sets br.
+// stream count of one wide sweep; returns the stream count and sets br.  The
+// split kernel has neither: where an operator's sweeps take it there is nothing
+// to pick, except for the level-0 matrix (`reducing`: its products and residuals
+// with sums take the other forms), recorded under a key of its own.
 template <class Op>
 int pick_spx(Hierarchy& H, const char* kind, int W, int& br, int n, int nnz, const int* rp, const int* ci,
-             const Op& op, hipStream_t s) {
+             const Op& op, bool reducing, hipStream_t s) {
+  const int Vc = 4;
+  const int lanes = wide_lanes(W, wide_v(W, (int)sizeof(typename Op::GT), Vc));
+  const bool split = wide_parts(n, nnz, kBlock / lanes) > 1;
+  if (split && !reducing) return 0;
   char key[160];
-  std::snprintf(key, sizeof key, "wide%s:n%d:nnz%d:W%d:S%d:p%d:t%d:br%d", kind, n, nnz, W, H.S, H.prm.vcycle_prec,
-                H.fp32() && H.prm.transfer_bf16, br);
+  std::snprintf(key, sizeof key, "wide%s:n%d:nnz%d:W%d:S%d:p%d:t%d:br%d%s", kind, n, nnz, W, H.S, H.prm.vcycle_prec,
+                H.fp32() && H.prm.transfer_bf16, br, split ? ":red" : "");
   Shape sh;
   if (tune_lookup(key, &sh)) {
     br = sh.g ? br : 0;
     return sh.stream;
   }
-  const int Vc = 4;
   hipEvent_t e0, e1;
   AMG_HIP(hipEventCreate(&e0));
   AMG_HIP(hipEventCreate(&e1));
@@ -1435,22 +1442,22 @@ void tune_wide(Hierarchy& H, int W, hipStream_t s) {
     BatchLevel& BL = B.lv[l];
     BatchLevel& BN = B.lv[l + 1];
     BL.spxA = pick_spx(H, "A", W, BL.brA, L.n, (int)L.nnz, L.rp.p, L.ci.p,
-                       WResid<SYS, T, T>{WB<T>::v(L), WB<T>::b(BL), WB<T>::x(BL), WB<T>::r(BL), W}, s);
+                       WResid<SYS, T, T>{WB<T>::v(L), WB<T>::b(BL), WB<T>::x(BL), WB<T>::r(BL), W}, l == 0, s);
     if constexpr (std::is_same<T, double>::value) {
       BL.spxP = pick_spx(H, "P", W, BL.brP, L.n, (int)L.pnnz, L.prp.p, L.pci.p,
-                         WProlong<SYS, double, T>{L.pv.p, WB<T>::x(BN), WB<T>::r(BL), W}, s);
+                         WProlong<SYS, double, T>{L.pv.p, WB<T>::x(BN), WB<T>::r(BL), W}, false, s);
       BL.spxR = pick_spx(H, "R", W, BL.brR, L.nagg, (int)L.pnnz, L.rrp.p, L.rci.p,
-                         WRestrict<SYS, double, T>{L.rv.p, WB<T>::x(BL), WB<T>::b(BN), nullptr, nullptr, W}, s);
+                         WRestrict<SYS, double, T>{L.rv.p, WB<T>::x(BL), WB<T>::b(BN), nullptr, nullptr, W}, false, s);
     } else if (H.bf16()) {
       BL.spxP = pick_spx(H, "P", W, BL.brP, L.n, (int)L.pnnz, L.prp.p, L.pci.p,
-                         WProlong<SYS, uint16_t, T>{L.pbf.p, WB<T>::x(BN), WB<T>::r(BL), W}, s);
+                         WProlong<SYS, uint16_t, T>{L.pbf.p, WB<T>::x(BN), WB<T>::r(BL), W}, false, s);
       BL.spxR = pick_spx(H, "R", W, BL.brR, L.nagg, (int)L.pnnz, L.rrp.p, L.rci.p,
-                         WRestrict<SYS, uint16_t, T>{L.rbf.p, WB<T>::x(BL), WB<T>::b(BN), nullptr, nullptr, W}, s);
+                         WRestrict<SYS, uint16_t, T>{L.rbf.p, WB<T>::x(BL), WB<T>::b(BN), nullptr, nullptr, W}, false, s);
     } else {
       BL.spxP = pick_spx(H, "P", W, BL.brP, L.n, (int)L.pnnz, L.prp.p, L.pci.p,
-                         WProlong<SYS, float, T>{L.pv32.p, WB<T>::x(BN), WB<T>::r(BL), W}, s);
+                         WProlong<SYS, float, T>{L.pv32.p, WB<T>::x(BN), WB<T>::r(BL), W}, false, s);
       BL.spxR = pick_spx(H, "R", W, BL.brR, L.nagg, (int)L.pnnz, L.rrp.p, L.rci.p,
-                         WRestrict<SYS, float, T>{L.rv32.p, WB<T>::x(BL), WB<T>::b(BN), nullptr, nullptr, W}, s);
+                         WRestrict<SYS, float, T>{L.rv32.p, WB<T>::x(BL), WB<T>::b(BN), nullptr, nullptr, W}, false, s);
     }
   }
   AMG_HIP(hipStreamSynchronize(s));
