@@ -346,7 +346,7 @@ struct Hierarchy {
   int64_t nnz = 0;
   std::vector<Level> lv;
   Coarse co;
-  // levels lf .. run the two-sweep cycle (lf = number of levels: none)
+  // levels lf .. run the two-sweep cycle (lf = the coarsest: only the dense end)
   int lf = 1 << 30;
   Tail tail;
   // whether A's pattern, and A's current values to rounding, are symmetric

@@ -14,9 +14,10 @@
 // reduction) of 2-5 us whatever its bytes, so halving the sweeps halves the
 // time; on the coarse levels of large systems D and Q hold 0.4 entries per
 // entry of A, so the two sweeps also move fewer bytes than the four (128^3
-// Poisson, level 1: 133 against 172 MB).  On a large level 0 the A P rows
-// (8 entries against 7 of A) make both forms move the same bytes, and the
-// four-sweep form keeps its offset-form matrix: see fuse_from.
+// Poisson, level 1: 161 against 172 MB, of which 28 are padding of the rows of
+// `up` and `dn`).  On a large level 0 the A P rows (8 entries against 7 of A)
+// make both forms move the same bytes, and the four-sweep form keeps its
+// offset-form matrix: see kFuse0.
 //
 // The sweep kernel reads rows in the sliced form of struct Ell: the only
 // loads ahead of the entries are the slice's offset and the done flag
@@ -40,7 +41,9 @@ constexpr int64_t kDenseE = 1 << 19;  // most entries of the dense product E = X
 // (time per CG iteration, two-sweep against four-sweep level 0, FP64: 2D 181^2
 // (0.4 M entries) 36 against 42 us, 2D 700^2 (6.6 M) 69 against 78, 2D 900^2
 // (11 M) 101 against 97; 3D 40^3 (1.5 M) 45 against 49, 64^3 (6.0 M) 62 against
-// 61, 80^3 (12 M) 98 against 85).
+// 61, 80^3 (12 M) 98 against 85).  The line is where 3D systems break even; by
+// entries alone 2D systems from there to about 9 M keep the slower four sweeps
+// (700^2: a tenth).
 constexpr int64_t kFuse0 = 6000000;
 
 __device__ inline int block_of_xcd() {

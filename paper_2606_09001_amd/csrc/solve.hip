@@ -13,9 +13,10 @@
 // Workgroups are renumbered so that each XCD (round-robin dispatch over the
 // 8 XCDs) owns one contiguous range of rows, which keeps neighbour gathers
 // in that XCD's L2.  Dot products are fused into the producing sweep as one
-// partial per workgroup (plain stores); a single-workgroup finalize kernel
-// folds the partials in a fixed order and forms the CG scalars on the
-// device, so there are no float atomics and no device-wide fences.
+// partial per workgroup (plain stores); the kernels that need them fold them in
+// a fixed order, or read the totals of one k_sum launch where they are many, and
+// form the CG scalars on the device, so there are no float atomics and no
+// device-wide fences.
 // Method: PCG from x0 = 0 with recursive-residual stopping, true-residual
 // verification and restart; damped-Jacobi/L1 V(nu_pre, nu_post) cycle with
 // R = P^T and an exact coarsest solve.  The FP32 cycle keeps CG vectors, dot
