@@ -195,7 +195,7 @@ struct Level {
   int mis_rounds = 0;
   double rho = 0.0, omegaP = 0.0;            // system 0
   std::vector<double> rhoS, omegaPS;         // per system
-  DBuf<double> drho;                         // rhoS on the device
+  DBuf<double> drho;                         // rhoS on the device; then the flags of the level's numerics
   // prolongator / restriction
   int64_t pnnz = 0;
   DBuf<int> prp, pci, rrp, rci, rperm;
@@ -335,6 +335,9 @@ struct Graphs {
   ~Graphs();
 };
 
+constexpr int kUniformFlags = 16, kFlagInts = 64;
+static_assert(kUniformFlags + AMG_MAX_LEVELS + 1 <= kFlagInts, "a flag per level");
+
 struct Hierarchy {
   Arena arena;  // buffers of the levels, the coarsest solve and the solve workspace (which go before it)
   amg_params prm{};
@@ -364,8 +367,12 @@ struct Hierarchy {
   DBuf<double> partials;
   DBuf<Ctl> ctl;
   Ctl* h_ctl = nullptr;  // pinned host mirror
-  DBuf<int> flags;       // device error flags / counters
+  // device error flags / counters and their pinned mirror: the first 16 belong
+  // to the step at hand, kUniformFlags + l to level l's uniform slots; h_rho
+  // (pinned, behind them) takes a level's bounds and flags
+  DBuf<int> flags;
   int* h_flags = nullptr;
+  double* h_rho = nullptr;
   // cache bookkeeping
   uint64_t key = 0;
   int refs = 0;
@@ -381,6 +388,7 @@ struct Hierarchy {
   double setup_ms = 0.0;
   bool fp32() const { return prm.vcycle_prec == AMG_PREC_FP32; }
   bool bf16() const { return fp32() && prm.transfer_bf16; }
+  void alloc_flags();
   ~Hierarchy();
 };
 

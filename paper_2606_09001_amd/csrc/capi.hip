@@ -49,6 +49,13 @@ Hierarchy::~Hierarchy() {
   if (bt.h_mask) (void)hipHostFree(bt.h_mask);
 }
 
+void Hierarchy::alloc_flags() {
+  flags.alloc(kFlagInts);
+  AMG_HIP(hipHostMalloc((void**)&h_flags, sizeof(int) * kFlagInts + sizeof(double) * (kMaxWidth + 1),
+                        hipHostMallocDefault));
+  h_rho = reinterpret_cast<double*>(h_flags + kFlagInts);
+}
+
 namespace {
 
 std::mutex g_mu;
@@ -233,8 +240,7 @@ Hierarchy& adjoint_hierarchy(Hierarchy& H, hipStream_t s) {
     A->n = H.n;
     A->nnz = H.nnz;
     A->lv.reserve(AMG_MAX_LEVELS + 1);
-    A->flags.alloc(16);
-    AMG_HIP(hipHostMalloc((void**)&A->h_flags, 64, hipHostMallocDefault));
+    A->alloc_flags();
     build_hierarchy(*A, H.trp.p, H.tci.p, H.tval.p, s);
     A->cache_event = AMG_CACHE_COLD;
     A->setup_ms = ms_since(t0);
@@ -344,8 +350,7 @@ amg_status amg_setup(const amg_params* params, int32_t n, int64_t nnz, const int
     H->nnz = nnz;
     H->lv.reserve(AMG_MAX_LEVELS + 1);
     try {
-      H->flags.alloc(16);
-      AMG_HIP(hipHostMalloc((void**)&H->h_flags, 64, hipHostMallocDefault));
+      H->alloc_flags();
       build_hierarchy(*H, d_row_ptr, d_col, d_val, stream);
     } catch (...) {
       (void)hipStreamSynchronize(stream);
@@ -383,8 +388,7 @@ amg_status amg_update_values(amg_handle h, const double* d_val, hipStream_t stre
       N->n = H->n;
       N->nnz = H->nnz;
       N->lv.reserve(AMG_MAX_LEVELS + 1);
-      N->flags.alloc(16);
-      AMG_HIP(hipHostMalloc((void**)&N->h_flags, 64, hipHostMallocDefault));
+      N->alloc_flags();
       try {
         build_hierarchy(*N, H->lv[0].rp.p, H->lv[0].ci.p, d_val, stream);
       } catch (...) {

@@ -362,7 +362,6 @@ void coarse_setup(Hierarchy& H, hipStream_t s) {
                        C.inv.p, C.inv32.p);
   }
   AMG_HIP(hipGetLastError());
-  AMG_HIP(hipStreamSynchronize(s));
 }
 
 }  // namespace amg

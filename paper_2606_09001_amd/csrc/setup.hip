@@ -1074,26 +1074,28 @@ void level_numerics(Hierarchy& H, size_t l, bool build, hipStream_t s) {
   L.diagpos.alloc(L.n);
   L.dinv.alloc((int64_t)L.n * S);
   L.sw.alloc((int64_t)L.n * S);
-  L.drho.alloc(S);
+  L.drho.alloc(S + 1);
+  int* flags = reinterpret_cast<int*>(L.drho.p + S);
   if (H.fp32()) L.sw32.alloc((int64_t)L.n * S);
-  zero_flags(H.flags.p, 1, s);
   AMG_HIP(hipMemsetAsync(L.drho.p, 0, L.drho.bytes(), s));
   const int grid = (int)std::min<int64_t>(sys_grid(L.n, sh), 8192);
   hipLaunchKernelGGL(k_diag, dim3(grid), dim3(kBlock), 0, s, L.n, S, sh, L.rp.p, L.ci.p, L.v.p, L.diagpos.p, L.dinv.p,
                      L.sw.p, H.fp32() ? L.sw32.p : nullptr, H.prm.omega, (int)(H.prm.smoother == AMG_SMOOTHER_L1),
-                     H.flags.p, reinterpret_cast<unsigned long long*>(L.drho.p));
+                     flags, reinterpret_cast<unsigned long long*>(L.drho.p));
   AMG_HIP(hipGetLastError());
   const bool look = l == 0 && rests_on_symmetry(H) && (build || (H.pattern_sym && H.lf + 1 < (int)H.lv.size()));
   if (look)
     hipLaunchKernelGGL(k_sym_values, dim3(stride_grid((int64_t)L.n * kSymLanes, kBlock)), dim3(kBlock), 0, s, L.n,
-                       L.rp.p, L.ci.p, L.v.p, L.dinv.p, (int)build, H.flags.p);
+                       L.rp.p, L.ci.p, L.v.p, L.dinv.p, (int)build, flags);
   AMG_HIP(hipGetLastError());
-  L.rhoS.resize(S);
-  AMG_HIP(hipMemcpyAsync(L.rhoS.data(), L.drho.p, sizeof(double) * S, hipMemcpyDeviceToHost, s));
-  sync_flags(H.flags.p, H.h_flags, 1, s);
-  if (H.h_flags[0] & F_ZERO_DIAG) throw Error(AMG_ERR_ZERO_DIAG, "zero diagonal");
-  if (look && build) H.pattern_sym = !(H.h_flags[0] & F_NONSYM);
-  if (look) H.values_sym = H.pattern_sym && !(H.h_flags[0] & F_ASYM);
+  AMG_HIP(hipMemcpyAsync(H.h_rho, L.drho.p, L.drho.bytes(), hipMemcpyDeviceToHost, s));
+  AMG_HIP(hipStreamSynchronize(s));
+  L.rhoS.assign(H.h_rho, H.h_rho + S);
+  int found;
+  std::memcpy(&found, H.h_rho + S, sizeof(int));
+  if (found & F_ZERO_DIAG) throw Error(AMG_ERR_ZERO_DIAG, "zero diagonal");
+  if (look && build) H.pattern_sym = !(found & F_NONSYM);
+  if (look) H.values_sym = H.pattern_sym && !(found & F_ASYM);
 }
 
 void strength_graph(Hierarchy& H, Level& L, hipStream_t s) {
@@ -1375,8 +1377,11 @@ void precision_copies(Hierarchy& H, hipStream_t s) {
 // Sliced copies of the levels whose rows are short (longest row at most
 // kSellMaxW, padding at most 1/8 of the nonzeros; one system only).  The
 // pattern part is built once; values are gathered again on every refresh.
+// Which offset-form operators are uniform is found with the next
+// synchronization (uniform_slots).
 void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
   if (H.S != 1) return;
+  AMG_HIP(hipMemsetAsync(H.flags.p + kUniformFlags, 0, sizeof(int) * H.lv.size(), s));
   for (size_t l = 0; l < H.lv.size(); ++l) {
     Level& L = H.lv[l];
     if (build) {
@@ -1454,15 +1459,25 @@ void sliced_copies(Hierarchy& H, bool build, hipStream_t s) {
         AMG_HIP(hipMemsetAsync(L.suv.p, 0, L.suv.bytes(), s));
         if (H.fp32()) AMG_HIP(hipMemsetAsync(L.suv32.p, 0, L.suv32.bytes(), s));
       }
-      zero_flags(H.flags.p, 1, s);
       hipLaunchKernelGGL(k_sell_uniform, dim3((ns + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, s, ns,
-                         L.soff.p, L.sslot.p, L.sv.p, L.suv.p, H.fp32() ? L.suv32.p : nullptr, H.flags.p);
-      sync_flags(H.flags.p, H.h_flags, 1, s);
-      L.sell_uniform = H.h_flags[0] == 0;
-      if (!build) L.shA.stream = L.sell_uniform ? 4 : 3;
+                         L.soff.p, L.sslot.p, L.sv.p, L.suv.p, H.fp32() ? L.suv32.p : nullptr,
+                         H.flags.p + kUniformFlags + l);
     }
   }
   AMG_HIP(hipGetLastError());
+  AMG_HIP(hipMemcpyAsync(H.h_flags + kUniformFlags, H.flags.p + kUniformFlags, sizeof(int) * H.lv.size(),
+                         hipMemcpyDeviceToHost, s));
+}
+
+// What sliced_copies found, once the stream has been waited for.
+void uniform_slots(Hierarchy& H, bool build) {
+  if (H.S != 1) return;
+  for (size_t l = 0; l < H.lv.size(); ++l) {
+    Level& L = H.lv[l];
+    if (!L.sell || L.sell_form != 2) continue;
+    L.sell_uniform = H.h_flags[kUniformFlags + l] == 0;
+    if (!build) L.shA.stream = L.sell_uniform ? 4 : 3;
+  }
 }
 
 void alloc_cycle_vectors(Hierarchy& H) {
@@ -1567,6 +1582,8 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   precision_copies(H, s);
   sliced_copies(H, true, s);
   fused_levels(H, true, s);
+  AMG_HIP(hipStreamSynchronize(s));
+  uniform_slots(H, true);
   alloc_cycle_vectors(H);
   choose_shapes(H, s);
   alloc_solve_workspace(H);
@@ -1653,6 +1670,7 @@ void refresh_hierarchy(Hierarchy& H, const double* d_val, hipStream_t s) {
   sliced_copies(H, false, s);
   fused_levels(H, false, s);
   AMG_HIP(hipStreamSynchronize(s));
+  uniform_slots(H, false);
 }
 
 }  // namespace amg
