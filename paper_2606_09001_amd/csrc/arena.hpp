@@ -26,8 +26,9 @@ class ArenaOf {
     for (Slab& s : slabs_) Mem::give(s.p);
   }
   // 256-byte aligned: a hole that something given back has left, the end of a
-  // slab, or a new slab.  Slabs grow with what is already held (2 to 256 MB, or
-  // the request itself); where that cannot be had, one of the request's size.
+  // slab, or a new slab: of what is expected and not held yet, then a quarter of
+  // what is held (2 to 256 MB, or the request itself); where that cannot be had,
+  // one of the request's size.
   void* get(size_t bytes) {
     bytes = round(bytes);
     for (Slab& s : slabs_) {
@@ -45,7 +46,8 @@ class ArenaOf {
         return q;
       }
     }
-    const size_t cap = std::max(bytes, std::min(std::max(held(), kMinSlab), kMaxSlab));
+    const size_t h = held(), grow = expected_ > h ? expected_ - h : expected_ ? h / 4 : h;
+    const size_t cap = std::max(bytes, std::min(std::max(grow, kMinSlab), kMaxSlab));
     slabs_.emplace_back();
     Slab& s = slabs_.back();
     try {
@@ -59,6 +61,12 @@ class ArenaOf {
     s.used = bytes;
     return s.p;
   }
+  // How much will be asked for in all.  From about 16 MB on a slab's allocation
+  // and free take 0.2 to 0.5 ms whatever its size: doubling from 2 to the 134 MB
+  // of a 300^2 hierarchy, and its setup's temporaries likewise, took 11 slabs and
+  // 6.5 ms for a setup (with one allocation per buffer 5.0); two slabs of the sizes
+  // expected 3.8.
+  void expect(size_t bytes) { expected_ = round(bytes); }
   // Takes back what get(bytes) returned.
   void put(void* q, size_t bytes) noexcept {
     bytes = round(bytes);
@@ -117,6 +125,7 @@ class ArenaOf {
     std::vector<Hole> holes;  // given back below `used`, by address
   };
   std::vector<Slab> slabs_;
+  size_t expected_ = 0;
 };
 
 }  // namespace amg

@@ -113,3 +113,29 @@ def test_a_slab_that_cannot_be_had_leaves_the_request(tmp_path):
   }
   CHECK(Host::live.empty());
 """)
+
+
+def test_expected_sizes_take_one_slab(tmp_path):
+    _run(tmp_path, r"""
+  {
+    A a;
+    a.expect((size_t)40 << 20);
+    for (int i = 0; i < 40; ++i) a.get((size_t)1 << 20);
+    CHECK(Host::live.size() == 1 && a.held() == (size_t)40 << 20);
+    a.get(1000);                          // beyond: a quarter of what is held
+    CHECK(Host::live.size() == 2 && a.held() == (size_t)50 << 20);
+  }
+  {
+    A b;
+    b.expect((size_t)600 << 20);          // in slabs of at most 256 MB
+    for (int i = 0; i < 58; ++i) b.get((size_t)10 << 20);
+    CHECK(Host::live.size() == 3 && b.held() == (size_t)600 << 20);
+  }
+  {
+    A c;
+    c.expect(1000);                       // at least 2 MB
+    c.get(100);
+    CHECK(c.held() == (size_t)2 << 20);
+  }
+  CHECK(Host::live.empty());
+""")
