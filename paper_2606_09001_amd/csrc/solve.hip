@@ -79,10 +79,19 @@ inline int round8(int64_t g) {
 // combined after its gathers (fold_total), in one fixed order, so that every
 // workgroup holds the same bits.  In larger solves the workgroups that would do
 // so are too many (128^3: 8192 of 16 KB and two barriers each, 7.3 against 6.9
-// ms): a launch of k_sum forms the totals first (two per CG iteration where the
-// finalize kernels took three), and the consumers read one value per sum (tot).
+// ms): launches of k_sum form the totals first, and the consumers read one value
+// per sum (tot): two per CG iteration.  In still larger ones (kEarlyStop) a third
+// sums the update (BiCGSTAB: the half step) at once and makes its stop test, so
+// that the cycle that follows is not run for nothing.
 // (Fewer and longer workgroups, several row blocks each, keep the partials few
 // but overlap less: 192^3 mixed 25.8 against 23.6 ms.)
+
+// Rows from which the stop test has a launch of its own ahead of the cycle: 2.7
+// us an iteration against a cycle a solve.  Solves to 1e-1 (2 iterations) and 1e-8
+// (33 to 48), ms without and with it: 192^3 FP32 cycle 1.94 1.52, 22.5 22.2; 128^3
+// 0.87 0.71, 8.60 8.52; 96^3 FP32 cycle 0.39 0.35, 2.97 3.05; 900^2 0.60 0.61 (5
+// iterations), 4.39 4.52.
+constexpr int kEarlyStop = 3 << 19;
 
 struct NoFold {};
 
@@ -1122,6 +1131,46 @@ __global__ void __launch_bounds__(kFinBlock) k_sum(SumArgs a, double* __restrict
   if (threadIdx.x == 0) out[blockIdx.x] = t[0];
 }
 
+// The same for ||r||^2 of CG's update (of parity par), with its stop test: the
+// outcome the next product would find.  One workgroup: the flag is written
+// after all its waves have read it.
+__global__ void __launch_bounds__(kFinBlock) k_sum_update(const double* __restrict__ pu, int np,
+                                                          double* __restrict__ out, Ctl* ctl, int par) {
+  if (ctl->done) return;
+  double t[1];
+  fold_partials<1>(pu, np, t);
+  if (threadIdx.x != 0) return;
+  const double rr = t[0];
+  out[0] = rr;
+  const int it = ctl->it2[par ^ 1] + 1;
+  const int st = rr <= ctl->thresh ? 1 : !(rr == rr) ? -1 : it >= ctl->maxiter ? 2 : 0;
+  if (st) {
+    ctl->rr = rr;
+    ctl->iters = it;
+    ctl->state = st;
+    ctl->done = 1;
+  }
+}
+
+// The same for ||s||^2 of BiCGSTAB's half step: the outcome k_bi_full would
+// find (which counts the step otherwise).
+__global__ void __launch_bounds__(kFinBlock) k_sum_half(const double* __restrict__ ps, int np,
+                                                        double* __restrict__ out, Ctl* ctl) {
+  if (ctl->gate[1]) return;
+  double t[1];
+  fold_partials<1>(ps, np, t);
+  if (threadIdx.x != 0) return;
+  const double ss = t[0];
+  out[0] = ss;
+  const int st = ss <= ctl->thresh ? 1 : !(ss == ss) ? -1 : 0;
+  if (st) {
+    ctl->rr = ss;
+    ctl->iters += 1;
+    ctl->state = st;
+    ctl->gate[1] = 1;
+  }
+}
+
 __global__ void __launch_bounds__(kFinBlock) k_fin_init(Ctl* ctl, const double* __restrict__ partials, int np,
                                                         double tol, int maxiter, int flexible, double* x) {
   double t[1];
@@ -2060,7 +2109,7 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
   const int64_t region = partials_region(H);
   double* pu = part + region;
   double* pz = part + 2 * region;
-  const bool tot = region > kFoldMax;
+  const bool tot = region > kFoldMax, early = tot && n >= kEarlyStop;
   double* pt = part + 4 * region;   // totals: product; update and V-cycle
   Sums start{pz, 0, 1};             // <r, z> as the first product after a (re)start reads it
   int npz = 0;
@@ -2103,12 +2152,14 @@ amg_status pcg_solve(Hierarchy& H, const SolveOpts& o, const SolveWork& w, const
       else launch_cg_update<double>(H, w, n, pb[c ^ 1], a.p, a.np, tot, pu, c, st);
     }
     u = Sums{pu, gu, 1};
-    if (plain) {
-      total(tot, {&u}, pt + 1, done, st);
-    } else {
+    if (early) hipLaunchKernelGGL(k_sum_update, dim3(1), dim3(kFinBlock), 0, st, pu, gu, pt + 1, ctl, c);
+    if (!plain) {
       vcycle(H, CycleArgs{w.r, w.z, w.q, done, pz, nv, multi ? 1 : 0}, st);
       z = Sums{pz, npz, nv};
-      total(tot, {&u, &z}, pt + 1, done, st);
+      if (early) total(tot, {&z}, pt + 2, done, st);
+      else total(tot, {&u, &z}, pt + 1, done, st);
+    } else if (!early) {
+      total(tot, {&u}, pt + 1, done, st);
     }
   };
   // two iterations captured once per direction-buffer parity and replayed
@@ -2274,7 +2325,7 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
   double* ps = part + region;       // <s, s>
   double* pt = part + 2 * region;   // <s, t>, <t, t>
   double* pf = part + 4 * region;   // <r, r>, <r^, r>
-  const bool tot = region > kFoldMax;
+  const bool tot = region > kFoldMax, early = tot && n >= kEarlyStop;
   double* ptot = part + 6 * region;  // totals
   Sums full{pf, gu, 2};             // as the direction update reads them
   totals_at(tot, {&full}, ptot + 4);
@@ -2318,13 +2369,19 @@ amg_status bicgstab_solve(Hierarchy& H, const SolveOpts& o, const double* d_b, d
     Sums a{part, np, 1};
     total(tot, {&a}, ptot, gate, st);
     launch_half(a, st);
+    if (early) hipLaunchKernelGGL(k_sum_half, dim3(1), dim3(kFinBlock), 0, st, ps, gu, ptot + 1, ctl);
     if (prec) vcycle(H, CycleArgs{sv, z, nullptr, gate + 1, part, 0, x0w ? 1 : 0}, st);
     {
       InstScope is(H, KID_SPMV_DOT, 0, st, gate + 1);
       np = sweep(L0.shA, n, L0.arp(), L0.aci(), OpSpmvDots<2>{L0.av(), z, t, sv}, gate + 1, pt, st);
     }
     Sums h{ps, gu, 1}, tt{pt, np, 2}, f{pf, gu, 2};
-    total(tot, {&h, &tt}, ptot + 1, gate + 1, st);
+    if (early) {
+      totals_at(tot, {&h}, ptot + 1);
+      total(tot, {&tt}, ptot + 2, gate + 1, st);
+    } else {
+      total(tot, {&h, &tt}, ptot + 1, gate + 1, st);
+    }
     hipLaunchKernelGGL(k_bi_full, dim3(gu), dim3(kBlock), 0, st, n, z, sv, t, rh, r, ctl, h.p, h.np, tt.p, tt.np, tot, pf);
     total(tot, {&f}, ptot + 4, done, st);
   };

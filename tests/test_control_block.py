@@ -51,3 +51,15 @@ def test_product_sweep_does_not_write_what_it_reads():
     # the sweep around it returns on this flag
     assert "done" not in writes
     assert re.search(r"sweep\([^;]*OpSpmvXpay\{[^}]*\}, done,", text), "the product's stop flag"
+
+
+@pytest.mark.parametrize("kernel", ["k_sum_update", "k_sum_half", "k_fin_chunk", "k_bfin_chunk"])
+def test_kernels_that_test_and_set_a_flag_are_one_workgroup(kernel):
+    text = _source()
+    reads, writes = _fields(_body(text, f" {kernel}("))
+    assert reads & writes <= {"done", "gate[1]"}
+    launches = re.findall(rf"hipLaunchKernelGGL\({kernel}, (dim3\(\w+\)), (dim3\(\w+\))", text)
+    assert launches and set(launches) == {("dim3(1)", "dim3(kFinBlock)")}
+    # set by one thread, after the barrier inside fold_partials
+    body = _body(text, f" {kernel}(")
+    assert body.index("fold_partials") < body.index("if (threadIdx.x != 0) return;") < body.rindex("= 1;")
