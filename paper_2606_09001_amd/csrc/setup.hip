@@ -1550,10 +1550,12 @@ void build_hierarchy(Hierarchy& H, const int* d_rp, const int* d_ci, const doubl
   H.arena.reset();
   Arena scratch;
   // measured: 165 to 280 bytes per entry of A (grids, 2D and 3D, level 0 in both
-  // forms), 26 to 41 more for every further system, 54 without a hierarchy;
-  // temporaries 10 to 32
-  H.arena.expect((size_t)H.nnz * (H.prm.precondition ? 200 + 32 * (size_t)H.S : 54));
-  scratch.expect(H.prm.precondition ? 32 * (size_t)H.nnz : 0);
+  // forms), 26 to 41 more for every further system; temporaries 10 to 32.  Without
+  // a hierarchy A, its sliced copy where rows are short, and vectors.
+  const size_t nz = (size_t)H.nnz, rows = (size_t)H.n;
+  H.arena.expect(H.prm.precondition ? nz * (200 + 32 * (size_t)H.S)
+                                    : nz * (nz <= kSellMaxW * rows ? 36 : 12) + 64 * rows);
+  scratch.expect(H.prm.precondition ? 32 * nz : 0);
   Arena::Use use(&H.arena, &scratch);
   H.lv.emplace_back();
   {
